@@ -123,6 +123,20 @@ DevParams derive(const dpps_params *p)
     P.c_hfast = 0.0f;
     P.c_pfast = (float)lam2;
     P.half_ar = (float)(0.5 * ar);
+    // time to q / 4 of a path of 1 m for the kick that stops at its end
+    for (int q = 0; q < 4; ++q) {
+        const double s = 0.25 * (q + 1);
+        const double v = 1.0 / sqrt(cD), w = rho * v, d1 = k2 * v * v;
+        const double tf = s <= d1 ? 2.0 * s / (v + sqrt(fmax(v * v - 2.0 * as * s, 0.0)))
+                                  : k1 * v + 2.0 * (s - d1) /
+                                        (w + sqrt(fmax(w * w - 2.0 * ar * (s - d1), 0.0)));
+        const double u = lam2 / sqrt(ccD), tl = lam3 / sqrt(ccD), sf = lam1 / ccD;
+        const double tc = s <= sf ? s / u
+                                  : tl + 2.0 * (s - sf) /
+                                        (u + sqrt(fmax(u * u - 2.0 * ar * (s - sf), 0.0)));
+        P.f_lim[q] = (float)(1.03 * 0.5 * A * tf);
+        P.c_lim[q] = (float)(1.03 * 0.5 * A * tc);
+    }
     P.margin_cap = p->margin_cap_s;
     P.w_ang_pi = (float)(p->w_angle / M_PI);
     P.w_dist = p->w_dist;
@@ -155,6 +169,7 @@ int build_tables(const dpps_params *p, int32_t n_frames, const dpps_frame *frame
     T.wins.clear();
     T.tiles.clear();
     T.points = 0;
+    T.max_variants = 1;
     T.frames.reserve(n_frames);
     const bool reduced = (p->out_flags & DPPS_OUT_REDUCED) != 0;
     for (int32_t f = 0; f < n_frames; ++f) {
@@ -184,6 +199,7 @@ int build_tables(const dpps_params *p, int32_t n_frames, const dpps_frame *frame
         D.n_windows = F.n_windows;
         D.win_off = (int32_t)T.wins.size();
         D.n_variants = F.n_variants;
+        if (F.n_variants > T.max_variants) T.max_variants = F.n_variants;
         D.variant_off = (int32_t)T.variants.size();
         D.ball_x = F.ball_x;
         D.ball_y = F.ball_y;
@@ -220,7 +236,6 @@ int build_tables(const dpps_params *p, int32_t n_frames, const dpps_frame *frame
             W.i0 = Wn.i0;
             W.j0 = Wn.j0;
             W.nx = Wn.nx;
-            W.ny = Wn.ny;
             W.halfNx = 0.5f * (float)(Nx - 1);
             W.halfNy = 0.5f * (float)(Ny - 1);
             W.frame = f;
@@ -231,8 +246,8 @@ int build_tables(const dpps_params *p, int32_t n_frames, const dpps_frame *frame
             if (elem >= 0x7FFFFFFF)
                 return fail(DPPS_E_UNSUPPORTED, "frame %d: more than 2^31 output elements", f);
             int32_t widx = (int32_t)T.wins.size();
-            if (tile_points > 0)
-                for (int32_t p0 = 0; p0 < W.npts; p0 += tile_points) T.tiles.push_back({widx, p0});
+            W.n_tiles = tile_points > 0 ? (int32_t)(((int64_t)W.npts + tile_points - 1) / tile_points) : 0;
+            for (int32_t k = 0; k < W.n_tiles; ++k) T.tiles.push_back({widx, k});
             T.points += W.npts;
             T.wins.push_back(W);
         }
@@ -365,8 +380,9 @@ void retile(HostTables &T, int tile_points)
         F.tile_begin = (int32_t)T.tiles.size();
         for (int w = 0; w < F.n_windows; ++w) {
             const int32_t widx = F.win_off + w;
-            for (int32_t p0 = 0; p0 < T.wins[widx].npts; p0 += tile_points)
-                T.tiles.push_back({widx, p0});
+            WinDev &W = T.wins[widx];
+            W.n_tiles = (int32_t)(((int64_t)W.npts + tile_points - 1) / tile_points);
+            for (int32_t k = 0; k < W.n_tiles; ++k) T.tiles.push_back({widx, k});
         }
         F.tile_count = (int32_t)T.tiles.size() - F.tile_begin;
     }
@@ -405,6 +421,7 @@ int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t s
     a.n_tiles = (int32_t)b->T.tiles.size();
     a.n_frames = b->n_frames;
     a.tile_points = c->tile_points;
+    a.max_variants = b->T.max_variants;
     // the search kernel cuts a tile into chunks of 4 points
     if (a.tile_points < 4 || a.tile_points % 4)
         return fail(DPPS_E_INVALID, "tile_points %d is not a multiple of 4", a.tile_points);
@@ -425,7 +442,8 @@ int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t s
         a.v0_out = v0_out;
     }
     int per_cu = c->wg_per_cu > 0 ? c->wg_per_cu
-                                  : search_occupancy(c->p.n_samples, c->waves, c->tile_points);
+                                  : search_occupancy(c->p.n_samples, c->waves, c->tile_points,
+                                                     b->T.max_variants);
     int64_t cap = (int64_t)c->n_cu * per_cu;
     int grid = (int)(a.n_tiles < cap ? a.n_tiles : cap);
     if (!c->persistent) grid = a.n_tiles;
@@ -651,7 +669,8 @@ int dpps_get_launch(const dpps_ctx *c, int32_t *tile_points, int32_t *waves_per_
     if (wg_per_cu)
         *wg_per_cu = !c->persistent ? -1
                      : c->wg_per_cu > 0 ? c->wg_per_cu
-                                        : search_occupancy(c->p.n_samples, c->waves, c->tile_points);
+                                        : search_occupancy(c->p.n_samples, c->waves, c->tile_points,
+                                                           DPPS_MAX_VARIANTS);
     return DPPS_OK;
 }
 

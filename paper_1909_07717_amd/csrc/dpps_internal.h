@@ -36,6 +36,10 @@ struct DevParams {
     // chip inversion: stopped / rolling / in-flight regimes (same layout)
     float c_icD, c_icA, c_icB, c_alpha, c_hbeta, c_hbeta2, c_hfast, c_pfast;
     float half_ar;
+    // 1.03 times the ball's time (robot stage units, A T / 2) to the end of each
+    // quarter of a path of length 1 m for the slowest kick that gets to its
+    // end; times scale with the square root of the length
+    float f_lim[4], c_lim[4];
     // scoring
     float margin_cap, w_ang_pi, w_dist, inv_dist_norm, w_margin;
     int32_t K;
@@ -49,21 +53,22 @@ struct DevParams {
 // One (frame, window) pair of a batch.
 struct WinDev {
     float h;
-    int32_t i0, j0, nx, ny;
+    int32_t i0, j0, nx;
+    int32_t n_tiles;        // tiles the window is cut into (search, shot map)
     float halfNx, halfNy;   // (Nx - 1) / 2, (Ny - 1) / 2 of the full lattice
     int32_t frame;
-    int32_t npts;           // nx * ny
+    int32_t npts;           // points
     int32_t elem_base;      // frame-relative index of this window's first element
     int64_t out_base;       // absolute output element of this window's first (reduced) element
 };
 
-// A tile of the passing-point search: p0 / tile_points = k, and the tile
-// holds chunks k, k + T, k + 2T, ... of 4 consecutive points (up to
-// tile_points points) of a window cut into T tiles.  A tile of the shot map: points p0 .. p0 + tile_points -
-// 1; of the direction sweep: directions p0 .. p0 + tile_dirs - 1.
+// Tile k of a window cut into T tiles holds, in the passing-point search,
+// chunks k, k + T, k + 2T, ... of 4 consecutive points (up to tile_points
+// points); in the shot map points k tile_points .. + tile_points - 1.  A tile
+// of the direction sweep: directions at .. at + tile_dirs - 1 of frame win.
 struct TileDev {
     int32_t win;
-    int32_t p0;
+    int32_t at;             // k, or the first direction
 };
 
 // Best pass found by one tile: packed key (score bits << 32 | ~element), and
@@ -111,6 +116,7 @@ struct LaunchArgs {
     int32_t n_tiles;
     int32_t n_frames;
     int32_t tile_points;
+    int32_t max_variants;   // most variants of any frame (rows of the staged maps)
     int32_t persistent;
     uint32_t *counter;      // 8 persistent work counters (one per class of workgroup
                             // index mod 8); the finalize kernel resets them
@@ -209,7 +215,7 @@ int launch_search(const LaunchArgs &a, int waves_per_wg, int grid, void *stream,
 // Zero n 32-bit words of device memory on `stream` (a kernel, no memset).
 int launch_zero_words(uint32_t *p, int n, void *stream);
 // Resident workgroups per CU of the search kernel for this K and block size.
-int search_occupancy(int K, int waves_per_wg, int tile_points);
+int search_occupancy(int K, int waves_per_wg, int tile_points, int max_variants);
 // Direction x variant search (ray kernel then its finalize) on `stream`;
 // ev_start / ev_stop (hipEvent_t or NULL) bracket the ray kernel only.
 // (cos, sin) of theta_d = 2 pi d / n for d < n into dirs (n <= 4096).

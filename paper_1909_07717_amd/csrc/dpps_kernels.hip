@@ -3,8 +3,8 @@
 // Work decomposition
 //   One workgroup per tile of candidate points (persistent workgroups pull
 //   tiles from an atomic counter, or one workgroup per tile).  A wave
-//   evaluates one candidate point at a time with its 64 lanes spread over the
-//   K path samples (K/64 per lane):
+//   evaluates two neighbouring candidate points at a time, one per half, with
+//   the 32 lanes of a half spread over the K path samples (K/32 per lane):
 //
 //   1. robot stage   for every interceptor and every sample, the robot's
 //                    arrival time (straight line, bounded acceleration and
@@ -43,8 +43,26 @@ namespace dpps {
 #define MAX_K 256
 #define PM_ROWS 4  // running-maximum rows per wave: flat team / opp, chip team / opp
 
-// Dynamic LDS of the search and ray kernels: PM_ROWS rows of K floats per wave.
+// Running-maximum floats of one half of a search wave: a team and an opponent
+// row of K, and 32 floats so that the halves' rows start in different banks.
+constexpr int half_rows(int K) { return 2 * K + 32; }
+
+// Dynamic LDS of the ray kernel: PM_ROWS rows of K floats per wave.
 static size_t pm_bytes(int K, int waves) { return (size_t)waves * PM_ROWS * K * sizeof(float); }
+
+// The kernel's arguments, read anew from the kernarg segment: the laundered
+// pointer keeps the compiler from holding every constant in scalar registers
+// over a whole tile loop, where they do not fit and spill to vector lanes
+// (two VALU instructions per spilled use); a scalar load from the cache costs
+// no VALU issue.
+template <class Args>
+__device__ __forceinline__ const Args &fresh_args()
+{
+    typedef const __attribute__((address_space(4))) Args *KernArgs;
+    KernArgs k = (KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return *(const Args *)k;
+}
 
 struct VarConst {
     double va1, a1, va2, a2, soff2, toff2, split, D, sf_reach;
@@ -59,19 +77,22 @@ struct StageLDS {
     int32_t n_tm, n_op, n_var, has_flat, has_chip, frame;
     int32_t vel_ok;           // every robot's speed is at most vmax
     float bx, by;
+    float lim[4];             // arrival limit per quarter of a path, over sqrt(length)
     BallParams64 bp;          // persistent kernels: written once at the start
 };
 
-// A wave's path-frame block: MAX_ROB entries, then MAX_ROB bound keys.
-#define PR_ENTRIES (MAX_ROB + MAX_ROB / 4)
+// A wave's path-frame block: MAX_ROB entries, then 64 words of bound keys.
+#define PR_ENTRIES (MAX_ROB + 16)
+#define SPLIT_ROB 16  // most robots whose bounds are kept per quarter of the path
 
 // Dynamic LDS of the search kernel, sized by the launch: each wave's
-// running-maximum rows and its two path-frame blocks, then the tile's staged
-// score and mask maps (MAX_VAR rows of tile_points).
-static size_t search_lds_bytes(int K, int waves, int tile_points)
+// running-maximum rows and path-frame blocks of two points, then the tile's staged
+// score and mask maps (a row of tile_points per variant of the frame with the
+// most, so that few variants leave room for more workgroups).
+static size_t search_lds_bytes(int K, int waves, int tile_points, int max_variants)
 {
-    const size_t maps = (size_t)MAX_VAR * tile_points * (sizeof(float) + 1);
-    return pm_bytes(K, waves) + (size_t)waves * 2 * PR_ENTRIES * sizeof(float4) +
+    const size_t maps = (size_t)max_variants * tile_points * (sizeof(float) + 1);
+    return (size_t)waves * 2 * (half_rows(K) * sizeof(float) + PR_ENTRIES * sizeof(float4)) +
            ((maps + 15) & ~(size_t)15);
 }
 __device__ __forceinline__ uint32_t *bound_keys(float4 *pr) { return (uint32_t *)(pr + MAX_ROB); }
@@ -81,8 +102,7 @@ __device__ __forceinline__ const uint32_t *bound_keys(const float4 *pr)
 }
 
 struct OutLDS {
-    TileRec wbest[MAX_WAVES];
-    TileRec wgbest;           // the workgroup's best over its tiles (one-frame launches)
+    TileRec wbest[MAX_WAVES];  // each wave's best pass
 };
 
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
@@ -182,6 +202,8 @@ __device__ void stage_frame(const DevParams &P, const BallParams64 &B, const Fra
         }
         S.has_flat = hf;
         S.has_chip = hc;
+        for (int b = 0; b < 4; ++b)
+            S.lim[b] = fmaxf(hf ? P.f_lim[b] : 0.0f, hc ? P.c_lim[b] : 0.0f);
         int ok = 1;
         for (int r = 0; r < nrob; ++r) {
             const dpps_robot R = robots[F.robot_off + r];
@@ -210,14 +232,20 @@ __device__ __forceinline__ int dpp_imax(int v)
     return max(v, u);
 }
 
-__device__ __forceinline__ int wave_prefix_imax(int v)
+// half_prefix_imax stops before the last step: the prefix maximum within each
+// half of 32 lanes.
+__device__ __forceinline__ int half_prefix_imax(int v)
 {
     v = dpp_imax<0x111, 0xf>(v);  // row_shr:1
     v = dpp_imax<0x112, 0xf>(v);  // row_shr:2
     v = dpp_imax<0x114, 0xf>(v);  // row_shr:4
     v = dpp_imax<0x118, 0xf>(v);  // row_shr:8
-    v = dpp_imax<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-    return dpp_imax<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+    return dpp_imax<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+}
+
+__device__ __forceinline__ int wave_prefix_imax(int v)
+{
+    return dpp_imax<0x143, 0xc>(half_prefix_imax(v));  // row_bcast:31 into rows 2 and 3
 }
 
 // Lane l gets lane l - 1's value, lane 0 gets INT_MIN (DPP wave_shr:1).
@@ -233,6 +261,15 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
+
+// The constants of the robot model, by value: read once before a robot loop.
+struct RobotK {
+    float RA, Vh, V2, inv2V, halfV;
+    __device__ __forceinline__ explicit RobotK(const DevParams &P)
+        : RA(P.RA), Vh(P.Vh), V2(P.V2), inv2V(P.inv2V), halfV(P.halfV)
+    {
+    }
+};
 
 // Arrival time of one robot at one sample.  Lengths are scaled by amax (a
 // distance d becomes A d) and speeds by 1/sqrt(2); with that scaling the
@@ -254,7 +291,7 @@ __device__ __forceinline__ void wave_lds_sync()
 // speed toward the sample (h w.e + q w.n) / length.  With CLAMP that speed is
 // limited to vmax; without it the caller knows that no robot is faster.
 template <bool CLAMP>
-__device__ __forceinline__ float robot_time_h(float4 r, float fq, float LA, const DevParams &P)
+__device__ __forceinline__ float robot_time_h(float4 r, float fq, float LA, const RobotK &P)
 {
     const float h = fmaf(fq, LA, -r.x);
     const float r2 = fmaf(h, h, r.y);
@@ -270,100 +307,172 @@ __device__ __forceinline__ float robot_time_h(float4 r, float fq, float LA, cons
     return fmaf(sg, 0.70710678118654752f, rh);
 }
 
-// Earliest arrival (A T / 2) of robots [j0, j0 + n) of the point's path
-// frame `pr` at each of the lane's samples.
-template <int KPL, bool CLAMP>
-__device__ __forceinline__ void robot_stage(const float4 *pr, const DevParams &P, int j0, int n,
-                                            const float (&fs)[KPL], float LA, float (&T)[KPL])
+// How a wave's lanes hold a path's samples: HALF_WAVE, lanes 0-31 one
+// point's and lanes 32-63 another's; FULL_WAVE, all 64 lanes one path's;
+// PLAIN, all 64 lanes in another order (bounds over the whole path only).
+enum { HALF_WAVE, FULL_WAVE, PLAIN };
+
+// Greatest of the lanes' values over groups of 8 lanes (8: row_half_mirror
+// last) or rows of 16, on every lane of the group.
+template <int CTRL>
+__device__ __forceinline__ int dpp_swap_imax(int v)
 {
-    // robots in pairs: two independent chains, joined by a three-way minimum
-    int j = j0;
-    for (; j + 1 < j0 + n; j += 2) {
-        const float4 ra = pr[j], rb = pr[j + 1];
-#pragma unroll
-        for (int q = 0; q < KPL; ++q)
-            T[q] = fminf(T[q], fminf(robot_time_h<CLAMP>(ra, fs[q], LA, P),
-                                     robot_time_h<CLAMP>(rb, fs[q], LA, P)));
-    }
-    if (j < j0 + n) {
-        const float4 r = pr[j];
-#pragma unroll
-        for (int q = 0; q < KPL; ++q) T[q] = fminf(T[q], robot_time_h<CLAMP>(r, fs[q], LA, P));
-    }
+    return max(v, __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ int group8_imax(int v)
+{
+    return dpp_swap_imax<0x141>(dpp_swap_imax<0x4E>(dpp_swap_imax<0xB1>(v)));
+}
+__device__ __forceinline__ int row_mirror_i(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, 0x140, 0xf, 0xf, true);
 }
 
-// Robots [j0, j0 + n) of a side, sorted by ascending lower bound on their
-// arrival times: after the first two, the side's latest arrival over all the
-// wave's samples so far is taken, and the robots whose bound is not below it
-// (a suffix of the sorted order) are left out: they cannot lower any
-// sample's minimum, so the minima are those of all the side's robots.
-// Arrival times are non-negative or +inf, bounds non-negative: both compare
-// as their bits.
-// The robots of the side among [j0, j0 + n) whose bound is below the
-// latest of the arrival minima T over the wave's samples (a prefix of the
-// sorted order; at least `done`).
-template <int KPL>
-__device__ __forceinline__ int robots_needed(const float4 *pr, int n, int done,
-                                             uint32_t side_bit, const float (&T)[KPL])
+// Which robots of the path's sorted order (bit = rank) may still lower an
+// arrival minimum T that matters, those not yet taken among them.  With the
+// bounds kept per quarter of the path (n_rob <= SPLIT_ROB) robot r is needed
+// in a quarter when its bound there is below both the latest of the minima
+// over the quarter's samples and the quarter's limit `lim` (in the same units;
+// lane's own quarter and, HALF_WAVE, the other one of its row).  With HALF_WAVE
+// the result covers both points.  Otherwise one bound per robot is compared
+// with the latest minimum of the whole path.  Arrival times are
+// non-negative or +inf, bounds non-negative: all compare as their bits.
+template <int KPL, int MODE>
+__device__ __forceinline__ uint32_t robots_needed(const float4 *pr, bool split, float lim,
+                                                  float lim_other, const float (&T)[KPL])
 {
+    const int l = lane_id();
     int m = __float_as_int(T[0]);
 #pragma unroll
     for (int q = 1; q < KPL; ++q) m = max(m, __float_as_int(T[q]));
-    m = __builtin_amdgcn_readlane(wave_prefix_imax(m), 63);
-    const int l = lane_id();
-    const uint32_t k = l < MAX_ROB ? bound_keys(pr)[l] : 0xFFFFFFFFu;
-    const bool below = k != 0xFFFFFFFFu && (k & 0x80000000u) == side_bit &&
-                       (int)(k & 0x7FFFFFFFu & ~(uint32_t)(MAX_ROB - 1)) < m;
-    return min(max((int)__builtin_popcountll(__ballot(below)), done), n);
+    bool below;
+    if (split) {
+        if (MODE == HALF_WAVE) {
+            m = group8_imax(m);
+            const int mo = min(row_mirror_i(m), __float_as_int(lim_other));
+            m = min(m, __float_as_int(lim));
+            const int b = (l & 31) >> 3, r = l & 15;
+            below = (int)bound_keys(pr)[b * 16 + r] < m || (int)bound_keys(pr)[(b ^ 1) * 16 + r] < mo;
+        } else {
+            m = dpp_swap_imax<0x140>(group8_imax(m));
+            below = (int)bound_keys(pr)[l] < m;
+        }
+        const unsigned long long b = __ballot(below);
+        const uint32_t x = (uint32_t)b | (uint32_t)(b >> 32);
+        return (x | (x >> 16)) & 0xFFFFu;
+    }
+    if (MODE == HALF_WAVE) {
+        m = half_prefix_imax(m);
+        const int m0 = __builtin_amdgcn_readlane(m, 31), m1 = __builtin_amdgcn_readlane(m, 63);
+        m = l < 32 ? m0 : m1;
+    } else {
+        m = __builtin_amdgcn_readlane(wave_prefix_imax(m), 63);
+    }
+    const unsigned long long b = __ballot((int)bound_keys(pr)[l & 31] < m);
+    return (uint32_t)b | (uint32_t)(b >> 32);
 }
 
-// Robots [j0, j0 + n) of a side, sorted by ascending lower bound on their
-// arrival times: after the first two, and again after the next two, the
-// side's latest arrival over all the wave's samples so far is taken, and the
-// robots whose bound is not below it (a suffix of the sorted order) are left
-// out: they cannot lower any sample's minimum, so the minima are those of
-// all the side's robots.  Arrival times are non-negative or +inf, bounds
-// non-negative: both compare as their bits.
-template <int KPL, bool CLAMP>
-__device__ __forceinline__ void robot_stage_bounded(const float4 *pr, const DevParams &P, int j0,
-                                                    int n, uint32_t side_bit,
-                                                    const float (&fs)[KPL], float LA,
-                                                    float (&T)[KPL])
+// Earliest arrival (A T / 2) of robots [j0, j0 + n) of the path frame, in
+// their sorted order, at each of the lane's samples: the first two, then,
+// pair by pair, those that robots_needed keeps.  A robot left out has, in
+// every quarter, a bound that is not below the latest minimum there, so it
+// lowers no sample's minimum; or not below the quarter's limit.  The limit is
+// 1.03 times the ball's time to the quarter's end for the slowest kick that
+// gets to the end of the path at all, of the frame's kick types: a robot that
+// is no earlier meets only slower kicks there, which no reachable variant
+// is, so minima at or past the limit may stay later than they would be and
+// every reachable variant's first crossing is still the same (critical speeds
+// at the limit are at least 1 % below that slowest kick; in the last quarter
+// the limit is past its stop, where the critical speed does not depend on
+// the arrival any more).  Pass +inf where the minima themselves are used.
+template <int KPL, bool CLAMP, int MODE>
+__device__ __forceinline__ void robot_stage(const float4 *pr, const RobotK &P, int j0, int n,
+                                            bool split, float lim, float lim_other,
+                                            const float (&fs)[KPL], float LA, float (&T)[KPL])
 {
-    // one copy of the pair body (the kernel's code stays small enough for
-    // the instruction cache): the tests run after the pairs at 0 and 2
-    int need = n;
-    int j = 0;
-    for (; j + 1 < need; j += 2) {
-        const float4 ra = pr[j0 + j], rb = pr[j0 + j + 1];
+    uint32_t todo = ((1u << n) - 1u) << j0;  // n <= 16
+    // one copy of each body (the kernel's code stays small enough for the
+    // instruction cache)
+    while (todo) {
+        const float4 ra = pr[__builtin_ctz(todo)];
+        todo &= todo - 1;
+        if (!todo) {
+#pragma unroll
+            for (int q = 0; q < KPL; ++q)
+                T[q] = fminf(T[q], robot_time_h<CLAMP>(ra, fs[q], LA, P));
+            break;
+        }
+        const float4 rb = pr[__builtin_ctz(todo)];
+        todo &= todo - 1;
 #pragma unroll
         for (int q = 0; q < KPL; ++q)
             T[q] = fminf(T[q], fminf(robot_time_h<CLAMP>(ra, fs[q], LA, P),
                                      robot_time_h<CLAMP>(rb, fs[q], LA, P)));
-        if (j < 4 && need > j + 2) need = robots_needed<KPL>(pr, need, j + 2, side_bit, T);
-    }
-    if (j < need) {
-        const float4 r = pr[j0 + j];
-#pragma unroll
-        for (int q = 0; q < KPL; ++q) T[q] = fminf(T[q], robot_time_h<CLAMP>(r, fs[q], LA, P));
+        if (todo) todo &= robots_needed<KPL, MODE>(pr, split, lim, lim_other, T);
     }
 }
 
+// A lower bound on a robot's arrival time (robot stage units) at every sample
+// of the segment [s0, s1] of the path along e.  With delta = max(dist - RA,
+// 0) for its distance to the segment, and u' the speed toward a sample
+// (clamped to +-vmax/sqrt 2 as the stage clamps it), the time -u'/sqrt 2 +
+// R(u'^2 + delta) falls as u' grows up to sqrt(delta) and grows with delta,
+// so with U the largest u' toward any sample: U < sqrt(delta) bounds it by
+// -U/sqrt 2 + R(U^2 + delta); otherwise, whatever the velocity, by
+// sqrt(delta / 2) for delta <= vmax^2 / 2 and else delta / (2 vmax) + vmax /
+// 4.  U: the scaled velocity w' = (w.e, w.n) against the directions (h, q) to
+// the samples, h in [s0 - t, s1 - t]: |w'| when w' lies among them, else the
+// larger end.  Less 2^-12 for the rounding of both computations.
+__device__ __forceinline__ float arrival_bound(const RobotK &P, double t, double q, float wef,
+                                               float wnf, double s0, double s1)
+{
+    const double tc = fmax(fmax(s0 - t, t - s1), 0.0);
+    const float dseg = hsqrt((float)(q * q + tc * tc));
+    const float del = fmaxf(dseg - P.RA, 0.0f);
+    const float qf = (float)q, h0 = (float)(s0 - t), h1 = (float)(s1 - t);
+    const float sq = qf < 0.0f ? -1.0f : 1.0f;
+    const bool among = ((h1 * wnf - qf * wef) * sq >= 0.0f) & ((wef * qf - wnf * h0) * sq >= 0.0f);
+    const float u0 = fmaf(h0, wef, qf * wnf) * rsq(fmaxf(fmaf(h0, h0, qf * qf), 1e-30f));
+    const float u1 = fmaf(h1, wef, qf * wnf) * rsq(fmaxf(fmaf(h1, h1, qf * qf), 1e-30f));
+    const float ww = hsqrt(fmaf(wef, wef, wnf * wnf));
+    const float U = med3(among ? ww : fmaxf(u0, u1), -P.Vh, P.Vh);
+    // every form, then selects (the lanes are robots: branches would split)
+    const float D = fmaf(U, U, del);
+    const float rd = hsqrt(D), rh = hsqrt(0.5f * del);
+    const float fast = fmaf(D, P.inv2V, P.halfV), far = fmaf(del, P.inv2V, 0.5f * P.halfV);
+    const float lb0 = fmaf(-0.70710678118654752f, U, D > P.V2 ? fast : rd);
+    const float lb1 = del <= 0.5f * P.V2 ? rh : far;
+    return (U * fabsf(U) < del ? lb0 : lb1) * (1.0f - 1.0f / 4096.0f);
+}
+
 // Path frame of a ball path along the unit direction e = (ux, uy) for the
-// staged robots (lanes = robots), in float64 and then rounded once: for robot
-// j with offset a = ball - x_j and normal n = (-e_y, e_x): t = -a.e and
-// q = a.n (scaled by amax), w = velocity / sqrt(2), and pr[j] =
-// (t, q^2, w.e, q w.n).  The lane frames robot l (lanes with l >= n_rob
-// idle); every lane of the wave takes part (the row syncs are wave-wide).
-template <bool SORT>
+// staged robots, in float64 and then rounded once: for robot j with offset a
+// = ball - x_j and normal n = (-e_y, e_x): t = -a.e and q = a.n (scaled by
+// amax), w = velocity / sqrt(2), and its entry (t, q^2, w.e, q w.n).  The
+// entries are written in the order of the robots' arrival bounds, each side's
+// by ascending bound, the team's first.  l is the lane's index among the
+// lanes that share the path (32 with HALF_WAVE, else 64).  With `split` (at
+// most SPLIT_ROB robots) every row of 16 of those lanes takes all robots and
+// bounds them over its own part of the path: with FULL_WAVE row b the
+// b-th quarter, with HALF_WAVE row b the quarters 2b and 2b + 1; the bounds
+// go to the key block as [quarter][rank], and the order is by the least.
+// Otherwise lane l takes robot l and bounds it over the whole path; keys by
+// rank (PLAIN: by robot, with the side in the top bit and the robot in the
+// low bits).  Every lane of the wave takes part (the syncs are wave-wide).
+template <int MODE>
 __device__ __forceinline__ void path_frame_dir(const StageLDS &S, const DevParams &P, float4 *pr,
                                                int n_rob, int n_tm, double LA, double ux,
                                                double uy, double bx, double by, int l)
 {
+    const bool split = MODE != PLAIN && n_rob <= SPLIT_ROB;
+    const int r0 = split ? l & 15 : l, row = l >> 4;
+    const RobotK rk(P);
+    uint32_t *const pk = bound_keys(pr);
     float4 fr = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     uint32_t key = 0xFFFFFFFFu;
-    if (l < n_rob) {
-        const float4 r = S.rob[l];
+    float lb0 = INFINITY, lb1 = INFINITY;  // the row's bounds (split)
+    if (r0 < n_rob) {
+        const float4 r = S.rob[r0];
         const double A = (double)P.A;
         const double ax = bx - (double)r.x, ay = by - (double)r.y;
         const double t = -(ax * ux + ay * uy) * A;
@@ -371,60 +480,48 @@ __device__ __forceinline__ void path_frame_dir(const StageLDS &S, const DevParam
         const double we = ((double)r.z * ux + (double)r.w * uy) * 0.70710678118654752;
         const double wn = ((double)r.w * ux - (double)r.z * uy) * 0.70710678118654752;
         fr = make_float4((float)t, (float)(q * q + 1e-30), (float)we, (float)(q * wn));
-        if (SORT) {
-            // A lower bound on the robot's arrival time (robot stage units)
-            // at every sample of the segment [0, LA] along e.  With delta =
-            // max(dist - RA, 0) for its distance to the segment, and u' the
-            // speed toward a sample (clamped to +-vmax/sqrt 2 as the stage
-            // clamps it), the time -u'/sqrt 2 + R(u'^2 + delta) falls as u'
-            // grows up to sqrt(delta) and grows with delta, so with U the
-            // largest u' toward any sample: U < sqrt(delta) bounds it by
-            // -U/sqrt 2 + R(U^2 + delta); otherwise, whatever the velocity,
-            // by sqrt(delta / 2) for delta <= vmax^2 / 2 and else
-            // delta / (2 vmax) + vmax / 4.  U: the scaled velocity w' = (w.e,
-            // w.n) against the directions (h, q) to the samples, h in [-t,
-            // LA - t]: |w'| when w' lies among them, else the larger end.
-            // Less 2^-12 for the rounding of both computations, then
-            // truncated to make room for the lane in the low bits.
-            const double tc = t < 0.0 ? -t : (t > LA ? t - LA : 0.0);
-            const float dseg = hsqrt((float)(q * q + tc * tc));
-            const float del = fmaxf(dseg - P.RA, 0.0f);
-            const float qf = (float)q, h0 = (float)(-t), h1 = (float)(LA - t);
-            const float wef = (float)we, wnf = (float)wn;
-            const float sq = qf < 0.0f ? -1.0f : 1.0f;
-            const bool among = (h1 * wnf - qf * wef) * sq >= 0.0f &&
-                               (wef * qf - wnf * h0) * sq >= 0.0f;
-            const float u0 = fmaf(h0, wef, qf * wnf) * rsq(fmaxf(fmaf(h0, h0, qf * qf), 1e-30f));
-            const float u1 = fmaf(h1, wef, qf * wnf) * rsq(fmaxf(fmaf(h1, h1, qf * qf), 1e-30f));
-            const float U = med3(among ? hsqrt(fmaf(wef, wef, wnf * wnf)) : fmaxf(u0, u1),
-                                 -P.Vh, P.Vh);
-            float lb;
-            if (U * fabsf(U) < del) {
-                const float D = fmaf(U, U, del);
-                lb = fmaf(-0.70710678118654752f, U,
-                          D > P.V2 ? fmaf(D, P.inv2V, P.halfV) : hsqrt(D));
-            } else {
-                lb = del <= 0.5f * P.V2 ? hsqrt(0.5f * del) : fmaf(del, P.inv2V, 0.5f * P.halfV);
-            }
-            key = (__float_as_uint(lb * (1.0f - 1.0f / 4096.0f)) & ~(uint32_t)(MAX_ROB - 1)) |
-                  (uint32_t)l | (l >= n_tm ? 0x80000000u : 0u);
+        double s0 = 0.0, s1 = LA;
+        if (split) {
+            s0 = 0.25 * LA * (double)(MODE == HALF_WAVE ? 2 * row : row);
+            s1 = s0 + 0.25 * LA;
         }
+        lb0 = arrival_bound(rk, t, q, (float)we, (float)wn, s0, s1);
+        if (MODE == HALF_WAVE && split)
+            lb1 = arrival_bound(rk, t, q, (float)we, (float)wn, s1, s1 + 0.25 * LA);
     }
-    if (SORT) {
-        // Rank by key: each side's robots by ascending bound (the side bit
-        // puts the team's first), written to the rows in that order.  The
-        // keys stay in the row's key block, by robot, for the bound test.
-        uint32_t *const pk = bound_keys(pr);
-        if (l < MAX_ROB) pk[l] = key;
-        wave_lds_sync();
-        int rank = 0;
-        for (int j = 0; j < n_rob; j += 4) {
-            const uint4 k4 = *(const uint4 *)(pk + j);
-            rank += (k4.x < key) + (k4.y < key) + (k4.z < key) + (k4.w < key);
+    if (split) {
+        // the robot's least bound over the rows
+        float lb = fminf(lb0, lb1);
+        lb = fminf(lb, __shfl_xor(lb, 16, 64));
+        if (MODE == FULL_WAVE) lb = fminf(lb, __shfl_xor(lb, 32, 64));
+        if (r0 < n_rob) key = __float_as_uint(lb);
+    } else if (r0 < n_rob) {
+        key = __float_as_uint(lb0);
+    }
+    // Rank by key: the bound's bits, with the robot in the low bits and the
+    // side in the top bit
+    if (r0 < n_rob)
+        key = (key & ~(uint32_t)(MAX_ROB - 1)) | (uint32_t)r0 | (r0 >= n_tm ? 0x80000000u : 0u);
+    if (split ? row == 0 : l < MAX_ROB) pk[r0] = key;
+    wave_lds_sync();
+    int rank = 0;
+    for (int j = 0; j < n_rob; j += 4) {
+        const uint4 k4 = *(const uint4 *)(pk + j);
+        rank += (k4.x < key) + (k4.y < key) + (k4.z < key) + (k4.w < key);
+    }
+    if (r0 < n_rob && (!split || row == 0)) pr[rank] = fr;
+    if (MODE != PLAIN) {
+        wave_lds_sync();  // the ranks are formed: the key block takes the bounds by rank
+        if (r0 < n_rob) {
+            if (!split) {
+                pk[rank] = __float_as_uint(lb0) & ~(uint32_t)(MAX_ROB - 1);
+            } else if (MODE == HALF_WAVE) {
+                pk[(2 * row) * 16 + rank] = __float_as_uint(lb0);
+                pk[(2 * row + 1) * 16 + rank] = __float_as_uint(lb1);
+            } else {
+                pk[row * 16 + rank] = __float_as_uint(lb0);
+            }
         }
-        if (l < n_rob) pr[rank] = fr;
-    } else if (l < n_rob) {
-        pr[l] = fr;
     }
     // the row is written and read by this wave only
     wave_lds_sync();
@@ -446,7 +543,7 @@ __device__ __forceinline__ float path_frame(const StageLDS &S, const DevParams &
     const bool pos = L2 > 0.0;
     const double L = pos ? L2 * iL : 0.0;
     const double ux = pos ? ex * iL : 1.0, uy = pos ? ey * iL : 0.0;
-    path_frame_dir<true>(S, P, pr, n_rob, n_tm, L * (double)P.A, ux, uy, bx, by, l);
+    path_frame_dir<HALF_WAVE>(S, P, pr, n_rob, n_tm, L * (double)P.A, ux, uy, bx, by, l);
     return (float)(L * (double)P.A);
 }
 
@@ -459,20 +556,23 @@ __device__ __forceinline__ float path_frame(const StageLDS &S, const DevParams &
 // then every variant lane counts by binary search in its kick type's two rows,
 // the team's and the opponents' searches interleaved.  The decisions are the
 // comparisons v0 <= vc_k of a scan over k.
-template <int KPL>
+// With HALF each half of the wave holds a point's samples and `row` is the
+// lane's own half's row.
+template <int KPL, bool HALF>
 __device__ __forceinline__ void store_running_max(const float (&vc)[KPL], float *row)
 {
-    const int l = lane_id();
+    const int l = HALF ? lane_id() & 31 : lane_id();
     int run[KPL];
     run[0] = __float_as_int(vc[0]);
 #pragma unroll
     for (int q = 1; q < KPL; ++q) run[q] = max(run[q - 1], __float_as_int(vc[q]));
-    const int excl = wave_shift_up_i(wave_prefix_imax(run[KPL - 1]));
+    int excl = wave_shift_up_i(HALF ? half_prefix_imax(run[KPL - 1]) : wave_prefix_imax(run[KPL - 1]));
+    if (HALF) excl = l == 0 ? INT_MIN : excl;
 #pragma unroll
     for (int q = 0; q < KPL; ++q) row[l * KPL + q] = __int_as_float(max(excl, run[q]));
 }
 
-template <int KPL>
+template <int K>
 __device__ __forceinline__ void count_below(const float *rt, const float *ro, float v0, int &kt,
                                             int &ko)
 {
@@ -481,8 +581,7 @@ __device__ __forceinline__ void count_below(const float *rt, const float *ro, fl
     // is below v0, and is then clamped); no branches, both sides interleaved.
     // The search moves row pointers (the step's offset goes into the LDS
     // read's immediate); when K is a power of two no read can pass the end.
-    constexpr int K = KPL * 64;
-    constexpr int S0 = KPL >= 3 ? 128 : (KPL == 2 ? 64 : 32);  // half of 2^n
+    constexpr int S0 = K > 128 ? 128 : K / 2;  // half of 2^n
     constexpr bool POW2 = (K & (K - 1)) == 0;
     const float *pt = rt, *po = ro;
     const float *const et = rt + (K - 1), *const eo = ro + (K - 1);
@@ -527,7 +626,8 @@ __device__ __forceinline__ float vcrit(float T, float s, float s_icA, float s_ic
     const float Q = fmaf(half_ar, T2, s);
     const bool stop = s_icA <= T2;
     const bool fast = s_icB >= T2;
-    const float m_slow = fmaxf(fmaf(alpha, Q, hbeta2 * T2), 0.0f);
+    // (negative, so a NaN root, in the other regimes only)
+    const float m_slow = fmaf(alpha, Q, hbeta2 * T2);
     const float d_slow = fmaf(hbeta, T, hsqrt(m_slow));
     const float N = fast ? (CHIP ? s : fmaf(hfast, T2, s)) : Q;
     const float D = fast ? (CHIP ? pfast * T : T) : d_slow;
@@ -535,8 +635,11 @@ __device__ __forceinline__ float vcrit(float T, float s, float s_icA, float s_ic
 }
 
 // The side-independent terms of the inversion at the lane's samples for one
-// kick type.
-template <int KPL, bool CHIP>
+// kick type.  With TARGET the path ends at the point passed to, so the variants
+// that count reach its last sample: they are faster than the stopped root of
+// every earlier sample (less by a factor sqrt((K - 1) / K) at least), which is
+// then taken as 0, and only the lane's last one is formed.
+template <int KPL, bool CHIP, bool TARGET>
 struct SampleTerms {
     float icA[KPL], icB[KPL], vst[KPL];
     __device__ __forceinline__ SampleTerms(const DevParams &P, const float (&sk)[KPL])
@@ -545,17 +648,17 @@ struct SampleTerms {
         for (int q = 0; q < KPL; ++q) {
             icA[q] = sk[q] * (CHIP ? P.c_icA : P.f_icA);
             icB[q] = sk[q] * (CHIP ? P.c_icB : P.f_icB);
-            vst[q] = hsqrt(sk[q] * (CHIP ? P.c_icD : P.f_icD));
+            vst[q] = TARGET && q < KPL - 1 ? 0.0f : hsqrt(sk[q] * (CHIP ? P.c_icD : P.f_icD));
         }
     }
 };
 
 // Critical speeds of one side at the lane's samples for one kick type (0 for
 // every sample when the side has no robot).
-template <int KPL, bool CHIP>
+template <int KPL, bool CHIP, bool TARGET>
 __device__ __forceinline__ void side_vcrit(const DevParams &P, int n_side, const float (&T)[KPL],
                                            const float (&sk)[KPL],
-                                           const SampleTerms<KPL, CHIP> &st,
+                                           const SampleTerms<KPL, CHIP, TARGET> &st,
                                            const float (&vair)[KPL], float (&v)[KPL])
 {
     if (n_side == 0) {
@@ -633,58 +736,23 @@ __device__ __forceinline__ unsigned long long dpp_max_u64(unsigned long long x)
 }
 
 // Largest 64-bit key over the wave, on every lane: the DPP scan steps of
-// wave_prefix_max (lanes without a source see 0), then lane 63's total.
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x)
+// wave_prefix_imax (lanes without a source see 0), then lane 63's total.
+// half_prefix_max_u64 leaves each half's largest on its lane 31.
+__device__ __forceinline__ unsigned long long half_prefix_max_u64(unsigned long long x)
 {
     x = dpp_max_u64<0x111, 0xf>(x);
     x = dpp_max_u64<0x112, 0xf>(x);
     x = dpp_max_u64<0x114, 0xf>(x);
     x = dpp_max_u64<0x118, 0xf>(x);
-    x = dpp_max_u64<0x142, 0xa>(x);
-    x = dpp_max_u64<0x143, 0xc>(x);
+    return dpp_max_u64<0x142, 0xa>(x);
+}
+
+__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x)
+{
+    x = dpp_max_u64<0x143, 0xc>(half_prefix_max_u64(x));
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), 63);
     return ((unsigned long long)hi << 32) | lo;
-}
-
-// Open goal angle at c = (cx, cy) against the staged opponents; lanes are
-// opponents.  Returns the same value on every lane.
-__device__ float open_angle(const StageLDS &S, const DevParams &P, float cx, float cy, int n_op,
-                            int n_tm)
-{
-    int l = lane_id();
-    float dxg = fmaxf(P.goal_x - cx, P.goal_eps);
-    // lanes < n_op: direction to the opponent; lanes 62/63: to the goal posts
-    float4 o = S.rob[n_tm + (l < n_op ? l : 0)];
-    float ox = o.x - cx, oy = o.y - cy;
-    float Y = l < n_op ? oy : (l == 62 ? -P.half_goal_w - cy : P.half_goal_w - cy);
-    float X = l < n_op ? ox : dxg;
-    float ang = atan2f(Y, X);
-    float lo = readlane_f(ang, 62);
-    float hi = readlane_f(ang, 63);
-    bool valid = l < n_op && o.x < P.goal_x;
-    float rho2 = fmaf(ox, ox, oy * oy);
-    bool inside = valid && rho2 <= P.R * P.R;
-    if (__ballot(inside)) return 0.0f;
-    float al = asinf(fminf(P.R * rsq(fmaxf(rho2, 1e-30f)), 1.0f));
-    float s = fmaxf(ang - al, lo);
-    float e = fminf(ang + al, hi);
-    bool has = valid && e > s;
-    // union length: each interval contributes what the intervals sorted
-    // before it (by start, then index) have not already covered
-    const unsigned long long hm = __ballot(has);
-    float M = -INFINITY;
-    for (unsigned long long m = hm; m; m &= m - 1) {
-        int k = __builtin_ctzll(m);
-        float sk = readlane_f(s, k);
-        float ek = readlane_f(e, k);
-        bool before = sk < s || (sk == s && k < l);
-        M = before ? fmaxf(M, ek) : M;
-    }
-    float contrib = has ? fmaxf(e - fmaxf(s, M), 0.0f) : 0.0f;
-    float blocked = 0.0f;
-    for (unsigned long long m = hm; m; m &= m - 1) blocked += readlane_f(contrib, __builtin_ctzll(m));
-    return (hi - lo) - blocked;
 }
 
 // Passing power (Sec. 4.1, Eq. 1-2) for a pass over d64 metres whose
@@ -708,16 +776,12 @@ __device__ __forceinline__ double pass_power(const DevParams &P, double d64, flo
 // samples (lanes = samples, K/64 consecutive samples per lane), critical
 // speeds, first crossings (pm: this wave's LDS block of 4 K floats).  On
 // return lane v (a staged variant) holds its first team / opponent crossing
-// samples (K: none).  With POWER the frame's variants are replaced by one
-// flat pass at the power of Eq. 1-2 (lane 0), whose receiver is the first
-// teammate at the last sample, the point itself; its speed is returned in v0.
-template <int KPL, bool POWER>
+// samples (K: none).
+template <int KPL>
 __device__ __forceinline__ void sbip_crossings(const StageLDS &S, const DevParams &P,
                                                const float4 *pr, float *pm, float myv0,
                                                int mytype, float d, float LA, int &my_kt,
-                                               int &my_ko, double d64 = 0.0, double buffer = 0.0,
-                                               double vmin = 0.0, double vmax = 0.0,
-                                               double *v0 = nullptr)
+                                               int &my_ko)
 {
     const int l = lane_id();
     const int K = KPL * 64;
@@ -733,12 +797,14 @@ __device__ __forceinline__ void sbip_crossings(const StageLDS &S, const DevParam
         To[q] = INFINITY;
     }
     // 1. robot stage, in the path frame
+    const bool split = n_tm + n_op <= SPLIT_ROB;
+    const RobotK rk(P);
     if (uni(S.vel_ok)) {
-        robot_stage_bounded<KPL, false>(pr, P, 0, n_tm, 0u, fs, LA, Tt);
-        robot_stage_bounded<KPL, false>(pr, P, n_tm, n_op, 0x80000000u, fs, LA, To);
+        robot_stage<KPL, false, FULL_WAVE>(pr, rk, 0, n_tm, split, INFINITY, INFINITY, fs, LA, Tt);
+        robot_stage<KPL, false, FULL_WAVE>(pr, rk, n_tm, n_op, split, INFINITY, INFINITY, fs, LA, To);
     } else {
-        robot_stage_bounded<KPL, true>(pr, P, 0, n_tm, 0u, fs, LA, Tt);
-        robot_stage_bounded<KPL, true>(pr, P, n_tm, n_op, 0x80000000u, fs, LA, To);
+        robot_stage<KPL, true, FULL_WAVE>(pr, rk, 0, n_tm, split, INFINITY, INFINITY, fs, LA, Tt);
+        robot_stage<KPL, true, FULL_WAVE>(pr, rk, n_tm, n_op, split, INFINITY, INFINITY, fs, LA, To);
     }
     // 2-3. critical kick speeds per sample, then the first crossing of each
     // lane's variant (a side with no robot never intercepts: critical speed 0)
@@ -747,181 +813,306 @@ __device__ __forceinline__ void sbip_crossings(const StageLDS &S, const DevParam
         Tt[q] *= P.invA2;  // seconds
         To[q] *= P.invA2;
     }
-    if (POWER) {
-        const float t_recv = readlane_f(Tt[KPL - 1], 63);
-        const double v = pass_power(P, d64, t_recv, buffer, vmin, vmax);
-        *v0 = v;
-        myv0 = (float)v;
-        mytype = (l == 0 && v > 0.0) ? DPPS_FLAT : -1;
-    }
     const unsigned long long flat_m = __ballot(mytype == DPPS_FLAT);
     const unsigned long long chip_m = __ballot(mytype == DPPS_CHIP);
     float *const pf = pm, *const pc = pm + 2 * K;  // flat rows, chip rows
     wave_lds_sync();  // the previous path's searches are done with the rows
     if (flat_m) {
         float vt[KPL], vo[KPL];
-        const SampleTerms<KPL, false> st(P, sk);
-        side_vcrit<KPL, false>(P, n_tm, Tt, sk, st, sk, vt);
-        side_vcrit<KPL, false>(P, n_op, To, sk, st, sk, vo);
-        store_running_max<KPL>(vt, pf);
-        store_running_max<KPL>(vo, pf + K);
+        const SampleTerms<KPL, false, false> st(P, sk);
+        side_vcrit<KPL, false, false>(P, n_tm, Tt, sk, st, sk, vt);
+        side_vcrit<KPL, false, false>(P, n_op, To, sk, st, sk, vo);
+        store_running_max<KPL, false>(vt, pf);
+        store_running_max<KPL, false>(vo, pf + K);
     }
     if (chip_m) {
         float vt[KPL], vo[KPL], vair[KPL];
 #pragma unroll
         for (int q = 0; q < KPL; ++q) vair[q] = hsqrt(sk[q] * P.lam1_inv);
-        const SampleTerms<KPL, true> st(P, sk);
-        side_vcrit<KPL, true>(P, n_tm, Tt, sk, st, vair, vt);
-        side_vcrit<KPL, true>(P, n_op, To, sk, st, vair, vo);
-        store_running_max<KPL>(vt, pc);
-        store_running_max<KPL>(vo, pc + K);
+        const SampleTerms<KPL, true, false> st(P, sk);
+        side_vcrit<KPL, true, false>(P, n_tm, Tt, sk, st, vair, vt);
+        side_vcrit<KPL, true, false>(P, n_op, To, sk, st, vair, vo);
+        store_running_max<KPL, false>(vt, pc);
+        store_running_max<KPL, false>(vo, pc + K);
     }
     wave_lds_sync();
     my_kt = K;
     my_ko = K;
     if ((mytype == DPPS_FLAT) | (mytype == DPPS_CHIP)) {
         const float *r = mytype == DPPS_CHIP ? pc : pf;
-        count_below<KPL>(r, r + K, myv0, my_kt, my_ko);
+        count_below<KPL * 64>(r, r + K, myv0, my_kt, my_ko);
     }
 }
 
-// Evaluate candidate point (cx, cy) for every staged variant, its path
-// frame already in pr (LA: |c - ball| A).  myv0 / mytype hold lane v's
-// variant (lanes >= n_var: type -1).  On return lane v (< n_var) holds that
-// variant's results.  With POWER the point has one flat variant at its own
-// passing power (returned in o_v0), computed from the launch's buffer and
-// kick range.
-template <int KPL, bool POWER>
-__device__ void eval_point(const StageLDS &S, const DevParams &P, const float4 *pr, float *pm,
-                           float myv0, int mytype, float cx, float cy, double cx64,
-                           double cy64, float LA, float &o_score, int &o_feas, float &o_tt,
-                           float &o_to, float &o_v0, const LaunchArgs &a)
+// Value of x held by lane `src` (0-31) of the lane's own half of the wave.
+__device__ __forceinline__ float half_read(float x, int src)
+{
+    const int a = ((lane_id() & 32) | src) << 2;
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(a, __float_as_int(x)));
+}
+
+// Open goal angle at two points, one per half of the wave (lane's own cx, cy),
+// against the staged opponents: lane o < n_op of a half holds opponent o, its
+// lanes 30 and 31 the goal posts.  Each interval contributes what the
+// half's intervals sorted before it (by start, then index) have not already
+// covered.  Returns on every lane the angle of its half's point.  Costs a
+// wave about what one point alone did.
+__device__ float open_angle_pair(const StageLDS &S, const DevParams &P, float cx, float cy,
+                                 int n_op, int n_tm)
+{
+    const int l = lane_id(), hl = l & 31;
+    const float dxg = fmaxf(P.goal_x - cx, P.goal_eps);
+    const float4 o = S.rob[n_tm + (hl < n_op ? hl : 0)];
+    const float ox = o.x - cx, oy = o.y - cy;
+    const float Y = hl < n_op ? oy : (hl == 30 ? -P.half_goal_w - cy : P.half_goal_w - cy);
+    const float X = hl < n_op ? ox : dxg;
+    const float ang = atan2f(Y, X);
+    const float lo = half_read(ang, 30);
+    const float hi = half_read(ang, 31);
+    const bool valid = hl < n_op && o.x < P.goal_x;
+    const float rho2 = fmaf(ox, ox, oy * oy);
+    const unsigned long long in = __ballot(valid && rho2 <= P.R * P.R);
+    const float al = asinf(fminf(P.R * rsq(fmaxf(rho2, 1e-30f)), 1.0f));
+    const float s = fmaxf(ang - al, lo);
+    const float e = fminf(ang + al, hi);
+    const bool has = valid && e > s;
+    const unsigned long long hm = __ballot(has);
+    const uint32_t any = (uint32_t)hm | (uint32_t)(hm >> 32);
+    const float sh = has ? s : INFINITY;  // a start of +inf marks no interval
+    float M = -INFINITY;
+    for (uint32_t m = any; m; m &= m - 1) {
+        const int k = __builtin_ctz(m);
+        const float sk = half_read(sh, k), ek = half_read(e, k);
+        const bool before = sk < sh || (sk == sh && k < hl);
+        M = before ? fmaxf(M, ek) : M;
+    }
+    const float contrib = has ? fmaxf(e - fmaxf(s, M), 0.0f) : 0.0f;
+    float blocked = 0.0f;
+    for (uint32_t m = any; m; m &= m - 1) blocked += half_read(contrib, __builtin_ctz(m));
+    const bool inside = (l < 32 ? (uint32_t)in : (uint32_t)(in >> 32)) != 0u;
+    return inside ? 0.0f : (hi - lo) - blocked;
+}
+
+// SBIP crossings of two candidate points at once, one per half of the wave:
+// the 32 lanes of a half hold the K samples of its point (K/32 consecutive
+// ones per lane), pr and pm are the lane's own half's path frame and its two
+// running-maximum rows (K floats each, used for the flat kicks and then for
+// the chips).  On return kt[c] / ko[c] are the first team / opponent crossing
+// samples (K: none) of the lane's variant of chunk c (variant 32 c + lane of
+// the half).  With POWER the frame's variants are replaced by one flat pass
+// at the power of Eq. 1-2 (lane 0 of the half), whose receiver is the first
+// teammate at the last sample, the point itself; its speed is returned in v0.
+template <int KPH, bool POWER>
+__device__ __forceinline__ void pair_crossings(const StageLDS &S, const float4 *pr, float *pm,
+                                               float d, float LA, int (&kt)[2], int (&ko)[2],
+                                               double d64, double &v0)
+{
+    constexpr int K = KPH * 32;
+    const int hl = lane_id() & 31;
+    const int n_tm = uni(S.n_tm), n_op = uni(S.n_op);
+    const int n_var = POWER ? 1 : uni(S.n_var);
+    // (the sample fractions are formed anew for each pair of points: kept
+    // across the tile loop they would hold KPH registers)
+    int k0 = hl * KPH + 1;
+    asm volatile("" : "+v"(k0));
+    float fs[KPH], Tt[KPH], To[KPH];
+#pragma unroll
+    for (int q = 0; q < KPH; ++q) {
+        fs[q] = (float)(k0 + q) * (1.0f / (float)K);
+        Tt[q] = INFINITY;
+        To[q] = INFINITY;
+    }
+    {
+    const RobotK rk(fresh_args<LaunchArgs>().P);
+    const bool split = n_tm + n_op <= SPLIT_ROB;
+    // arrival limits of the lane's quarter of the path and the other of its
+    // row; with POWER the team's minimum at the last sample is the
+    // receiver's time itself
+    const float rd = hsqrt(d);
+    const int b = hl >> 3;
+    const float lim = rd * S.lim[b], limx = rd * S.lim[b ^ 1];
+    const float lim_t = POWER && b == 3 ? INFINITY : lim;
+    const float limx_t = POWER && b == 2 ? INFINITY : limx;
+    if (uni(S.vel_ok)) {
+        robot_stage<KPH, false, HALF_WAVE>(pr, rk, 0, n_tm, split, lim_t, limx_t, fs, LA, Tt);
+        robot_stage<KPH, false, HALF_WAVE>(pr, rk, n_tm, n_op, split, lim, limx, fs, LA, To);
+    } else {
+        robot_stage<KPH, true, HALF_WAVE>(pr, rk, 0, n_tm, split, lim_t, limx_t, fs, LA, Tt);
+        robot_stage<KPH, true, HALF_WAVE>(pr, rk, n_tm, n_op, split, lim, limx, fs, LA, To);
+    }
+    }
+    const LaunchArgs &a = fresh_args<LaunchArgs>();
+    const float invA2 = a.P.invA2;
+    float sk[KPH];
+#pragma unroll
+    for (int q = 0; q < KPH; ++q) {
+        sk[q] = fs[q] * d;
+        Tt[q] *= invA2;  // seconds
+        To[q] *= invA2;
+    }
+    if (POWER) {
+        v0 = pass_power(a.P, d64, half_read(Tt[KPH - 1], 31), (double)a.p_buffer, (double)a.p_vmin,
+                        (double)a.p_vmax);
+    }
+    kt[0] = kt[1] = ko[0] = ko[1] = K;
+    if (POWER || uni(S.has_flat)) {
+        const DevParams &P = fresh_args<LaunchArgs>().P;
+        float vc[KPH];
+        const SampleTerms<KPH, false, true> st(P, sk);
+        wave_lds_sync();  // the previous searches are done with the rows
+        side_vcrit<KPH, false, true>(P, n_tm, Tt, sk, st, sk, vc);
+        store_running_max<KPH, true>(vc, pm);
+        side_vcrit<KPH, false, true>(P, n_op, To, sk, st, sk, vc);
+        store_running_max<KPH, true>(vc, pm + K);
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int v = 32 * c + hl;
+            if (POWER && c == 0 && hl == 0 && v0 > 0.0)
+                count_below<K>(pm, pm + K, (float)v0, kt[0], ko[0]);
+            if (!POWER && 32 * c < n_var && v < n_var && S.type[v] == DPPS_FLAT)
+                count_below<K>(pm, pm + K, S.v0[v], kt[c], ko[c]);
+        }
+    }
+    if (!POWER && uni(S.has_chip)) {
+        const DevParams &P = fresh_args<LaunchArgs>().P;
+        float vc[KPH], vair[KPH];
+#pragma unroll
+        for (int q = 0; q < KPH; ++q) vair[q] = hsqrt(sk[q] * P.lam1_inv);
+        const SampleTerms<KPH, true, true> st(P, sk);
+        wave_lds_sync();
+        side_vcrit<KPH, true, true>(P, n_tm, Tt, sk, st, vair, vc);
+        store_running_max<KPH, true>(vc, pm);
+        side_vcrit<KPH, true, true>(P, n_op, To, sk, st, vair, vc);
+        store_running_max<KPH, true>(vc, pm + K);
+        wave_lds_sync();
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int v = 32 * c + hl;
+            if (32 * c < n_var && v < n_var && S.type[v] == DPPS_CHIP)
+                count_below<K>(pm, pm + K, S.v0[v], kt[c], ko[c]);
+        }
+    }
+}
+
+// The wave's best pass (the lane with the largest key) into its record.
+__device__ __forceinline__ void wave_best(OutLDS &O, int w, unsigned long long key, float tt,
+                                          float to, float v0)
+{
+    const unsigned long long wk = wave_max_u64(key);
+    const unsigned long long who = __ballot(key == wk);
+    if (lane_id() == (int)__builtin_ctzll(who)) {
+        O.wbest[w].key = wk;
+        O.wbest[w].t_team = wk ? tt : INFINITY;
+        O.wbest[w].t_opp = wk ? to : INFINITY;
+        O.wbest[w].v0 = wk ? v0 : 0.0f;
+        O.wbest[w].pad = 0.0f;
+    }
+}
+
+// The largest of the waves' records (keys of different waves differ unless
+// both are 0), written by one wave.
+__device__ __forceinline__ void group_best(const OutLDS &O, int nw, TileRec *rec)
 {
     const int l = lane_id();
-    const int K = KPL * 64;
-    const int n_tm = uni(S.n_tm), n_op = uni(S.n_op), n_var = uni(S.n_var);
-    const float bx = unif(S.bx), by = unif(S.by);
-    const float ex = cx - bx, ey = cy - by;
-    const float d = hsqrt(fmaf(ex, ex, ey * ey));
-    const double ex64 = cx64 - (double)bx, ey64 = cy64 - (double)by;
-    const double d64 = sqrt64(ex64 * ex64 + ey64 * ey64);
-    int my_kt, my_ko;
-    double v0 = 0.0;
-    sbip_crossings<KPL, POWER>(S, P, pr, pm, myv0, mytype, d, LA, my_kt, my_ko, d64,
-                               (double)a.p_buffer, (double)a.p_vmin, (double)a.p_vmax, &v0);
-    o_v0 = (float)v0;
-    // 4. finish: lanes = variants
-    o_score = -INFINITY;
-    o_feas = 0;
-    o_tt = INFINITY;
-    o_to = INFINITY;
-    bool feas = false;
-    double m = -INFINITY;
-    if (l < n_var && (!POWER || v0 > 0.0)) {
-        const VarConst c = POWER ? var_const(P.bp, DPPS_FLAT, (float)v0) : S.vc[l];
-        bool reach = d64 >= 1e-9 && d64 <= c.D && d64 >= c.sf_reach;
-        double tt = INFINITY, to = INFINITY;
-        if (reach) {
-            if (my_kt < K) tt = ball_time64(c, (double)(my_kt + 1) * P.invK_d * d64);
-            if (my_ko < K) to = ball_time64(c, (double)(my_ko + 1) * P.invK_d * d64);
-        }
-        bool tfin = tt < INFINITY;
-        m = !tfin ? -INFINITY : (to < INFINITY ? to - tt : INFINITY);
-        feas = reach && tfin && m >= P.margin_d;
-        o_feas = feas;
-        o_tt = (float)tt;
-        o_to = (float)to;
-    }
-    // the open goal angle (lanes = opponents) enters only feasible scores
-    if (__ballot(feas)) {
-        const float ang = open_angle(S, P, cx, cy, n_op, n_tm);
-        if (feas) {
-            float gx = cx - P.goal_x;
-            float dg = hsqrt(fmaf(gx, gx, cy * cy));
-            float mc = fminf(fmaxf((float)m, 0.0f), P.margin_cap);
-            o_score = fmaf(P.w_ang_pi, ang, fmaf(P.w_dist, fmaf(-dg, P.inv_dist_norm, 1.0f),
-                                                 P.w_margin * mc));
-        }
-    }
+    const unsigned long long k = l < nw ? O.wbest[l].key : 0ull;
+    const unsigned long long tk = wave_max_u64(k);
+    const unsigned long long at = __ballot(k == tk && l < nw);
+    if (l == (int)__builtin_ctzll(at)) *rec = O.wbest[l];
 }
 
+// Bound by VALU issue.  One point per half of a wave rather than per wave: the
+// bound tests, prefix maxima, searches, the float64 finish (32 lanes are
+// variants) and the open angle cost a pair of points what they cost one,
+// the robot stage and the inversions cost the same per sample.  With the bounds
+// kept per quarter of the path, its arrival limits and the arguments read
+// where they are used (57-100 spilled scalars gone) the default-shape full
+// frame (8v8, 43 621 points, 32 variants, K = 256) takes 123 us instead of
+// 142 and 52.5 M VALU instructions instead of 66.9 M; 256 uneven windows at
+// 8 variants, K = 128, 3.40 ms instead of 4.42; passing power 96 us instead of 122.
 // At most 128 VGPRs, so four waves fit on each SIMD.  POWER: one flat pass
 // per point at the point's own passing power (Eq. 1-2).
-template <int KPL, bool POWER>
-__global__ void __launch_bounds__(512, 4) search_kernel(LaunchArgs a)
+template <int KPH, bool POWER>
+__global__ void __launch_bounds__(512, 4) search_kernel(LaunchArgs args)
 {
     __shared__ StageLDS S;
     __shared__ OutLDS O;
-    // dynamic: each wave's running maxima (4 rows of K), its path frames of
-    // two points, the tile's staged score and mask maps
+    // dynamic: each wave's running maxima (two rows of K for each half), its
+    // path frames of two points, the tile's staged score and mask maps
     extern __shared__ float PMX[];
     __shared__ int s_tile;
-    const DevParams &P = a.P;
     const int nw = blockDim.x >> 6;
     const int w = threadIdx.x >> 6;
     const int l = lane_id();
-    const int TP = a.tile_points;
-    float4 *const PR = (float4 *)(PMX + nw * PM_ROWS * KPL * 64);
+    const int TP = args.tile_points;
+    constexpr int K = KPH * 32, HROWS = half_rows(K);
+    const int h = l >> 5, hl = l & 31;  // half of the wave, lane in it
+    float4 *const PR = (float4 *)(PMX + nw * 2 * HROWS);
     float *const OS = (float *)(PR + nw * 2 * PR_ENTRIES);
-    uint8_t *const OM = (uint8_t *)(OS + MAX_VAR * TP);
-    const bool reduced = (P.out_flags & DPPS_OUT_REDUCED) != 0;
+    uint8_t *const OM = (uint8_t *)(OS + args.max_variants * TP);
+    const bool reduced = (args.P.out_flags & DPPS_OUT_REDUCED) != 0;
     int iter = 0;
     int cur_frame = -1;
-    float myv0 = 0.0f;
-    int mytype = -1;
-    int myvid = 0;  // the caller's index of lane l's variant
     // Persistent workgroups take the tiles round-robin (no atomics; tiles of
     // differing cost spread evenly) for all but the last one or two rounds,
     // whose tiles they then pull from the work counter as they finish, so
     // that the last tiles go to the workgroups that are free.
     const int G = (int)gridDim.x;
-    const int n_tiles = a.n_frames_dev ? *a.n_frames_dev * a.tiles_per_frame : a.n_tiles;
-    const int n_static = a.persistent ? max(n_tiles / G - 1, 0) * G : 0;
-    if (threadIdx.x == 0) {  // read after the loop's first barrier
-        S.bp = P.bp;
-        O.wgbest.key = 0ull;
-        O.wgbest.t_team = INFINITY;
-        O.wgbest.t_opp = INFINITY;
-        O.wgbest.v0 = 0.0f;
-        O.wgbest.pad = 0.0f;
-    }
+    const int n_tiles = args.n_frames_dev ? *args.n_frames_dev * args.tiles_per_frame : args.n_tiles;
+    const int n_static = args.persistent ? max(n_tiles / G - 1, 0) * G : 0;
+    if (threadIdx.x == 0) S.bp = args.P.bp;  // read after the loop's first barrier
+    // a persistent grid's workgroup b sits on XCD b % 8, and so do its static
+    // tiles when the grid is a multiple of 8; its dynamic tiles keep that class
+    // too, from one counter per class, so that the tiles an XCD runs together
+    // write neighbouring chunks (below) and its L2 merges their lines.  C
+    // classes: every class has a workgroup (a grid under 8 workgroups uses G
+    // classes).
+    const int C = min(G, 8), xcd = (int)(blockIdx.x % (unsigned)C);
+    // the lane's best pass of the tile, or of all the workgroup's tiles with
+    // one record per workgroup
+    unsigned long long bkey = 0ull;
+    float btt = INFINITY, bto = INFINITY, bv0 = 0.0f;
     while (true) {
         // the previous tile (its staged results and records) is finished
         __syncthreads();
+        const LaunchArgs &a = fresh_args<LaunchArgs>();
         int t = (int)blockIdx.x + iter * G;
         if (a.persistent && t >= n_static) {
-            // a persistent grid's workgroup b sits on XCD b % 8, and so do
-            // its static tiles when the grid is a multiple of 8; its dynamic
-            // tiles keep that class too, from one counter per class, so
-            // that the tiles an XCD runs together write neighbouring chunks
-            // (below) and its L2 merges their lines.  C classes: every class
-            // has a workgroup (a grid under 8 workgroups uses G classes).
-            const int C = min(G, 8);
-            const int x = (int)blockIdx.x % C;
-            if (threadIdx.x == 0) s_tile = n_static + C * (int)atomicAdd(a.counter + x, 1u) + x;
+            if (threadIdx.x == 0)
+                s_tile = n_static + C * (int)atomicAdd(a.counter + xcd, 1u) + xcd;
             __syncthreads();
-            t = s_tile;
+            t = uni(s_tile);
         }
         if (t >= n_tiles) break;
         ++iter;
+        // (the tile and its window are the same for every lane: scalar)
         TileDev tile;
         if (a.tiles_per_frame > 0) {
-            tile.win = t / a.tiles_per_frame;
-            tile.p0 = (t - tile.win * a.tiles_per_frame) * TP;
+            tile.win = (int)((unsigned)t / (unsigned)a.tiles_per_frame);
+            tile.at = t - tile.win * a.tiles_per_frame;
         } else {
             tile = a.tiles[t];
         }
-        const WinDev W = a.wins[tile.win];
+        const int tk = uni(tile.at);
+        WinDev W = a.wins[uni(tile.win)];
+        W.h = unif(W.h);
+        W.halfNx = unif(W.halfNx);
+        W.halfNy = unif(W.halfNy);
+        W.i0 = uni(W.i0);
+        W.j0 = uni(W.j0);
+        W.nx = uni(W.nx);
+        W.frame = uni(W.frame);
+        W.npts = uni(W.npts);
+        W.n_tiles = uni(W.n_tiles);
+        W.elem_base = uni(W.elem_base);
+        W.out_base = (int64_t)(((uint64_t)(uint32_t)uni((int)((uint64_t)W.out_base >> 32)) << 32) |
+                               (uint32_t)uni((int)(uint32_t)W.out_base));
         if (W.frame != cur_frame) {
             stage_frame(a.P, S.bp, a.frames, a.robots, a.variants, W.frame, S);
             __syncthreads();
             cur_frame = W.frame;
-            const int nv = S.n_var;
-            myv0 = l < nv ? S.v0[l] : 0.0f;
-            mytype = l < nv ? S.type[l] : -1;
-            myvid = l < nv ? S.vidx[l] : 0;
         }
-        const int n_var = S.n_var;
+        const int n_var = uni(S.n_var);
         // the window's points in chunks of CH; tile k of a window cut into T
         // tiles holds chunks pk, pk + T, pk + 2T, ...: every tile samples the
         // whole window, so tiles cost alike (neighbouring points cost alike,
@@ -933,127 +1124,161 @@ __global__ void __launch_bounds__(512, 4) search_kernel(LaunchArgs a)
         // is point (pk + (s / CH) T) CH + s % CH; only the window's last
         // chunk can be short, and it is the last chunk of its tile.
         constexpr int CH = 4;
-        const int tk = tile.p0 / TP;
-        const int NC = (W.npts + CH - 1) / CH, cpt = TP / CH;
-        const int Tw = max((NC + cpt - 1) / cpt, 1);  // = ceil(npts / TP)
+        const int NC = (int)((unsigned)(W.npts + CH - 1) / CH), cpt = TP / CH;
+        const int Tw = W.n_tiles;  // ceil(npts / TP)
         const int pk = (tk & 7) * (Tw >> 3) + min(tk & 7, Tw & 7) + (tk >> 3);
-        const int nch = tk < Tw ? min(cpt, (NC - pk + Tw - 1) / Tw) : 0;
+        int nch = tk < Tw ? cpt : 0;
+        while (nch > 0 && (int64_t)pk + (int64_t)(nch - 1) * Tw >= NC) --nch;
         const int npts =
             nch > 0 ? (nch - 1) * CH + min(CH, W.npts - (pk + (nch - 1) * Tw) * CH) : 0;
-        unsigned long long bkey = 0ull;
-        float btt = INFINITY, bto = INFINITY, bv0 = 0.0f;
-        // the wave's points in pairs, slots s0 and s0 + nw: one pass of the
-        // path-frame stage frames both (lanes 0-31 the first point's robots,
-        // lanes 32-63 the second's; a lone last point is framed twice)
-        for (int s0 = w; s0 < npts; s0 += 2 * nw) {
-            const int n_pair = s0 + nw < npts ? 2 : 1;
-            const int s1 = n_pair == 2 ? s0 + nw : s0;
-            float LA0, LA1;
-            {
-                const int sl = l < 32 ? s0 : s1;
-                const int p = (pk + (sl / CH) * Tw) * CH + (sl & (CH - 1));
-                const int j = p / W.nx, i = p - j * W.nx;
-                const float mi = (float)(W.i0 + i) - W.halfNx;
-                const float mj = (float)(W.j0 + j) - W.halfNy;
-                const float LAl = path_frame(S, P, PR + (w * 2 + (l >> 5)) * PR_ENTRIES,
-                                             S.n_tm + S.n_op, S.n_tm,
-                                             (double)W.h * (double)mi, (double)W.h * (double)mj,
-                                             (double)unif(S.bx), (double)unif(S.by), l & 31);
-                LA0 = readlane_f(LAl, 0);
-                LA1 = readlane_f(LAl, 32);
-            }
-            for (int g = 0; g < n_pair; ++g) {
-            const int slot = g ? s1 : s0;
+        if (!args.wg_records) {
+            bkey = 0ull;
+            btt = bto = INFINITY;
+            bv0 = 0.0f;
+        }
+        // the wave's points in pairs of neighbours, slots s0 and s0 + 1, one
+        // per half of the wave (a lone last point is taken by both halves,
+        // which write the same values)
+        for (int s0 = 2 * w; s0 < npts; s0 += 2 * nw) {
+            const int slot = min(s0 + h, npts - 1);
             const int p = (pk + (slot / CH) * Tw) * CH + (slot & (CH - 1));
-            const int j = p / W.nx, i = p - j * W.nx;
+            const int j = (int)((unsigned)p / (unsigned)W.nx), i = p - j * W.nx;
             const float mi = (float)(W.i0 + i) - W.halfNx;
             const float mj = (float)(W.j0 + j) - W.halfNy;
             const float cx = W.h * mi, cy = W.h * mj;
             const double cx64 = (double)W.h * (double)mi, cy64 = (double)W.h * (double)mj;
-            float sc, tt, to, pv0;
-            int fe;
-            eval_point<KPL, POWER>(S, P, PR + (w * 2 + g) * PR_ENTRIES, PMX + w * PM_ROWS * KPL * 64,
-                                   myv0, mytype, cx,
-                                   cy, cx64, cy64, g ? LA1 : LA0, sc, fe, tt, to, pv0, a);
-            if (POWER && l == 0 && a.v0_out) a.v0_out[W.out_base + p] = pv0;
-            unsigned long long key = 0ull;
-            if (fe) {
-                uint32_t lin = (uint32_t)(W.elem_base + myvid * W.npts + p);
-                key = ((unsigned long long)ordered_bits(sc) << 32) |
-                      (unsigned long long)(0xFFFFFFFFu - lin);
+            const float bx = unif(S.bx), by = unif(S.by);
+            const int n_tm = uni(S.n_tm), n_op = uni(S.n_op);
+            float4 *const pr = PR + (w * 2 + h) * PR_ENTRIES;
+            const float LA = path_frame(S, fresh_args<LaunchArgs>().P, pr, n_tm + n_op, n_tm, cx64, cy64, (double)bx,
+                                        (double)by, hl);
+            const float ex = cx - bx, ey = cy - by;
+            const float d = hsqrt(fmaf(ex, ex, ey * ey));
+            const double ex64 = cx64 - (double)bx, ey64 = cy64 - (double)by;
+            const double d64 = sqrt64(ex64 * ex64 + ey64 * ey64);
+            int kt[2], ko[2];
+            double v0 = 0.0;
+            pair_crossings<KPH, POWER>(S, pr, PMX + (w * 2 + h) * HROWS, d, LA, kt, ko, d64, v0);
+            // finish: the lanes of a half are its point's variants
+            const LaunchArgs &a = fresh_args<LaunchArgs>();
+            const DevParams &P = a.P;
+            float tt[2], to[2], mc[2];
+            bool feas[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                tt[c] = INFINITY;
+                to[c] = INFINITY;
+                mc[c] = 0.0f;
+                feas[c] = false;
+                const int v = 32 * c + hl;
+                if (c > 0 && (POWER || n_var <= 32)) continue;
+                if (v < n_var && (!POWER || v0 > 0.0)) {
+                    const VarConst vc = POWER ? var_const(P.bp, DPPS_FLAT, (float)v0) : S.vc[v];
+                    const bool reach = d64 >= 1e-9 && d64 <= vc.D && d64 >= vc.sf_reach;
+                    double t1 = INFINITY, t2 = INFINITY;
+                    if (reach) {
+                        if (kt[c] < K) t1 = ball_time64(vc, (double)(kt[c] + 1) * P.invK_d * d64);
+                        if (ko[c] < K) t2 = ball_time64(vc, (double)(ko[c] + 1) * P.invK_d * d64);
+                    }
+                    const bool tfin = t1 < INFINITY;
+                    const double m = !tfin ? -INFINITY : (t2 < INFINITY ? t2 - t1 : INFINITY);
+                    feas[c] = reach && tfin && m >= P.margin_d;
+                    tt[c] = (float)t1;
+                    to[c] = (float)t2;
+                    mc[c] = fminf(fmaxf((float)m, 0.0f), P.margin_cap);
+                }
             }
-            if (key > bkey) {
-                bkey = key;
-                btt = tt;
-                bto = to;
-                bv0 = POWER ? pv0 : myv0;
+            // the open goal angle (lanes = opponents) and the distance to the
+            // goal enter only feasible scores
+            float ang = 0.0f, dterm = 0.0f;
+            if (__ballot(feas[0] || feas[1])) {
+                ang = open_angle_pair(S, P, cx, cy, n_op, n_tm);
+                const float gx = cx - P.goal_x;
+                const float dg = hsqrt(fmaf(gx, gx, cy * cy));
+                dterm = fmaf(-dg, P.inv_dist_norm, 1.0f);
+            }
+            if (POWER && hl == 0 && a.v0_out) a.v0_out[W.out_base + p] = (float)v0;
+            unsigned long long pkey = 0ull;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                if (c > 0 && (POWER || n_var <= 32)) continue;
+                const int v = 32 * c + hl;
+                const int vid = v < n_var ? S.vidx[v] : 0;  // the caller's index
+                float sc = -INFINITY;
+                unsigned long long key = 0ull;
+                if (feas[c]) {
+                    sc = fmaf(P.w_ang_pi, ang, fmaf(P.w_dist, dterm, P.w_margin * mc[c]));
+                    const uint32_t lin = (uint32_t)(W.elem_base + vid * W.npts + p);
+                    key = ((unsigned long long)ordered_bits(sc) << 32) |
+                          (unsigned long long)(0xFFFFFFFFu - lin);
+                }
+                if (key > bkey) {
+                    bkey = key;
+                    btt = tt[c];
+                    bto = to[c];
+                    bv0 = POWER ? (float)v0 : S.v0[v];
+                }
+                if (reduced) {
+                    pkey = key > pkey ? key : pkey;
+                } else if (v < n_var) {
+                    OS[vid * TP + slot] = sc;
+                    OM[vid * TP + slot] = (uint8_t)feas[c];
+                    const int64_t e = W.out_base + (int64_t)vid * W.npts + p;
+                    if (a.t_team) a.t_team[e] = tt[c];
+                    if (a.t_opp) a.t_opp[e] = to[c];
+                }
             }
             if (reduced) {
-                unsigned long long pk = wave_max_u64(key);
-                if (l == 0) {
-                    int64_t o = W.out_base + p;
+                pkey = half_prefix_max_u64(pkey);
+                if (hl == 31) {
+                    const int64_t o = W.out_base + p;
                     if (a.score)
-                        a.score[o] = pk ? unordered_bits((uint32_t)(pk >> 32)) : -INFINITY;
+                        a.score[o] = pkey ? unordered_bits((uint32_t)(pkey >> 32)) : -INFINITY;
                     if (a.mask) {
-                        uint32_t lin = 0xFFFFFFFFu - (uint32_t)pk;
-                        a.mask[o] = pk ? (uint8_t)((lin - (uint32_t)W.elem_base) / (uint32_t)W.npts)
-                                       : (uint8_t)255;
+                        const uint32_t lin = 0xFFFFFFFFu - (uint32_t)pkey;
+                        a.mask[o] = pkey ? (uint8_t)((lin - (uint32_t)W.elem_base) /
+                                                     (uint32_t)W.npts)
+                                         : (uint8_t)255;
                     }
                 }
-            } else if (l < n_var) {
-                OS[myvid * TP + slot] = sc;
-                OM[myvid * TP + slot] = (uint8_t)fe;
-                if (a.t_team) a.t_team[W.out_base + (int64_t)myvid * W.npts + p] = tt;
-                if (a.t_opp) a.t_opp[W.out_base + (int64_t)myvid * W.npts + p] = to;
-            }
             }
         }
-        // the wave's best pass (and its times), then the tile's
-        const unsigned long long wk = wave_max_u64(bkey);
-        const unsigned long long who = __ballot(bkey == wk);
-        const int src = who ? __builtin_ctzll(who) : 0;
-        const float wtt = readlane_f(btt, src), wto = readlane_f(bto, src);
-        const float wv0 = readlane_f(bv0, src);
-        if (l == 0) {
-            O.wbest[w].key = wk;
-            O.wbest[w].t_team = wtt;
-            O.wbest[w].t_opp = wto;
-            O.wbest[w].v0 = wv0;
-            O.wbest[w].pad = 0.0f;
-        }
+        // the staged maps are complete; with one record per tile so are the
+        // waves' best passes
+        if (!args.wg_records) wave_best(O, w, bkey, btt, bto, bv0);
         __syncthreads();
-        if (w == 0) {
-            // lanes < nw hold the waves' records; the largest key wins (keys
-            // of different waves differ unless both are 0)
-            const unsigned long long k = l < nw ? O.wbest[l].key : 0ull;
-            const unsigned long long tk = wave_max_u64(k);
-            const unsigned long long at = __ballot(k == tk && l < nw);
-            if (l == (int)__builtin_ctzll(at)) {
-                TileRec r = O.wbest[l];
-                if (r.key == 0ull) {
-                    r.t_team = INFINITY;
-                    r.t_opp = INFINITY;
-                }
-                if (!a.wg_records)
-                    a.tile_rec[t] = r;
-                else if (r.key > O.wgbest.key)
-                    O.wgbest = r;
-            }
-        }
+        if (!args.wg_records && w == 0) group_best(O, nw, args.tile_rec + t);
         if (!reduced) {
-            const int tot = n_var * npts;
-            for (int e = threadIdx.x; e < tot; e += blockDim.x) {
-                const int v = e / npts, slot = e - v * npts;
-                const int64_t o = W.out_base + (int64_t)v * W.npts + (pk + (slot / CH) * Tw) * CH +
-                                  (slot & (CH - 1));
-                if (a.score) a.score[o] = OS[v * TP + slot];
-                if (a.mask) a.mask[o] = OM[v * TP + slot];
+            // one variant's piece of one chunk per thread: four scores in one
+            // store and their flags in another (the last chunk of the window
+            // may be short)
+            const LaunchArgs &a = fresh_args<LaunchArgs>();
+            const float rn = hrcp((float)nch);
+            for (int e = threadIdx.x; e < n_var * nch; e += blockDim.x) {
+                const int v = (int)(((float)e + 0.5f) * rn), c = e - v * nch;
+                const int first = (pk + c * Tw) * CH;
+                const int64_t o = W.out_base + (int64_t)v * W.npts + first;
+                const float *const sv = OS + v * TP + c * CH;
+                const uint8_t *const mv = OM + v * TP + c * CH;
+                if (first + CH <= W.npts) {
+                    const float4 x = *(const float4 *)sv;
+                    const uint32_t y = *(const uint32_t *)mv;
+                    if (a.score) __builtin_memcpy(a.score + o, &x, sizeof x);
+                    if (a.mask) __builtin_memcpy(a.mask + o, &y, sizeof y);
+                } else {
+                    for (int q = 0; q < W.npts - first; ++q) {
+                        if (a.score) a.score[o + q] = sv[q];
+                        if (a.mask) a.mask[o + q] = mv[q];
+                    }
+                }
             }
         }
     }
-    // (wave 0 made the last update of the workgroup's best before the barrier
-    // that ended the loop)
-    if (a.wg_records && threadIdx.x == 0) a.tile_rec[blockIdx.x] = O.wgbest;
+    if (args.wg_records) {
+        wave_best(O, w, bkey, btt, bto, bv0);
+        __syncthreads();
+        if (w == 0) group_best(O, nw, args.tile_rec + blockIdx.x);
+    }
 }
 
 // One workgroup per frame: reduce the frame's tile records to its best pass;
@@ -1157,11 +1382,11 @@ __global__ void __launch_bounds__(256) finalize_kernel(LaunchArgs a)
         V.i0 = 0;
         V.j0 = 0;
         V.nx = a.fb.nx;
-        V.ny = a.fb.ny;
         V.halfNx = 0.5f * (float)(a.fb.nx - 1);
         V.halfNy = 0.5f * (float)(a.fb.ny - 1);
         V.frame = slot;
         V.npts = a.fb.nx * a.fb.ny;
+        V.n_tiles = a.fb.tiles_per_frame;
         V.elem_base = 0;
         V.out_base = 0;
         a.fb.wins[slot] = V;
@@ -1176,12 +1401,13 @@ static int launch_kpl(const LaunchArgs &a, int waves_per_wg, int grid, hipStream
 {
     if (e0) (void)hipEventRecord(e0, st);
     if (a.n_tiles > 0 && grid > 0) {
-        const size_t lds = search_lds_bytes(KPL * 64, waves_per_wg, a.tile_points);
+        const size_t lds = search_lds_bytes(KPL * 64, waves_per_wg, a.tile_points,
+                                            a.max_variants);
         if (a.power)
-            hipLaunchKernelGGL((search_kernel<KPL, true>), dim3(grid), dim3(64 * waves_per_wg),
+            hipLaunchKernelGGL((search_kernel<2 * KPL, true>), dim3(grid), dim3(64 * waves_per_wg),
                                lds, st, a);
         else
-            hipLaunchKernelGGL((search_kernel<KPL, false>), dim3(grid), dim3(64 * waves_per_wg),
+            hipLaunchKernelGGL((search_kernel<2 * KPL, false>), dim3(grid), dim3(64 * waves_per_wg),
                                lds, st, a);
     }
     if (e1) (void)hipEventRecord(e1, st);
@@ -1424,9 +1650,9 @@ __device__ RayOut ray_direction(const StageLDS &S, const DevParams &P, float4 *p
     const double2 u = dirs[d];
     const double ux = u.x, uy = u.y;
     const double L = ray_length(P, bx, by, ux, uy);
-    path_frame_dir<true>(S, P, pr, n_tm + n_op, n_tm, L * (double)P.A, ux, uy, bx, by, l);
+    path_frame_dir<FULL_WAVE>(S, P, pr, n_tm + n_op, n_tm, L * (double)P.A, ux, uy, bx, by, l);
     int my_kt, my_ko;
-    sbip_crossings<KPL, false>(S, P, pr, pm, myv0, mytype, (float)L, (float)(L * (double)P.A), my_kt,
+    sbip_crossings<KPL>(S, P, pr, pm, myv0, mytype, (float)L, (float)(L * (double)P.A), my_kt,
                         my_ko);
 
     RayOut o;
@@ -1529,7 +1755,7 @@ __global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs a)
         }
         const int n_var = S.n_var;
         const int64_t base = a.frames[f].ray_base;
-        const int nd = min(a.tile_dirs, a.n_dirs - tile.p0);
+        const int nd = min(a.tile_dirs, a.n_dirs - tile.at);
         // the wave's best so far: its key in a uniform register, its record
         // in the wave's LDS slot (written by the lane that holds it)
         unsigned long long wbk = 0ull;
@@ -1541,7 +1767,7 @@ __global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs a)
         // each wave takes slot w, then claims the tile's next free slot as it
         // finishes one (directions differ in cost: the waves end together)
         for (int slot = w; slot < nd;) {
-            const int d = tile.p0 + slot;
+            const int d = tile.at + slot;
             const RayOut o = ray_direction<KPL>(S, P, PR[w], PMX + w * PM_ROWS * KPL * 64, myv0,
                                                 mytype, myvid, d, a.dirs, a.w_time,
                                                 a.w_refract);
@@ -1719,14 +1945,15 @@ __device__ __forceinline__ void shot_opponents(const float4 *pr, const DevParams
                                                float D, float LA, float tbm, float (&T)[KPL])
 {
     const float tbh = tbm * (1.0f + 1.0f / 262144.0f);
+    const RobotK rk(P);
     int need = n_op;
     int j = 0;
     for (; j + 1 < need; j += 2) {
         const float4 ra = pr[n_tm + j], rb = pr[n_tm + j + 1];
 #pragma unroll
         for (int q = 0; q < KPL; ++q)
-            T[q] = fminf(T[q], fminf(robot_time_h<true>(ra, fs[q], LA, P),
-                                     robot_time_h<true>(rb, fs[q], LA, P)));
+            T[q] = fminf(T[q], fminf(robot_time_h<true>(ra, fs[q], LA, rk),
+                                     robot_time_h<true>(rb, fs[q], LA, rk)));
         if (j < 4 && need > j + 2) {
             float m = INFINITY;
 #pragma unroll
@@ -1746,7 +1973,7 @@ __device__ __forceinline__ void shot_opponents(const float4 *pr, const DevParams
     if (j < need) {
         const float4 r = pr[n_tm + j];
 #pragma unroll
-        for (int q = 0; q < KPL; ++q) T[q] = fminf(T[q], robot_time_h<true>(r, fs[q], LA, P));
+        for (int q = 0; q < KPL; ++q) T[q] = fminf(T[q], robot_time_h<true>(r, fs[q], LA, rk));
     }
 }
 
@@ -1820,7 +2047,7 @@ __device__ dpps_shot shot_origin(const StageLDS &S, const DevParams &P, float4 *
     const float aim = gap > 0.0f ? fmaf(0.5f, gap, g0) : atan2f(-fy, (float)dxg);
     const double ux = (double)cosf(aim), uy = (double)sinf(aim);
     const double L = dxg / ux;
-    path_frame_dir<true>(S, P, pr, n_tm + n_op, n_tm, L * (double)P.A, ux, uy, cx, cy, l);
+    path_frame_dir<PLAIN>(S, P, pr, n_tm + n_op, n_tm, L * (double)P.A, ux, uy, cx, cy, l);
     const float Lf = (float)L, LA = (float)(L * (double)P.A);
     const float D = (float)vc.D;
     float fs[KPL], sk[KPL], tb[KPL], T[KPL];
@@ -1876,10 +2103,11 @@ __global__ void __launch_bounds__(512) shot_kernel(ShotArgs a)
         if (l == 0) a.ball[f] = r;
         return;
     }
-    const int np = min(a.tile_points, W.npts - tile.p0);
+    const int p0 = tile.at * a.tile_points;
+    const int np = min(a.tile_points, W.npts - p0);
     const int nw = blockDim.x >> 6;
     for (int slot = w; slot < np; slot += nw) {
-        const int p = tile.p0 + slot;
+        const int p = p0 + slot;
         const int j = p / W.nx, i = p - j * W.nx;
         const double cx = (double)W.h * ((double)(W.i0 + i) - (double)W.halfNx);
         const double cy = (double)W.h * ((double)(W.j0 + j) - (double)W.halfNy);
@@ -2075,17 +2303,17 @@ int launch_search(const LaunchArgs &a, int waves_per_wg, int grid, void *stream,
     }
 }
 
-int search_occupancy(int K, int waves_per_wg, int tile_points)
+int search_occupancy(int K, int waves_per_wg, int tile_points, int max_variants)
 {
     int n = 0;
     hipError_t e = hipErrorInvalidValue;
     const int bs = 64 * waves_per_wg;
-    const size_t lds = search_lds_bytes(K, waves_per_wg, tile_points);
+    const size_t lds = search_lds_bytes(K, waves_per_wg, tile_points, max_variants);
     switch (K / 64) {
-    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<1, false>, bs, lds); break;
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<2, false>, bs, lds); break;
-    case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<3, false>, bs, lds); break;
-    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<4, false>, bs, lds); break;
+    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<2, false>, bs, lds); break;
+    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<4, false>, bs, lds); break;
+    case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<6, false>, bs, lds); break;
+    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<8, false>, bs, lds); break;
     default: break;
     }
     return e == hipSuccess && n > 0 ? n : 1;

@@ -633,17 +633,17 @@ __device__ void rescore_windows(const RescoreTables &rt, int f, int k, int cell,
         W.i0 = i0;
         W.j0 = j0;
         W.nx = nx;
-        W.ny = ny;
         W.halfNx = 0.5f * (float)(rt.fine_nx - 1);
         W.halfNy = 0.5f * (float)(rt.fine_ny - 1);
         W.frame = f;
         W.npts = nx * ny;
+        W.n_tiles = 1;
         W.elem_base = (incl - nx * ny) * F.n_variants;
         W.out_base = 0;
         rt.wins[(size_t)f * k + t] = W;
         TileDev T;
         T.win = f * k + t;
-        T.p0 = 0;
+        T.at = 0;
         rt.tiles[(size_t)f * k + t] = T;
     }
     if (t == 0) {

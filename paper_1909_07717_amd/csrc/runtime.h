@@ -25,6 +25,7 @@ struct HostTables {
     std::vector<WinDev> wins;
     std::vector<TileDev> tiles;
     int64_t points = 0;
+    int32_t max_variants = 1;  // most variants of any frame
 };
 
 // Validate host frames and build their device tables; tile_points 0 builds
