@@ -407,9 +407,6 @@ int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t s
                      bool timed, const dpps_power_params *power, float *v0_out)
 {
     if (!out) return fail(DPPS_E_INVALID, "outputs is NULL");
-    if (b->tile_points != c->tile_points)
-        return fail(DPPS_E_INVALID, "batch built for tile_points %d, context now uses %d",
-                    b->tile_points, c->tile_points);
     LaunchArgs a;
     memset(&a, 0, sizeof a);
     a.P = c->P;
@@ -420,7 +417,7 @@ int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t s
     a.tiles = b->d_tiles;
     a.n_tiles = (int32_t)b->T.tiles.size();
     a.n_frames = b->n_frames;
-    a.tile_points = c->tile_points;
+    a.tile_points = b->tile_points;
     a.max_variants = b->T.max_variants;
     // the search kernel cuts a tile into chunks of 4 points
     if (a.tile_points < 4 || a.tile_points % 4)
@@ -442,7 +439,7 @@ int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t s
         a.v0_out = v0_out;
     }
     int per_cu = c->wg_per_cu > 0 ? c->wg_per_cu
-                                  : search_occupancy(c->p.n_samples, c->waves, c->tile_points,
+                                  : search_occupancy(c->p.n_samples, c->waves, b->tile_points,
                                                      b->T.max_variants);
     int64_t cap = (int64_t)c->n_cu * per_cu;
     int grid = (int)(a.n_tiles < cap ? a.n_tiles : cap);
@@ -638,6 +635,7 @@ int dpps_set_launch(dpps_ctx *c, int32_t tile_points, int32_t waves_per_wg, int3
         if (tile_points < 8 || tile_points > 64 || tile_points % 8)
             return fail(DPPS_E_INVALID, "tile_points must be a multiple of 8 in [8, 64]");
         c->tile_points = tile_points;
+        c->tile_set = true;
     }
     if (waves_per_wg) {
         if (waves_per_wg != 1 && waves_per_wg != 2 && waves_per_wg != 4 && waves_per_wg != 8)
@@ -676,6 +674,35 @@ int dpps_get_launch(const dpps_ctx *c, int32_t *tile_points, int32_t *waves_per_
 
 }  // extern "C"
 
+// Points per tile of a host request while the caller has not set a tile size:
+// the largest of 64, 32, 16 that still gives every resident workgroup (4 per
+// CU) two and a half tiles and whose staged maps (variants x points) stay
+// small, else the default.  A tile costs each of its waves about 200 VALU
+// instructions and two barriers beside its points (a pair of points: 1000 to
+// 2500), while the last round needs tiles to spread: the full frame (43 621
+// points) runs 118 us at 8 points and 116 at 16, the passing power of the same
+// points 95 and 91, 16 mixed requests (307 000 points) 461 at 8 and 400 at 64.  Malformed requests get the default
+// and are refused by build_tables.
+static int request_tile(const dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
+                        const dpps_window *windows)
+{
+    if (c->tile_set || n_frames < 1 || !frames || !windows) return c->tile_points;
+    int64_t pts = 0;
+    int nv = 1;
+    for (int32_t f = 0; f < n_frames; ++f) {
+        const dpps_frame &F = frames[f];
+        if (F.n_windows < 0 || F.window_off < 0) return c->tile_points;
+        for (int w = 0; w < F.n_windows; ++w) {
+            const dpps_window &W = windows[F.window_off + w];
+            if (W.nx > 0 && W.ny > 0) pts += (int64_t)W.nx * W.ny;
+        }
+        if (F.n_variants > nv) nv = F.n_variants;
+    }
+    for (int tp = 64; tp > c->tile_points; tp /= 2)
+        if (pts >= (int64_t)10 * c->n_cu * tp && tp * nv <= 2048) return tp;
+    return c->tile_points;
+}
+
 // Validate host frames and copy their tables into a batch the context owns
 // (c->scratch or c->fallback), through the pinned staging buffer and an
 // asynchronous copy on st; device memory grows only when a request is larger
@@ -684,10 +711,11 @@ int stage_batch(dpps_ctx *c, dpps_batch *b, int32_t n_frames, const dpps_frame *
                 const dpps_robot *robots, const dpps_window *windows,
                 const dpps_variant *variants, hipStream_t st)
 {
-    int rc = build_tables(&c->p, n_frames, frames, robots, windows, variants, c->tile_points, b->T);
+    const int tp = request_tile(c, n_frames, frames, windows);
+    int rc = build_tables(&c->p, n_frames, frames, robots, windows, variants, tp, b->T);
     if (rc) return rc;
     b->n_frames = n_frames;
-    b->tile_points = c->tile_points;
+    b->tile_points = tp;
     return stage_tables(c, b, st);
 }
 

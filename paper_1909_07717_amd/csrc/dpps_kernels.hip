@@ -78,7 +78,6 @@ struct StageLDS {
     int32_t vel_ok;           // every robot's speed is at most vmax
     float bx, by;
     float lim[4];             // arrival limit per quarter of a path, over sqrt(length)
-    BallParams64 bp;          // persistent kernels: written once at the start
 };
 
 // A wave's path-frame block: MAX_ROB entries, then 64 words of bound keys.
@@ -153,63 +152,50 @@ __device__ VarConst var_const(const BallParams64 &B, int type, float v0f)
     return c;
 }
 
-// Stage the frame into LDS: interceptors (passer dropped), scaled by amax so
-// that the robot model runs in units where the acceleration limit is 1; the
-// per-variant ball constants in float64 (from B: persistent kernels pass
-// their LDS copy, so that the float64 parameters do not hold scalar
-// registers across the whole tile loop).  Called by all threads of a block.
-__device__ void stage_frame(const DevParams &P, const BallParams64 &B, const FrameDev *frames,
-                            const dpps_robot *robots, const dpps_variant *variants, int f,
-                            StageLDS &S)
+// Stage frame f (its record F) into LDS: interceptors (passer dropped), the
+// per-variant ball constants in float64, the counts and flags.  Done by the
+// block's first wave with one round of loads: the lanes are robots and
+// variants, the flags ballots, the variants' ranks lane reads (the block waits
+// for this, so its length is latency; loops of dependent loads on one thread
+// cost several microseconds).
+__device__ void stage_frame(const DevParams &P, const FrameDev &F, const dpps_robot *robots,
+                            const dpps_variant *variants, int f, StageLDS &S)
 {
-    const FrameDev F = frames[f];
-    int tid = threadIdx.x;
-    int nrob = F.n_team + F.n_opp;
-    if (tid < nrob) {
-        dpps_robot r = robots[F.robot_off + tid];
-        int slot;
-        if (tid < F.n_team) {
-            slot = tid < F.passer ? tid : tid - 1;
-        } else {
-            slot = F.n_team - 1 + (tid - F.n_team);
-        }
-        if (tid != F.passer || tid >= F.n_team) S.rob[slot] = make_float4(r.x, r.y, r.vx, r.vy);
+    const int tid = threadIdx.x;
+    if (tid >= 64) return;
+    const int nrob = F.n_team + F.n_opp, nv = F.n_variants;
+    dpps_robot r = {0.0f, 0.0f, 0.0f, 0.0f};
+    dpps_variant v = {-1, 0.0f};
+    if (tid < nrob) r = robots[F.robot_off + tid];
+    if (tid < nv) v = variants[F.variant_off + tid];
+    if (tid < nrob && tid != F.passer)
+        S.rob[tid < F.passer ? tid : tid - 1] = make_float4(r.x, r.y, r.vx, r.vy);
+    const bool over = tid < nrob && !(fmaf(r.vx, r.vx, r.vy * r.vy) <= P.V * P.V);
+    const bool all_slow = __ballot(over) == 0ull;
+    const bool hf = __ballot(v.type == DPPS_FLAT) != 0ull;
+    const bool hc = __ballot(v.type == DPPS_CHIP) != 0ull;
+    // staged in order of kick type, then speed (stable): within a type the
+    // first crossing never moves earlier as the speed grows
+    int rank = 0;
+    for (int j = 0; j < nv; ++j) {
+        const int tj = readlane_i(v.type, j);
+        const float vj = readlane_f(v.v0, j);
+        rank += tj < v.type || (tj == v.type && (vj < v.v0 || (vj == v.v0 && j < tid)));
     }
-    if (tid < F.n_variants) {
-        // staged in order of kick type, then speed (stable): within a type
-        // the first crossing never moves earlier as the speed grows
-        const dpps_variant v = variants[F.variant_off + tid];
-        int rank = 0;
-        for (int j = 0; j < F.n_variants; ++j) {
-            const dpps_variant u = variants[F.variant_off + j];
-            rank += u.type < v.type ||
-                    (u.type == v.type && (u.v0 < v.v0 || (u.v0 == v.v0 && j < tid)));
-        }
+    if (tid < nv) {
         S.v0[rank] = v.v0;
         S.type[rank] = v.type;
         S.vidx[rank] = tid;
-        S.vc[rank] = var_const(B, v.type, v.v0);
+        S.vc[rank] = var_const(P.bp, v.type, v.v0);
     }
+    if (tid < 4) S.lim[tid] = fmaxf(hf ? P.f_lim[tid] : 0.0f, hc ? P.c_lim[tid] : 0.0f);
     if (tid == 0) {
         S.n_tm = F.n_team - 1;
         S.n_op = F.n_opp;
-        S.n_var = F.n_variants;
-        int hf = 0, hc = 0;
-        for (int v = 0; v < F.n_variants; ++v) {
-            int t = variants[F.variant_off + v].type;
-            hf |= t == DPPS_FLAT;
-            hc |= t == DPPS_CHIP;
-        }
+        S.n_var = nv;
         S.has_flat = hf;
         S.has_chip = hc;
-        for (int b = 0; b < 4; ++b)
-            S.lim[b] = fmaxf(hf ? P.f_lim[b] : 0.0f, hc ? P.c_lim[b] : 0.0f);
-        int ok = 1;
-        for (int r = 0; r < nrob; ++r) {
-            const dpps_robot R = robots[F.robot_off + r];
-            ok &= fmaf(R.vx, R.vx, R.vy * R.vy) <= P.V * P.V;
-        }
-        S.vel_ok = ok;
+        S.vel_ok = all_slow;
         S.frame = f;
         S.bx = F.ball_x;
         S.by = F.ball_y;
@@ -1021,6 +1007,22 @@ __device__ __forceinline__ void group_best(const OutLDS &O, int nw, TileRec *rec
     if (l == (int)__builtin_ctzll(at)) *rec = O.wbest[l];
 }
 
+// Tile t of the launch: from the list, or implicit (tables built on the device).
+__device__ __forceinline__ TileDev tile_at(const LaunchArgs &a, int t)
+{
+    if (a.tiles_per_frame == 0) return a.tiles[t];
+    const int win = (int)((unsigned)t / (unsigned)a.tiles_per_frame);
+    return TileDev{win, t - win * a.tiles_per_frame};
+}
+
+// Word l of a window's record in lane l.
+__device__ __forceinline__ int window_words(const LaunchArgs &a, int win)
+{
+    static_assert(sizeof(WinDev) == 48, "12 words");
+    const int l = lane_id();
+    return l < 12 ? ((const int *)(a.wins + win))[l] : 0;
+}
+
 // Bound by VALU issue.  One point per half of a wave rather than per wave: the
 // bound tests, prefix maxima, searches, the float64 finish (32 lanes are
 // variants) and the open angle cost a pair of points what they cost one,
@@ -1030,10 +1032,12 @@ __device__ __forceinline__ void group_best(const OutLDS &O, int nw, TileRec *rec
 // frame (8v8, 43 621 points, 32 variants, K = 256) takes 123 us instead of
 // 142 and 52.5 M VALU instructions instead of 66.9 M; 256 uneven windows at
 // 8 variants, K = 128, 3.40 ms instead of 4.42; passing power 96 us instead of 122.
-// At most 128 VGPRs, so four waves fit on each SIMD.  POWER: one flat pass
+// At most 128 VGPRs, so four waves fit on each SIMD; K = 128 fits in 96 and runs
+// five (256 windows 3.56 -> 3.39 ms; at K = 64 five were slower for one small
+// frame, 16.2 -> 19.0 us, and K >= 192 does not fit).  POWER: one flat pass
 // per point at the point's own passing power (Eq. 1-2).
 template <int KPH, bool POWER>
-__global__ void __launch_bounds__(512, 4) search_kernel(LaunchArgs args)
+__global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(LaunchArgs args)
 {
     __shared__ StageLDS S;
     __shared__ OutLDS O;
@@ -1051,64 +1055,97 @@ __global__ void __launch_bounds__(512, 4) search_kernel(LaunchArgs args)
     float *const OS = (float *)(PR + nw * 2 * PR_ENTRIES);
     uint8_t *const OM = (uint8_t *)(OS + args.max_variants * TP);
     const bool reduced = (args.P.out_flags & DPPS_OUT_REDUCED) != 0;
-    int iter = 0;
     int cur_frame = -1;
-    // Persistent workgroups take the tiles round-robin (no atomics; tiles of
-    // differing cost spread evenly) for all but the last one or two rounds,
-    // whose tiles they then pull from the work counter as they finish, so
-    // that the last tiles go to the workgroups that are free.
-    const int G = (int)gridDim.x;
+    const int G = (int)gridDim.x, b = (int)blockIdx.x;
     const int n_tiles = args.n_frames_dev ? *args.n_frames_dev * args.tiles_per_frame : args.n_tiles;
-    const int n_static = args.persistent ? max(n_tiles / G - 1, 0) * G : 0;
-    if (threadIdx.x == 0) S.bp = args.P.bp;  // read after the loop's first barrier
-    // a persistent grid's workgroup b sits on XCD b % 8, and so do its static
-    // tiles when the grid is a multiple of 8; its dynamic tiles keep that class
-    // too, from one counter per class, so that the tiles an XCD runs together
-    // write neighbouring chunks (below) and its L2 merges their lines.  C
-    // classes: every class has a workgroup (a grid under 8 workgroups uses G
-    // classes).
-    const int C = min(G, 8), xcd = (int)(blockIdx.x % (unsigned)C);
+    // One workgroup per tile, or a persistent grid: every workgroup takes its
+    // own n_own tiles (first, first + stride, ...) and then pulls from a work
+    // counter as it finishes, so that the last tiles go to the workgroups that
+    // are free.
+    // One frame: round-robin for all but the last one or two rounds.
+    // Workgroup b of the grid sits on XCD b % 8, and so do its own tiles when
+    // the grid is a multiple of 8; its pulled tiles keep that class too, from
+    // one counter per class, so that the tiles an XCD runs together write
+    // neighbouring chunks (below) and its L2 merges their lines.  C classes:
+    // every class has a workgroup (a grid under 8 workgroups uses G classes).
+    // Several frames: a run of consecutive tiles (three quarters of the even
+    // share: frames differ in cost), then groups of `claim` tiles, so that a
+    // workgroup stages few frames; the chunks of a run fill whole lines by
+    // themselves.
+    const int C = min(G, 8), xcd = (int)((unsigned)b % (unsigned)C);
+    const bool runs = args.persistent && args.n_frames > 1;
+    const int even = n_tiles / G;
+    const int n_own = !args.persistent ? 1 : runs ? even - (even + 3) / 4 : max(even - 1, 0);
+    const int first = runs ? b * n_own : b, stride = runs ? 1 : G;
+    const int n_static = n_own * G;
+    const int claim = min(max(even / 16, 1), 8);
     // the lane's best pass of the tile, or of all the workgroup's tiles with
     // one record per workgroup
     unsigned long long bkey = 0ull;
     float btt = INFINITY, bto = INFINITY, bv0 = 0.0f;
+    // the next own tile and its window's record (word i in lane i) are loaded
+    // while the current tile is searched
+    TileDev ta = {0, 0}, tb = {0, 0};
+    int words = 0;
+    if (n_own > 0) {
+        ta = tile_at(args, first);
+        if (n_own > 1) tb = tile_at(args, first + stride);
+        words = window_words(args, ta.win);
+    }
+    if (args.n_frames == 1 && !args.n_frames_dev) {  // known without the tile: one round trip less
+        stage_frame(args.P, args.frames[0], args.robots, args.variants, 0, S);
+        cur_frame = 0;
+    }
+    int it = 0, pull = 0, pull_end = 0;
     while (true) {
         // the previous tile (its staged results and records) is finished
         __syncthreads();
         const LaunchArgs &a = fresh_args<LaunchArgs>();
-        int t = (int)blockIdx.x + iter * G;
-        if (a.persistent && t >= n_static) {
-            if (threadIdx.x == 0)
-                s_tile = n_static + C * (int)atomicAdd(a.counter + xcd, 1u) + xcd;
-            __syncthreads();
-            t = uni(s_tile);
-        }
-        if (t >= n_tiles) break;
-        ++iter;
-        // (the tile and its window are the same for every lane: scalar)
-        TileDev tile;
-        if (a.tiles_per_frame > 0) {
-            tile.win = (int)((unsigned)t / (unsigned)a.tiles_per_frame);
-            tile.at = t - tile.win * a.tiles_per_frame;
+        int t, at, cw;
+        if (it < n_own) {
+            t = first + it * stride;
+            at = ta.at;
+            cw = words;
+            ++it;
+            if (it < n_own) {
+                ta = tb;
+                words = window_words(a, ta.win);
+                if (it + 1 < n_own) tb = tile_at(a, first + (it + 1) * stride);
+            }
         } else {
-            tile = a.tiles[t];
+            if (!a.persistent) break;
+            if (pull < pull_end) {
+                t = pull++;
+            } else {
+                if (threadIdx.x == 0)
+                    s_tile = runs ? n_static + claim * (int)atomicAdd(a.counter, 1u)
+                                  : n_static + C * (int)atomicAdd(a.counter + xcd, 1u) + xcd;
+                __syncthreads();
+                t = uni(s_tile);
+                pull = t + 1;
+                pull_end = runs ? min(t + claim, n_tiles) : 0;
+            }
+            if (t >= n_tiles) break;
+            const TileDev tile = tile_at(a, t);
+            at = tile.at;
+            cw = window_words(a, tile.win);
         }
-        const int tk = uni(tile.at);
-        WinDev W = a.wins[uni(tile.win)];
-        W.h = unif(W.h);
-        W.halfNx = unif(W.halfNx);
-        W.halfNy = unif(W.halfNy);
-        W.i0 = uni(W.i0);
-        W.j0 = uni(W.j0);
-        W.nx = uni(W.nx);
-        W.frame = uni(W.frame);
-        W.npts = uni(W.npts);
-        W.n_tiles = uni(W.n_tiles);
-        W.elem_base = uni(W.elem_base);
-        W.out_base = (int64_t)(((uint64_t)(uint32_t)uni((int)((uint64_t)W.out_base >> 32)) << 32) |
-                               (uint32_t)uni((int)(uint32_t)W.out_base));
+        const int tk = uni(at);
+        WinDev W;  // the same for every lane: scalar
+        W.h = readlane_f(__int_as_float(cw), 0);
+        W.i0 = readlane_i(cw, 1);
+        W.j0 = readlane_i(cw, 2);
+        W.nx = readlane_i(cw, 3);
+        W.n_tiles = readlane_i(cw, 4);
+        W.halfNx = readlane_f(__int_as_float(cw), 5);
+        W.halfNy = readlane_f(__int_as_float(cw), 6);
+        W.frame = readlane_i(cw, 7);
+        W.npts = readlane_i(cw, 8);
+        W.elem_base = readlane_i(cw, 9);
+        W.out_base = (int64_t)(((uint64_t)(uint32_t)readlane_i(cw, 11) << 32) |
+                               (uint32_t)readlane_i(cw, 10));
         if (W.frame != cur_frame) {
-            stage_frame(a.P, S.bp, a.frames, a.robots, a.variants, W.frame, S);
+            stage_frame(a.P, a.frames[W.frame], a.robots, a.variants, W.frame, S);
             __syncthreads();
             cur_frame = W.frame;
         }
@@ -1728,10 +1765,7 @@ __global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs a)
     const int R = max(a.n_tiles / G - 1, 0);
     const int n_static = R * G;
     int iter = 0;
-    if (threadIdx.x == 0) {  // read after the loop's first barrier
-        S.bp = P.bp;
-        s_dir = nw;
-    }
+    if (threadIdx.x == 0) s_dir = nw;  // read after the loop's first barrier
     while (true) {
         __syncthreads();  // the previous tile is finished
         int t = iter < R ? (int)blockIdx.x * R + iter : n_static;
@@ -1745,7 +1779,7 @@ __global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs a)
         const TileDev tile = a.tiles[t];
         const int f = tile.win;
         if (f != cur_frame) {
-            stage_frame(a.P, S.bp, a.frames, a.robots, a.variants, f, S);
+            stage_frame(a.P, a.frames[f], a.robots, a.variants, f, S);
             __syncthreads();
             cur_frame = f;
             const int nv = S.n_var;
@@ -2094,7 +2128,7 @@ __global__ void __launch_bounds__(512) shot_kernel(ShotArgs a)
     const TileDev tile = MAP ? a.tiles[t] : TileDev{0, 0};
     const WinDev W = MAP ? a.wins[tile.win] : WinDev{};
     const int f = MAP ? W.frame : t;
-    stage_frame(P, P.bp, a.frames, a.robots, a.variants, f, S);
+    stage_frame(P, a.frames[f], a.robots, a.variants, f, S);
     __syncthreads();
     const VarConst vc = var_const(P.bp, DPPS_FLAT, a.v_shot);
     if (!MAP) {
@@ -2225,7 +2259,7 @@ __global__ void __launch_bounds__(256) run_kernel(RunArgs a)
     __shared__ unsigned long long red[4];
     const DevParams &P = a.P;
     const WinDev W = a.wins[blockIdx.x];
-    stage_frame(P, P.bp, a.frames, a.robots, a.variants, W.frame, S);
+    stage_frame(P, a.frames[W.frame], a.robots, a.variants, W.frame, S);
     __syncthreads();
     const int n_tm = S.n_tm, n_op = S.n_op;
     unsigned long long best = 0ull;

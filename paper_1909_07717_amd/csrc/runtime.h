@@ -84,6 +84,7 @@ struct dpps_ctx {
     int waves = 4;
     int wg_per_cu = 0;       // 0: as many as fit (occupancy of the search kernel)
     int persistent = 1;
+    bool tile_set = false;   // the tile size was chosen by the caller or the autotuner
     dpps_batch scratch;      // used by dpps_search / dpps_search_batch / host-frame surrogate
     dpps_batch fallback;     // exact searches of surrogate frames without a feasible proposal
     dpps_batch rays;         // tables of dpps_ray_search
