@@ -764,8 +764,8 @@ __device__ __forceinline__ double pass_power(const DevParams &P, double d64, flo
 // return lane v (a staged variant) holds its first team / opponent crossing
 // samples (K: none).
 template <int KPL>
-__device__ __forceinline__ void sbip_crossings(const StageLDS &S, const DevParams &P,
-                                               const float4 *pr, float *pm, float myv0,
+__device__ __forceinline__ void sbip_crossings(const StageLDS &S, const float4 *pr, float *pm,
+                                               float myv0,
                                                int mytype, float d, float LA, int &my_kt,
                                                int &my_ko)
 {
@@ -773,18 +773,19 @@ __device__ __forceinline__ void sbip_crossings(const StageLDS &S, const DevParam
     const int K = KPL * 64;
     const int n_tm = uni(S.n_tm), n_op = uni(S.n_op);
     const float invK = 1.0f / (float)K;
+    int k0 = l * KPL + 1;  // (fractions formed anew for each ray: fewer registers)
+    asm volatile("" : "+v"(k0));
 
     float fs[KPL], sk[KPL], Tt[KPL], To[KPL];
 #pragma unroll
     for (int q = 0; q < KPL; ++q) {
-        fs[q] = (float)(l * KPL + q + 1) * invK;
-        sk[q] = fs[q] * d;
+        fs[q] = (float)(k0 + q) * invK;
         Tt[q] = INFINITY;
         To[q] = INFINITY;
     }
     // 1. robot stage, in the path frame
     const bool split = n_tm + n_op <= SPLIT_ROB;
-    const RobotK rk(P);
+    const RobotK rk(fresh_args<RayArgs>().P);
     if (uni(S.vel_ok)) {
         robot_stage<KPL, false, FULL_WAVE>(pr, rk, 0, n_tm, split, INFINITY, INFINITY, fs, LA, Tt);
         robot_stage<KPL, false, FULL_WAVE>(pr, rk, n_tm, n_op, split, INFINITY, INFINITY, fs, LA, To);
@@ -794,16 +795,19 @@ __device__ __forceinline__ void sbip_crossings(const StageLDS &S, const DevParam
     }
     // 2-3. critical kick speeds per sample, then the first crossing of each
     // lane's variant (a side with no robot never intercepts: critical speed 0)
+    const float invA2 = fresh_args<RayArgs>().P.invA2;
 #pragma unroll
     for (int q = 0; q < KPL; ++q) {
-        Tt[q] *= P.invA2;  // seconds
-        To[q] *= P.invA2;
+        sk[q] = fs[q] * d;
+        Tt[q] *= invA2;  // seconds
+        To[q] *= invA2;
     }
     const unsigned long long flat_m = __ballot(mytype == DPPS_FLAT);
     const unsigned long long chip_m = __ballot(mytype == DPPS_CHIP);
     float *const pf = pm, *const pc = pm + 2 * K;  // flat rows, chip rows
     wave_lds_sync();  // the previous path's searches are done with the rows
     if (flat_m) {
+        const DevParams &P = fresh_args<RayArgs>().P;
         float vt[KPL], vo[KPL];
         const SampleTerms<KPL, false, false> st(P, sk);
         side_vcrit<KPL, false, false>(P, n_tm, Tt, sk, st, sk, vt);
@@ -812,6 +816,7 @@ __device__ __forceinline__ void sbip_crossings(const StageLDS &S, const DevParam
         store_running_max<KPL, false>(vo, pf + K);
     }
     if (chip_m) {
+        const DevParams &P = fresh_args<RayArgs>().P;
         float vt[KPL], vo[KPL], vair[KPL];
 #pragma unroll
         for (int q = 0; q < KPL; ++q) vair[q] = hsqrt(sk[q] * P.lam1_inv);
@@ -1676,21 +1681,27 @@ int launch_ray_dirs(double2 *dirs, int n, void *stream)
 }
 
 template <int KPL>
-__device__ RayOut ray_direction(const StageLDS &S, const DevParams &P, float4 *pr, float *pm,
-                                float myv0, int mytype, int myvid, int d, const double2 *dirs,
-                                float w_time, float w_refract)
+__device__ RayOut ray_direction(const StageLDS &S, float4 *pr, float *pm, float myv0, int mytype,
+                                int myvid, int d)
 {
     const int l = lane_id();
     const int K = KPL * 64;
     const int n_tm = uni(S.n_tm), n_op = uni(S.n_op), n_var = uni(S.n_var);
     const double bx = (double)unif(S.bx), by = (double)unif(S.by);
-    const double2 u = dirs[d];
-    const double ux = u.x, uy = u.y;
-    const double L = ray_length(P, bx, by, ux, uy);
-    path_frame_dir<FULL_WAVE>(S, P, pr, n_tm + n_op, n_tm, L * (double)P.A, ux, uy, bx, by, l);
+    double ux, uy, L, LA;
+    {
+        const RayArgs &a = fresh_args<RayArgs>();
+        const double2 u = a.dirs[d];
+        ux = u.x;
+        uy = u.y;
+        L = ray_length(a.P, bx, by, ux, uy);
+        LA = L * (double)a.P.A;
+        path_frame_dir<FULL_WAVE>(S, a.P, pr, n_tm + n_op, n_tm, LA, ux, uy, bx, by, l);
+    }
     int my_kt, my_ko;
-    sbip_crossings<KPL>(S, P, pr, pm, myv0, mytype, (float)L, (float)(L * (double)P.A), my_kt,
-                        my_ko);
+    sbip_crossings<KPL>(S, pr, pm, myv0, mytype, (float)L, (float)LA, my_kt, my_ko);
+    const RayArgs &a = fresh_args<RayArgs>();
+    const DevParams &P = a.P;
 
     RayOut o;
     o.key = 0ull;
@@ -1732,7 +1743,7 @@ __device__ RayOut ray_direction(const StageLDS &S, const DevParams &P, float4 *p
         const float sc = fmaf(P.w_ang_pi, my_ang,
                               fmaf(P.w_dist, fmaf(-dg, P.inv_dist_norm, 1.0f),
                                    fmaf(P.w_margin, mc,
-                                        fmaf(-w_time, o.t_team, -w_refract * refr * 0.318309886183790672f))));
+                                        fmaf(-a.w_time, o.t_team, -a.w_refract * refr * 0.318309886183790672f))));
         o.score = sc;
         o.open_angle = my_ang;
         o.refract = refr;
@@ -1743,7 +1754,7 @@ __device__ RayOut ray_direction(const StageLDS &S, const DevParams &P, float4 *p
 }
 
 template <int KPL>
-__global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs a)
+__global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs args)
 {
     __shared__ StageLDS S;
     __shared__ float4 PR[MAX_WAVES][PR_ENTRIES];
@@ -1751,7 +1762,6 @@ __global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs a)
     __shared__ RayRec WB[MAX_WAVES];
     __shared__ int s_tile;
     __shared__ int s_dir;  // next unclaimed direction slot of the tile
-    const DevParams &P = a.P;
     const int nw = blockDim.x >> 6;
     const int w = threadIdx.x >> 6;
     const int l = lane_id();
@@ -1762,22 +1772,23 @@ __global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs a)
     // frame, so it is staged once per run) for all but the last one or two
     // rounds' worth, then the work counter
     const int G = (int)gridDim.x;
-    const int R = max(a.n_tiles / G - 1, 0);
+    const int R = max(args.n_tiles / G - 1, 0);
     const int n_static = R * G;
     int iter = 0;
     if (threadIdx.x == 0) s_dir = nw;  // read after the loop's first barrier
     while (true) {
         __syncthreads();  // the previous tile is finished
+        const RayArgs &a = fresh_args<RayArgs>();
         int t = iter < R ? (int)blockIdx.x * R + iter : n_static;
         if (t >= n_static) {
             if (threadIdx.x == 0) s_tile = n_static + (int)atomicAdd(a.counter, 1u);
             __syncthreads();
-            t = s_tile;
+            t = uni(s_tile);
         }
         if (t >= a.n_tiles) break;
         ++iter;
         const TileDev tile = a.tiles[t];
-        const int f = tile.win;
+        const int f = uni(tile.win), d0 = uni(tile.at);
         if (f != cur_frame) {
             stage_frame(a.P, a.frames[f], a.robots, a.variants, f, S);
             __syncthreads();
@@ -1787,9 +1798,9 @@ __global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs a)
             mytype = l < nv ? S.type[l] : -1;
             myvid = l < nv ? S.vidx[l] : 0;
         }
-        const int n_var = S.n_var;
+        const int n_var = uni(S.n_var);
         const int64_t base = a.frames[f].ray_base;
-        const int nd = min(a.tile_dirs, a.n_dirs - tile.at);
+        const int nd = min(a.tile_dirs, a.n_dirs - d0);
         // the wave's best so far: its key in a uniform register, its record
         // in the wave's LDS slot (written by the lane that holds it)
         unsigned long long wbk = 0ull;
@@ -1801,10 +1812,10 @@ __global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs a)
         // each wave takes slot w, then claims the tile's next free slot as it
         // finishes one (directions differ in cost: the waves end together)
         for (int slot = w; slot < nd;) {
-            const int d = tile.at + slot;
-            const RayOut o = ray_direction<KPL>(S, P, PR[w], PMX + w * PM_ROWS * KPL * 64, myv0,
-                                                mytype, myvid, d, a.dirs, a.w_time,
-                                                a.w_refract);
+            const int d = d0 + slot;
+            const RayOut o = ray_direction<KPL>(S, PR[w], PMX + w * PM_ROWS * KPL * 64, myv0,
+                                                mytype, myvid, d);
+            const RayArgs &a = fresh_args<RayArgs>();
             if (l < n_var) {
                 const int64_t e = base + (int64_t)d * n_var + myvid;
                 if (a.mask) a.mask[e] = (uint8_t)o.feas;
