@@ -43,7 +43,7 @@ struct dpps_mlp {
     void *arena = nullptr;
     size_t arena_bytes = 0;
     float *w[NL], *b[NL], *gw[NL], *gb[NL], *mw[NL], *vw[NL], *mb[NL], *vb[NL];
-    uint16_t *wb[NL], *wbt[NL];
+    uint16_t *wb[NL];
     uint16_t *x0;
     float *z[3];
     uint16_t *a[3];
@@ -90,7 +90,7 @@ static int refresh_bf16(dpps_mlp *m, hipStream_t st)
 {
     for (int l = 0; l < NL; ++l) {
         int64_t n = (int64_t)OUT_DIM[l] * IN_DIM[l];
-        if (launch_cast(m->w[l], n, m->wb[l], m->wbt[l], OUT_DIM[l], IN_DIM[l], (void *)st))
+        if (launch_cast(m->w[l], n, m->wb[l], (void *)st))
             return fail(DPPS_E_DEVICE, "cast kernel launch failed");
     }
     return DPPS_OK;
@@ -123,7 +123,9 @@ static int params_xfer(dpps_mlp *m, float *const *dw, float *const *db, float *h
 // every padded row and uses the tiled GEMM.
 constexpr int SMALL_ROWS = 64;
 
-static int forward(dpps_mlp *m, const dpps_batch *bt, hipStream_t st, bool training)
+// out (may be NULL): the caller's copy of the predicted maps, ld_out floats a row.
+static int forward(dpps_mlp *m, const dpps_batch *bt, hipStream_t st, bool training,
+                   float *out = nullptr, int64_t ld_out = 0)
 {
     const int nf = bt->n_frames, R = rows_pad(nf);
     const bool small = !training && nf >= 1 && nf <= SMALL_ROWS;
@@ -148,12 +150,16 @@ static int forward(dpps_mlp *m, const dpps_batch *bt, hipStream_t st, bool train
         g.bias = m->b[l];
         int epi;
         if (l < NL - 1) {
-            g.Cf = m->z[l];
+            g.Cf = training ? m->z[l] : nullptr;  // pre-activations: backward only
             g.Cb = m->a[l];
             epi = EPI_BIAS_GELU;
             in = m->a[l];
         } else {
             g.Cf = m->y;
+            g.out = out;
+            g.ld_out = ld_out;
+            g.out_m = nf;
+            g.out_n = OUT;
             epi = EPI_BIAS;
         }
         if (small ? gemm_rows(g, epi, (void *)st) : gemm(g, true, true, epi, (void *)st))
@@ -175,6 +181,8 @@ static int backward_loss(dpps_mlp *m, int nf, const float *tgt, int64_t ld_t, Lo
                     lc.tau, m->dz4, m->partial, (void *)st))
         return fail(DPPS_E_DEVICE, "loss launch failed");
     const uint16_t *dz_top = m->dz4;
+    ColsumJobs cs;
+    float *part = m->colpart;
     for (int l = NL - 1; l >= 0; --l) {
         const uint16_t *act = l == 0 ? m->x0 : m->a[l - 1];
         // dW_l = dZ_l^T act  ([out][in], reduction over rows)
@@ -192,25 +200,29 @@ static int backward_loss(dpps_mlp *m, int nf, const float *tgt, int64_t ld_t, Lo
         g.work = m->gwork;  // the reduction over the batch may be split
         g.work_elems = GWORK_ELEMS;
         if (gemm(g, false, false, EPI_NONE, (void *)st)) return fail(DPPS_E_DEVICE, "gemm failed");
-        if (launch_colsum(dz_top, R, OUT_DIM[l], OUT_DIM[l], m->gb[l], m->colpart, (void *)st))
-            return fail(DPPS_E_DEVICE, "colsum failed");
+        cs.dz[l] = dz_top;
+        cs.db[l] = m->gb[l];
+        cs.n[l] = OUT_DIM[l];
+        cs.part[l] = part;
+        part += (size_t)colsum_chunks(R) * OUT_DIM[l];
         if (l == 0) break;
         // dZ_{l-1} = (dZ_l W_l) * gelu'(Z_{l-1})
         GemmArgs h;
         memset(&h, 0, sizeof h);
         h.A = dz_top;
         h.lda = OUT_DIM[l];
-        h.B = m->wbt[l];
-        h.ldb = OUT_DIM[l];
+        h.B = m->wb[l];
+        h.ldb = IN_DIM[l];
         h.M = R;
         h.N = IN_DIM[l];
         h.K = OUT_DIM[l];
         h.ldc = IN_DIM[l];
         h.Zin = m->z[l - 1];
         h.Cb = m->dz[l - 1];
-        if (gemm(h, true, true, EPI_GELU_GRAD, (void *)st)) return fail(DPPS_E_DEVICE, "gemm failed");
+        if (gemm(h, true, false, EPI_GELU_GRAD, (void *)st)) return fail(DPPS_E_DEVICE, "gemm failed");
         dz_top = m->dz[l - 1];
     }
+    if (launch_colsum(cs, R, (void *)st)) return fail(DPPS_E_DEVICE, "colsum failed");
     return DPPS_OK;
 }
 
@@ -255,14 +267,14 @@ int dpps_mlp_create(dpps_ctx *c, int32_t max_frames, int32_t max_k, uint64_t see
     m->fine_nx = fnx;
     m->fine_ny = fny;
     const size_t R = (size_t)m->rows_cap;
-    size_t off = 0, ow[NL], ob[NL], ogw[NL], ogb[NL], omw[NL], ovw[NL], omb[NL], ovb[NL], owb[NL], owbt[NL];
+    size_t off = 0, ow[NL], ob[NL], ogw[NL], ogb[NL], omw[NL], ovw[NL], omb[NL], ovb[NL], owb[NL];
     for (int l = 0; l < NL; ++l) {
         size_t nw = (size_t)OUT_DIM[l] * IN_DIM[l], nb = OUT_DIM[l];
         ow[l] = carve(off, nw * 4); ob[l] = carve(off, nb * 4);
         ogw[l] = carve(off, nw * 4); ogb[l] = carve(off, nb * 4);
         omw[l] = carve(off, nw * 4); ovw[l] = carve(off, nw * 4);
         omb[l] = carve(off, nb * 4); ovb[l] = carve(off, nb * 4);
-        owb[l] = carve(off, nw * 2); owbt[l] = carve(off, nw * 2);
+        owb[l] = carve(off, nw * 2);
     }
     size_t ox0 = carve(off, R * IN_PAD * 2), oz[3], oa[3], odz[3];
     for (int l = 0; l < 3; ++l) {
@@ -272,7 +284,7 @@ int dpps_mlp_create(dpps_ctx *c, int32_t max_frames, int32_t max_k, uint64_t see
     }
     size_t oy = carve(off, R * OUT_PAD * 4), odz4 = carve(off, R * OUT_PAD * 2);
     size_t opart = carve(off, R * 8);
-    size_t ocol = carve(off, (size_t)colsum_chunks((int)R) * OUT_PAD * 4);
+    size_t ocol = carve(off, (size_t)colsum_chunks((int)R) * (OUT_PAD + 3 * HID) * 4);
     size_t ogwork = carve(off, (size_t)GWORK_ELEMS * 4);
     size_t ocells = carve(off, R * max_k * 4);
     size_t orf = carve(off, R * sizeof(FrameDev));
@@ -304,7 +316,7 @@ int dpps_mlp_create(dpps_ctx *c, int32_t max_frames, int32_t max_k, uint64_t see
         m->gw[l] = (float *)(A + ogw[l]); m->gb[l] = (float *)(A + ogb[l]);
         m->mw[l] = (float *)(A + omw[l]); m->vw[l] = (float *)(A + ovw[l]);
         m->mb[l] = (float *)(A + omb[l]); m->vb[l] = (float *)(A + ovb[l]);
-        m->wb[l] = (uint16_t *)(A + owb[l]); m->wbt[l] = (uint16_t *)(A + owbt[l]);
+        m->wb[l] = (uint16_t *)(A + owb[l]);
     }
     m->x0 = (uint16_t *)(A + ox0);
     for (int l = 0; l < 3; ++l) {
@@ -430,12 +442,7 @@ int dpps_mlp_forward(dpps_mlp *m, dpps_batch *b, float *d_out, int64_t ld_out, v
     if (d_out && ld_out < OUT) return fail(DPPS_E_INVALID, "ld_out must be >= %d", OUT);
     HIP_OK(hipSetDevice(m->ctx->device));
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : m->ctx->stream;
-    int rc = forward(m, b, st, false);
-    if (rc) return rc;
-    if (d_out && b->n_frames > 0)
-        HIP_OK(hipMemcpy2DAsync(d_out, (size_t)ld_out * 4, m->y, (size_t)OUT_PAD * 4, (size_t)OUT * 4,
-                                b->n_frames, hipMemcpyDeviceToDevice, st));
-    return DPPS_OK;
+    return forward(m, b, st, false, d_out, ld_out);
 }
 
 int dpps_mlp_loss_grad(dpps_mlp *m, dpps_batch *b, const float *d_target, int64_t ld_target,
@@ -467,14 +474,14 @@ int dpps_mlp_adam(dpps_mlp *m, float lr, float beta1, float beta2, float eps, fl
     m->step += 1;
     float c1 = (float)(1.0 - pow((double)beta1, (double)m->step));
     float c2 = (float)(1.0 - pow((double)beta2, (double)m->step));
+    AdamJobs jobs;
     for (int l = 0; l < NL; ++l) {
-        int64_t nw = (int64_t)OUT_DIM[l] * IN_DIM[l];
-        if (launch_adam(m->w[l], m->gw[l], m->mw[l], m->vw[l], nw, lr, beta1, beta2, eps, c1, c2,
-                        weight_decay, m->wb[l], m->wbt[l], OUT_DIM[l], IN_DIM[l], (void *)st) ||
-            launch_adam(m->b[l], m->gb[l], m->mb[l], m->vb[l], OUT_DIM[l], lr, beta1, beta2, eps, c1,
-                        c2, 0.0f, nullptr, nullptr, 1, OUT_DIM[l], (void *)st))
-            return fail(DPPS_E_DEVICE, "adam launch failed");
+        jobs.job[2 * l] = {m->w[l], m->gw[l], m->mw[l], m->vw[l], m->wb[l],
+                           (int64_t)OUT_DIM[l] * IN_DIM[l], weight_decay};
+        jobs.job[2 * l + 1] = {m->b[l], m->gb[l], m->mb[l], m->vb[l], nullptr, OUT_DIM[l], 0.0f};
     }
+    if (launch_adam(jobs, lr, beta1, beta2, eps, c1, c2, (void *)st))
+        return fail(DPPS_E_DEVICE, "adam launch failed");
     return DPPS_OK;
 }
 

@@ -19,29 +19,52 @@ struct GemmArgs {
     int M, N, K;
     const float *bias;   // EPI_BIAS, EPI_BIAS_GELU
     const float *Zin;    // EPI_GELU_GRAD: pre-activation, [M][ldc]
-    float *Cf;           // f32 output
+    float *Cf;           // f32 output (EPI_BIAS_GELU: may be NULL)
     uint16_t *Cb;        // bf16 output
     float *work;         // optional workspace for a K split (EPI_NONE only), work_elems floats
     int64_t work_elems;
     int k_slice;         // set by the dispatcher
+    float *out;          // EPI_BIAS: a second copy of rows < out_m, columns < out_n (may be NULL)
+    int64_t ld_out;
+    int out_m, out_n;
 };
 
 int gemm(const GemmArgs &g, bool a_k, bool b_k, int epi, void *stream);
 // Inference GEMM of a few rows (A, B k-contiguous; EPI_BIAS or EPI_BIAS_GELU),
 // bit-identical per element to gemm(g, true, true, epi, stream).
 int gemm_rows(const GemmArgs &g, int epi, void *stream);
-// Column sums (bias gradients); part holds colsum_chunks(M) x N floats.
-int launch_colsum(const uint16_t *dz, int M, int N, int ld, float *db, float *part, void *st);
+// Column sums of the layers' output gradients dz [M][n] (n a multiple of 64):
+// db; part holds colsum_chunks(M) x n floats.
+struct ColsumJobs {
+    const uint16_t *dz[4];
+    float *db[4];
+    float *part[4];
+    int n[4];
+};
+int launch_colsum(const ColsumJobs &jobs, int M, void *st);
 int colsum_chunks(int M);
 int launch_loss(const float *y, int ldy, const float *tgt, int ldt, int rows, int outs, int rows_pad,
                 int outs_pad, float pos_weight, float ce_weight, float tau, uint16_t *dz,
                 float *partial, void *st);
 int launch_pool(const float *fine, int n_frames, int fnx, int fny, float *coarse, int cnx, int cny,
                 void *st);
-int launch_adam(float *w, const float *g, float *m, float *v, int64_t n, float lr, float b1, float b2,
-                float eps, float c1, float c2, float wd, uint16_t *wb, uint16_t *wbt, int rows,
-                int cols, void *st);
-int launch_cast(const float *w, int64_t n, uint16_t *wb, uint16_t *wbt, int rows, int cols, void *st);
+// One Adam step on a list of tensors (n multiples of 4, 16-byte aligned); wb
+// (may be NULL) is refreshed from w.
+#define ADAM_JOBS 8
+struct AdamJob {
+    float *w;
+    const float *g;
+    float *m, *v;
+    uint16_t *wb;
+    int64_t n;
+    float wd;
+};
+struct AdamJobs {
+    AdamJob job[ADAM_JOBS];
+    int blocks[ADAM_JOBS];  // set by the launcher
+};
+int launch_adam(AdamJobs jobs, float lr, float b1, float b2, float eps, float c1, float c2, void *st);
+int launch_cast(const float *w, int64_t n, uint16_t *wb, void *st);
 int launch_featurize(const FrameDev *frames, const dpps_robot *robots, int n_frames, int rows_pad,
                      int in_pad, float inv_hl, float inv_hw, float inv_v, uint16_t *x, void *st);
 // Re-score tables written by the top-k kernel: per frame f, its copy

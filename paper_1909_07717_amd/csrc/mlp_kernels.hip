@@ -44,55 +44,111 @@ __device__ __forceinline__ float gelu_grad(float x)
 // GEMM: C[M][N] = sum_k A(m, k) B(k, n), bf16 operands, f32 accumulation.
 // A(m, k) = A[m*lda + k] when A_K (k contiguous), else A[k*lda + m].
 // B(k, n) = B[n*ldb + k] when B_K (k contiguous), else B[k*ldb + n].
-// M, N, K are multiples of 8 (vectors of 8 never straddle an edge).
-// Block tile BM x BN (128 x 128 or 64 x 64), K step 32, 256 threads: four
+// M, N are multiples of 8, K and every K slice multiples of 32.
+// Block tile BM x BN (128 x 128 or 64 x 64), K step 64, 256 threads: four
 // waves in a 2 x 2 arrangement, each owning a (BM/2) x (BN/2) quarter as
-// (BM/32) x (BN/32) MFMA tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16).  The
-// next K step is fetched into registers while the current one multiplies
-// out of LDS, into the other of two LDS buffers, one barrier per step.
+// (BM/32) x (BN/32) MFMA tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16, k
+// ascending from 0, so an output element has the same bits whatever the tile).
+// The layers are narrow (K = 512 mostly, a few hundred tiles): what bounds
+// them is the latency of a K step, not MFMA issue, so a step is 64 deep, goes
+// from memory straight into LDS (no registers, no LDS write pass), and the
+// next one is in flight while the current one multiplies.  An operand
+// that is not k-contiguous (the weight gradients) stays as it lies in memory
+// and is transposed by the LDS reads (ds_read_b64_tr_b16).  16-byte chunks
+// are permuted within LDS so that a read's lanes spread over the banks.
 // blockIdx.z splits K into slices of g.k_slice; with EPI_PARTIAL slice z
 // writes its partial product to Cf + z * M * ldc (summed by gemm_reduce).
 // ---------------------------------------------------------------------------
-#define GK 32
-#define LDSK (GK + 8)   // padded row (bf16 elements) to spread LDS banks
+#define GK 64
 
-template <int BM, bool A_K>
-__device__ __forceinline__ void fetch_tile(const uint16_t *__restrict__ A, int lda, int M, int K,
-                                           int m0, int k0, uint4 (&r)[BM / 64])
+// Chunk permutation of row r of an operand tile (BX rows or columns).
+// k-contiguous rows are 128 bytes: 8 lanes read the same chunk of 8 rows.
+__device__ __forceinline__ int swz_k(int r) { return r & 7; }
+// Otherwise row = k: a transposing read takes 32 bytes of rows r0 .. r0 + 3,
+// r0 = 8 g for the wave's four groups of 16 lanes.
+template <int BX>
+__device__ __forceinline__ int swz_x(int r)
 {
+    return BX == 128 ? (((r & 3) | (((r >> 3) & 1) << 2)) << 1)
+                     : ((((r >> 1) & 1) | (((r >> 3) & 1) << 1)) << 1);
+}
+
+// One K step of an operand into its LDS tile: each wave instruction moves 64
+// chunks of 16 bytes to consecutive LDS addresses; the lane chooses which
+// chunk of the matrix lands on its place.  Rows, columns and k past the edge
+// are clamped to valid ones (their products are not used).
+template <int BX, bool X_K>
+__device__ __forceinline__ void load_tile(const uint16_t *__restrict__ src, int ld, int X, int K,
+                                          int x0, int k0, uint16_t *tile)
+{
+    constexpr int CR = X_K ? GK / 8 : BX / 8;  // chunks per LDS row
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
-    for (int i = 0; i < BM / 64; ++i) {
-        const int idx = threadIdx.x + i * 256;
-        int m, kk;
-        if (A_K) {
-            m = idx >> 2;
-            kk = (idx & 3) * 8;
+    for (int i = 0; i < BX * GK * 2 / 4096; ++i) {
+        const int n = i * 4 + w;
+        const int row = n * (64 / CR) + l / CR, phys = l % CR;
+        const uint16_t *p;
+        if (X_K) {
+            const int k = min(k0 + (phys ^ swz_k(row)) * 8, K - 8);
+            p = src + (size_t)min(x0 + row, X - 1) * ld + k;
         } else {
-            kk = idx / (BM / 8);
-            m = (idx % (BM / 8)) * 8;
+            const int x = min(x0 + (phys ^ swz_x<BX>(row)) * 8, X - 8);
+            p = src + (size_t)min(k0 + row, K - 1) * ld + x;
         }
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (m0 + m < M && k0 + kk < K)
-            v = A_K ? *(const uint4 *)(A + (size_t)(m0 + m) * lda + k0 + kk)
-                    : *(const uint4 *)(A + (size_t)(k0 + kk) * lda + m0 + m);
-        r[i] = v;
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void *)p,
+            (__attribute__((address_space(3))) void *)(tile + n * 512), 16, 0, 0);
     }
 }
 
-// Tiles are kept in LDS as [row][k] (rows = m for A, n for B).
-template <int BM, bool A_K>
-__device__ __forceinline__ void store_tile(const uint4 (&r)[BM / 64], uint16_t *As)
+// MFMA operand of 16 rows (columns) from x and the 32 k of half kk of the step:
+// lane l holds row x + l % 16, k = 32 kk + 8 (l / 16) .. + 7.
+template <int BX, bool X_K>
+__device__ __forceinline__ bf16x8_t load_frag(const uint16_t *tile, int x, int kk)
 {
+    const int l = threadIdx.x & 63;
+    if (X_K) {
+        const int row = x + (l & 15);
+        const int phys = (kk * 4 + (l >> 4)) ^ swz_k(row);
+        return *(const bf16x8_t *)(tile + row * GK + phys * 8);
+    }
+    const int row = kk * 32 + (l >> 4) * 8 + ((l & 15) >> 2);
+    const int col = x + (l & 3) * 4;
+    const uint16_t *p = tile + row * BX + (((col >> 3) ^ swz_x<BX>(row)) * 8 + (col & 4));
+    typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+    typedef __attribute__((address_space(3))) s16x4_t *lds_t;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)p);
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_t)(p + 4 * BX));
+    typedef __attribute__((ext_vector_type(8))) short s16x8_t;
+    return __builtin_bit_cast(bf16x8_t, (s16x8_t)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Four consecutive outputs from column n of row m (m < M, n + 3 < N).
+template <int EPI>
+__device__ __forceinline__ void gemm_store(const GemmArgs &g, float *part, int m, int n, f32x4_t v)
+{
+    const size_t o = (size_t)m * g.ldc + n;
+    if (EPI == EPI_BIAS_GELU || EPI == EPI_BIAS) v = v + *(const f32x4_t *)(g.bias + n);
+    if (EPI == EPI_BIAS_GELU || EPI == EPI_GELU_GRAD) {
+        float z[4] = {v[0], v[1], v[2], v[3]};
+        f32x4_t zin = v;
+        if (EPI == EPI_GELU_GRAD) zin = *(const f32x4_t *)(g.Zin + o);
+        uint16_t h[4];
 #pragma unroll
-    for (int i = 0; i < BM / 64; ++i) {
-        const int idx = threadIdx.x + i * 256;
-        if (A_K) {
-            *(uint4 *)(As + (idx >> 2) * LDSK + (idx & 3) * 8) = r[i];
+        for (int i = 0; i < 4; ++i)
+            h[i] = EPI == EPI_BIAS_GELU ? f2bf(gelu(z[i])) : f2bf(z[i] * gelu_grad(zin[i]));
+        if (EPI == EPI_BIAS_GELU && g.Cf) *(f32x4_t *)(g.Cf + o) = v;  // pre-activation
+        *(uint2 *)(g.Cb + o) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16),
+                                          (uint32_t)h[2] | ((uint32_t)h[3] << 16));
+        return;
+    }
+    *(f32x4_t *)((EPI == EPI_PARTIAL ? part : g.Cf) + o) = v;
+    if (EPI == EPI_BIAS && g.out && m < g.out_m) {  // the caller's copy, real columns only
+        float *p = g.out + (size_t)m * g.ld_out + n;
+        if (n + 4 <= g.out_n) {
+            __builtin_memcpy(p, &v, sizeof v);
         } else {
-            const int kk = idx / (BM / 8), m = (idx % (BM / 8)) * 8;
-            const uint16_t *e = (const uint16_t *)&r[i];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) As[(m + j) * LDSK + kk] = e[j];
+            for (int i = 0; i < g.out_n - n; ++i) p[i] = v[i];
         }
     }
 }
@@ -101,8 +157,8 @@ template <int BM, int BN, bool A_K, bool B_K, int EPI>
 __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g)
 {
     constexpr int TM = BM / 32, TN = BN / 32;
-    __shared__ __attribute__((aligned(16))) uint16_t As[2][BM * LDSK];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][BN * LDSK];
+    __shared__ __attribute__((aligned(16))) uint16_t As[2][BM * GK];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][BN * GK];
     const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
     const int kb = blockIdx.z * g.k_slice;
     const int ke = min(kb + g.k_slice, g.K);
@@ -113,81 +169,70 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g)
     for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b) acc[a][b] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-    const int fr = l & 15, fk = (l >> 4) * 8;  // fragment row/col and k offset
-    uint4 ra[BM / 64], rb[BN / 64];
-    fetch_tile<BM, A_K>(g.A, g.lda, g.M, g.K, m0, kb, ra);
-    fetch_tile<BN, B_K>(g.B, g.ldb, g.N, g.K, n0, kb, rb);
-    store_tile<BM, A_K>(ra, As[0]);
-    store_tile<BN, B_K>(rb, Bs[0]);
-    __syncthreads();
+    load_tile<BM, A_K>(g.A, g.lda, g.M, g.K, m0, kb, As[0]);
+    load_tile<BN, B_K>(g.B, g.ldb, g.N, g.K, n0, kb, Bs[0]);
     int cur = 0;
-    for (int k0 = kb; k0 < ke; k0 += GK) {
-        const bool more = k0 + GK < ke;
-        if (more) {
-            fetch_tile<BM, A_K>(g.A, g.lda, g.M, g.K, m0, k0 + GK, ra);
-            fetch_tile<BN, B_K>(g.B, g.ldb, g.N, g.K, n0, k0 + GK, rb);
-        }
-        bf16x8_t af[TM], bfr[TN];
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-            af[a] = *(const bf16x8_t *)(As[cur] + (wm + a * 16 + fr) * LDSK + fk);
-#pragma unroll
-        for (int b = 0; b < TN; ++b)
-            bfr[b] = *(const bf16x8_t *)(Bs[cur] + (wn + b * 16 + fr) * LDSK + fk);
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-            for (int b = 0; b < TN; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
-        if (more) {
-            // the other buffer was last read before the previous barrier
-            store_tile<BM, A_K>(ra, As[cur ^ 1]);
-            store_tile<BN, B_K>(rb, Bs[cur ^ 1]);
-        }
+    for (int k0 = kb; k0 < ke; k0 += GK, cur ^= 1) {
+        // this wave's part of the step has landed; after the barrier all of
+        // it has, and every wave is done with the other buffer
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        cur ^= 1;
+        bf16x8_t af[2][TM], bfr[2][TN];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a) af[kk][a] = load_frag<BM, A_K>(As[cur], wm + a * 16, kk);
+#pragma unroll
+            for (int b = 0; b < TN; ++b) bfr[kk][b] = load_frag<BN, B_K>(Bs[cur], wn + b * 16, kk);
+        }
+        if (k0 + GK < ke) {
+            load_tile<BM, A_K>(g.A, g.lda, g.M, g.K, m0, k0 + GK, As[cur ^ 1]);
+            load_tile<BN, B_K>(g.B, g.ldb, g.N, g.K, n0, k0 + GK, Bs[cur ^ 1]);
+        }
+        // operands swapped: the lane then holds four consecutive columns n of
+        // one row m
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            if (kk == 1 && k0 + 32 >= ke) break;  // a last half step
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[kk][b], af[kk][a],
+                                                                        acc[a][b], 0, 0, 0);
+        }
     }
-    // epilogue: lane holds D[(l/16)*4 + i][l%16] of each 16 x 16 tile
     float *part = g.Cf + (size_t)blockIdx.z * g.M * g.ldc;
 #pragma unroll
     for (int a = 0; a < TM; ++a) {
+        const int m = m0 + wm + a * 16 + (l & 15);
+        if (m >= g.M) continue;
 #pragma unroll
         for (int b = 0; b < TN; ++b) {
-            const int n = n0 + wn + b * 16 + (l & 15);
-            if (n >= g.N) continue;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = m0 + wm + a * 16 + (l >> 4) * 4 + i;
-                if (m >= g.M) continue;
-                float v = acc[a][b][i];
-                const size_t o = (size_t)m * g.ldc + n;
-                if (EPI == EPI_BIAS_GELU) {
-                    v += g.bias[n];
-                    g.Cf[o] = v;                    // pre-activation (f32)
-                    g.Cb[o] = f2bf(gelu(v));        // activation (bf16)
-                } else if (EPI == EPI_BIAS) {
-                    g.Cf[o] = v + g.bias[n];
-                } else if (EPI == EPI_GELU_GRAD) {
-                    // v = dA; dZ = dA * gelu'(Z)
-                    g.Cb[o] = f2bf(v * gelu_grad(g.Zin[o]));
-                } else if (EPI == EPI_PARTIAL) {
-                    part[o] = v;
-                } else {
-                    g.Cf[o] = v;
-                }
-            }
+            const int n = n0 + wn + b * 16 + (l >> 4) * 4;
+            if (n < g.N) gemm_store<EPI>(g, part, m, n, acc[a][b]);
         }
     }
 }
 
-// out[m][n] = sum over z of part[z][m][n], in order of z.
-__global__ void gemm_reduce_kernel(const float *__restrict__ part, int splits, int64_t n_el,
-                                   float *__restrict__ out)
+// out[e] = sum over z of part[z][e], in order of z; four elements per thread,
+// the slices' loads in flight together.
+__global__ void __launch_bounds__(256) gemm_reduce_kernel(const f32x4_t *__restrict__ part,
+                                                          int splits, int64_t n4,
+                                                          f32x4_t *__restrict__ out)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_el) return;
-    float s = 0.0f;
-    for (int z = 0; z < splits; ++z) s += part[(size_t)z * n_el + e];
+    if (e >= n4) return;
+    f32x4_t s = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int z0 = 0; z0 < splits; z0 += 8) {
+        f32x4_t v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (z0 + q < splits) v[q] = part[(size_t)(z0 + q) * n4 + e];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (z0 + q < splits) s = s + v[q];
+    }
     out[e] = s;
 }
 
@@ -212,14 +257,14 @@ static void launch_shape(GemmArgs g, hipStream_t st)
         const int64_t mn = (int64_t)g.M * g.ldc;
         while (splits > 1 && (int64_t)splits * mn > g.work_elems) --splits;
         if (splits > 1) {
-            const int slice = ((g.K + splits - 1) / splits + GK - 1) / GK * GK;
+            const int slice = ((g.K + splits - 1) / splits + 31) / 32 * 32;
             splits = (g.K + slice - 1) / slice;
             GemmArgs h = g;
             h.k_slice = slice;
             h.Cf = g.work;
             launch_gemm<64, 64, A_K, B_K, EPI_PARTIAL>(h, splits, st);
-            hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)((mn + 255) / 256)), dim3(256), 0,
-                               st, (const float *)g.work, splits, mn, g.Cf);
+            hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)((mn / 4 + 255) / 256)), dim3(256),
+                               0, st, (const f32x4_t *)g.work, splits, mn / 4, (f32x4_t *)g.Cf);
             return;
         }
     }
@@ -250,7 +295,7 @@ __global__ void __launch_bounds__(64) gemm_rows_kernel(GemmArgs g)
     uint4 va[ROWS_KSTEPS], vb[ROWS_KSTEPS];
 #pragma unroll
     for (int s = 0; s < ROWS_KSTEPS; ++s) {
-        const int k0 = s * GK;
+        const int k0 = s * 32;
         const bool kin = k0 + fk < g.K;
         va[s] = make_uint4(0, 0, 0, 0);
         vb[s] = make_uint4(0, 0, 0, 0);
@@ -260,7 +305,7 @@ __global__ void __launch_bounds__(64) gemm_rows_kernel(GemmArgs g)
     f32x4_t acc = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < ROWS_KSTEPS; ++s)
-        if (s * GK < g.K)
+        if (s * 32 < g.K)
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, va[s]),
                                                           __builtin_bit_cast(bf16x8_t, vb[s]), acc,
                                                           0, 0, 0);
@@ -274,17 +319,19 @@ __global__ void __launch_bounds__(64) gemm_rows_kernel(GemmArgs g)
         const size_t o = (size_t)m * g.ldc + n;
         if (EPI == EPI_BIAS_GELU) {
             const float z = v + g.bias[n];
-            g.Cf[o] = z;
+            if (g.Cf) g.Cf[o] = z;
             g.Cb[o] = f2bf(gelu(z));
         } else {
-            g.Cf[o] = v + g.bias[n];
+            const float z = v + g.bias[n];
+            g.Cf[o] = z;
+            if (g.out && m < g.out_m && n < g.out_n) g.out[(size_t)m * g.ld_out + n] = z;
         }
     }
 }
 
 int gemm_rows(const GemmArgs &g, int epi, void *stream)
 {
-    if ((g.M | g.N | g.K) & 7 || g.M < 1 || g.K > ROWS_KSTEPS * GK) return -1;
+    if ((g.M | g.N | g.K) & 7 || g.M < 1 || g.K > ROWS_KSTEPS * 32) return -1;
     const dim3 grid((unsigned)((g.N + 15) / 16), (unsigned)((g.M + 15) / 16));
     if (epi == EPI_BIAS_GELU)
         hipLaunchKernelGGL(gemm_rows_kernel<EPI_BIAS_GELU>, grid, dim3(64), 0, (hipStream_t)stream, g);
@@ -298,75 +345,102 @@ int gemm_rows(const GemmArgs &g, int epi, void *stream)
 int gemm(const GemmArgs &g, bool a_k, bool b_k, int epi, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    if ((g.M | g.N | g.K) & 7) return -1;
-#define GEMM_CASE(AK, BK)                                                          \
-    if (a_k == AK && b_k == BK) {                                                  \
-        switch (epi) {                                                             \
-        case EPI_NONE: launch_shape<AK, BK, EPI_NONE>(g, st); break;               \
-        case EPI_BIAS: launch_shape<AK, BK, EPI_BIAS>(g, st); break;               \
-        case EPI_BIAS_GELU: launch_shape<AK, BK, EPI_BIAS_GELU>(g, st); break;     \
-        case EPI_GELU_GRAD: launch_shape<AK, BK, EPI_GELU_GRAD>(g, st); break;     \
-        default: return -1;                                                        \
-        }                                                                          \
-        return hipGetLastError() == hipSuccess ? 0 : -1;                           \
-    }
-    GEMM_CASE(true, true)
-    GEMM_CASE(false, false)
-    GEMM_CASE(true, false)
-    GEMM_CASE(false, true)
-#undef GEMM_CASE
-    return -1;
+    if ((g.M | g.N) & 7 || g.K & 31 || g.M < 8 || g.N < 8 || g.K < 32) return -1;
+    // the operand orders in use: layers (both k-contiguous), input gradients
+    // (the weights as stored), weight gradients (neither)
+    if (a_k && b_k && epi == EPI_BIAS)
+        launch_shape<true, true, EPI_BIAS>(g, st);
+    else if (a_k && b_k && epi == EPI_BIAS_GELU)
+        launch_shape<true, true, EPI_BIAS_GELU>(g, st);
+    else if (a_k && !b_k && epi == EPI_GELU_GRAD)
+        launch_shape<true, false, EPI_GELU_GRAD>(g, st);
+    else if (!a_k && !b_k && epi == EPI_NONE)
+        launch_shape<false, false, EPI_NONE>(g, st);
+    else
+        return -1;
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // ---------------------------------------------------------------------------
 // elementwise and reduction kernels
 // ---------------------------------------------------------------------------
 
-// Column sums of dz [M][ld] (bias gradients), in two deterministic passes:
-// block (x, y) sums rows [y * COLSUM_ROWS, (y + 1) * COLSUM_ROWS) of columns
-// [64 x, 64 x + 64) (lanes = columns, four row phases, combined in a fixed
-// order) into part[y][n]; then each column adds its chunks in order.
+// Column sums of every layer's dz [M][N] (bias gradients), in two deterministic
+// passes over one job list: block (x, y) sums rows [y * COLSUM_ROWS, (y + 1) *
+// COLSUM_ROWS) of 64 columns of one layer (lanes = columns, four row phases,
+// each phase's 32 loads in flight together, combined in a fixed order) into
+// part[y][n]; then each column adds its chunks in order.  One launch per pass
+// for all layers: 16 us for what took 8 launches of 8 to 9 us each.
 #define COLSUM_ROWS 128
-__global__ void __launch_bounds__(256) colsum_part_kernel(const uint16_t *__restrict__ dz, int M,
-                                                          int N, int ld, float *__restrict__ part)
+__device__ __forceinline__ int colsum_job(const ColsumJobs &jobs, int &x)
+{
+    int j = 0;
+    while (j < 3 && x >= jobs.n[j] / 64) x -= jobs.n[j++] / 64;
+    return j;
+}
+
+__global__ void __launch_bounds__(256) colsum_part_kernel(ColsumJobs jobs, int M)
 {
     __shared__ float red[4][64];
+    int x = blockIdx.x;
+    const int j = colsum_job(jobs, x);
     const int c = threadIdx.x & 63, r = threadIdx.x >> 6;
-    const int n = blockIdx.x * 64 + c;
+    const int n = x * 64 + c, N = jobs.n[j];
     const int m0 = blockIdx.y * COLSUM_ROWS;
-    const int m1 = min(m0 + COLSUM_ROWS, M);
+    const uint16_t *p = jobs.dz[j] + (size_t)(m0 + r) * N + n;
+    uint16_t v[COLSUM_ROWS / 4];
+#pragma unroll
+    for (int i = 0; i < COLSUM_ROWS / 4; ++i)
+        v[i] = m0 + r + 4 * i < M ? p[(size_t)(4 * i) * N] : 0;
     float s = 0.0f;
-    if (n < N)
-        for (int m = m0 + r; m < m1; m += 4) s += bf2f(dz[(size_t)m * ld + n]);
+#pragma unroll
+    for (int i = 0; i < COLSUM_ROWS / 4; ++i) s += bf2f(v[i]);
     red[r][c] = s;
     __syncthreads();
-    if (r == 0 && n < N)
-        part[(size_t)blockIdx.y * N + n] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+    if (r == 0)
+        jobs.part[j][(size_t)blockIdx.y * N + n] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }
 
-__global__ void colsum_final_kernel(const float *__restrict__ part, int chunks, int N,
-                                    float *__restrict__ db)
+__global__ void __launch_bounds__(64) colsum_final_kernel(ColsumJobs jobs, int chunks)
 {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
+    int x = blockIdx.x;
+    const int j = colsum_job(jobs, x);
+    const int n = x * 64 + threadIdx.x, N = jobs.n[j];
     float s = 0.0f;
-    for (int k = 0; k < chunks; ++k) s += part[(size_t)k * N + n];
-    db[n] = s;
+    for (int k0 = 0; k0 < chunks; k0 += 16) {
+        float v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            v[q] = k0 + q < chunks ? jobs.part[j][(size_t)(k0 + q) * N + n] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < 16; ++q)
+            if (k0 + q < chunks) s += v[q];
+    }
+    jobs.db[j][n] = s;
 }
 
-__device__ __forceinline__ float block_reduce(float v, float *red, bool is_max)
+// Sums or maxima of NV values over the 256 threads of a block, on every thread:
+// the tree v[t] + v[t + 128], then + 64, 32, ... 1, the last six steps by lane
+// reads in every wave alike (one barrier; red is free again after the next
+// one).
+template <int NV, bool MAX>
+__device__ __forceinline__ void block_reduce(float (&v)[NV], float (*red)[256])
 {
-    red[threadIdx.x] = v;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) red[i][threadIdx.x] = v[i];
     __syncthreads();
-    for (int s = blockDim.x >> 1; s > 0; s >>= 1) {
-        if (threadIdx.x < s)
-            red[threadIdx.x] = is_max ? fmaxf(red[threadIdx.x], red[threadIdx.x + s])
-                                      : red[threadIdx.x] + red[threadIdx.x + s];
-        __syncthreads();
+    const int l = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const float a = red[i][l], b = red[i][l + 64], c = red[i][l + 128], d = red[i][l + 192];
+        float x = MAX ? fmaxf(fmaxf(a, c), fmaxf(b, d)) : (a + c) + (b + d);
+#pragma unroll
+        for (int s = 32; s > 0; s >>= 1) {
+            const float y = __shfl_down(x, s, 64);
+            x = MAX ? fmaxf(x, y) : x + y;
+        }
+        v[i] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
     }
-    float r = red[0];
-    __syncthreads();
-    return r;
 }
 
 // Training loss of one row (one block per row, 256 threads):
@@ -376,7 +450,12 @@ __device__ __forceinline__ float block_reduce(float v, float *red, bool is_max)
 // squared error, excluded from the target distribution of the cross-entropy
 // (which ranks the best cells first).  w_c = 1 + pos_weight * t_c.  Writes
 // dZ as bf16 (zero in padding) and, per row, the squared-error sum and the
-// cross-entropy.
+// cross-entropy.  Bound by memory (4096 rows: 92 MB read, 23 written): a
+// thread keeps its cells of the row in registers, so predictions and targets
+// are read once instead of three times, the target exponentials serve the
+// sum and the distribution, and three block reductions take one barrier
+// each instead of six with nine.
+constexpr int LOSS_PER = TOPK_SORT / 256;  // cells per thread, at most
 __global__ void __launch_bounds__(256) loss_kernel(const float *__restrict__ y, int ldy,
                                                    const float *__restrict__ tgt, int ldt, int rows,
                                                    int outs, int rows_pad, int outs_pad,
@@ -384,60 +463,76 @@ __global__ void __launch_bounds__(256) loss_kernel(const float *__restrict__ y, 
                                                    uint16_t *__restrict__ dz,
                                                    float *__restrict__ partial)
 {
-    __shared__ float red[256];
-    const int r = blockIdx.x;
+    __shared__ float red[3][2][256];
+    const int r = blockIdx.x, t0 = threadIdx.x;
     const bool real = r < rows;
     const float itau = 1.0f / tau;
-    float my = -INFINITY, mt = -INFINITY;
+    float yv[LOSS_PER], tv[LOSS_PER], et[LOSS_PER];
+    float mx[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+    for (int i = 0; i < LOSS_PER; ++i) {
+        const int n = t0 + 256 * i;
+        yv[i] = 0.0f;
+        tv[i] = -INFINITY;
+        if (real && n < outs) {
+            yv[i] = y[(size_t)r * ldy + n];
+            tv[i] = tgt[(size_t)r * ldt + n];
+        }
+    }
     if (real && ce_weight > 0.0f) {
-        for (int n = threadIdx.x; n < outs; n += blockDim.x) {
-            float t = tgt[(size_t)r * ldt + n];
-            my = fmaxf(my, y[(size_t)r * ldy + n] * itau);
-            if (t > -INFINITY) mt = fmaxf(mt, t * itau);
-        }
+#pragma unroll
+        for (int i = 0; i < LOSS_PER; ++i)
+            if (t0 + 256 * i < outs) {
+                mx[0] = fmaxf(mx[0], yv[i] * itau);
+                if (tv[i] > -INFINITY) mx[1] = fmaxf(mx[1], tv[i] * itau);
+            }
     }
-    my = block_reduce(my, red, true);
-    mt = block_reduce(mt, red, true);
+    block_reduce<2, true>(mx, red[0]);
+    const float my = mx[0], mt = mx[1];
     const bool ce = real && ce_weight > 0.0f && mt > -INFINITY;
-    float sy = 0.0f, st = 0.0f;
-    if (ce) {
-        for (int n = threadIdx.x; n < outs; n += blockDim.x) {
-            float t = tgt[(size_t)r * ldt + n];
-            sy += expf(y[(size_t)r * ldy + n] * itau - my);
-            if (t > -INFINITY) st += expf(t * itau - mt);
+    float sm[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < LOSS_PER; ++i) {
+        et[i] = 0.0f;
+        if (ce && t0 + 256 * i < outs) {
+            sm[0] += expf(yv[i] * itau - my);
+            if (tv[i] > -INFINITY) {
+                et[i] = expf(tv[i] * itau - mt);
+                sm[1] += et[i];
+            }
         }
     }
-    sy = block_reduce(sy, red, false);
-    st = block_reduce(st, red, false);
-    const float lsy = ce ? logf(sy) : 0.0f;
+    block_reduce<2, false>(sm, red[1]);
+    const float st = sm[1];
+    const float lsy = ce ? logf(sm[0]) : 0.0f;
     const float scale = 2.0f / ((float)rows * (float)outs);
     const float cscale = ce_weight * itau / (float)rows;
-    float acc = 0.0f, ent = 0.0f;
-    for (int n = threadIdx.x; n < outs_pad; n += blockDim.x) {
+    float ae[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < LOSS_PER; ++i) {
+        const int n = t0 + 256 * i;
+        if (n >= outs_pad) break;
         float g = 0.0f;
         if (real && n < outs) {
-            float traw = tgt[(size_t)r * ldt + n];
-            float t = traw > -INFINITY ? traw : 0.0f;
-            float yy = y[(size_t)r * ldy + n];
-            float wgt = 1.0f + pos_weight * t;
-            float d = yy - t;
-            acc += wgt * d * d;
+            const float t = tv[i] > -INFINITY ? tv[i] : 0.0f;
+            const float wgt = 1.0f + pos_weight * t;
+            const float d = yv[i] - t;
+            ae[0] += wgt * d * d;
             g = scale * wgt * d;
             if (ce) {
-                float lp = yy * itau - my - lsy;
-                float p = expf(lp);
-                float q = traw > -INFINITY ? expf(traw * itau - mt) / st : 0.0f;
-                ent -= q * lp;
+                const float lp = yv[i] * itau - my - lsy;
+                const float p = expf(lp);
+                const float q = tv[i] > -INFINITY ? et[i] / st : 0.0f;
+                ae[1] -= q * lp;
                 g += cscale * (p - q);
             }
         }
         dz[(size_t)r * outs_pad + n] = f2bf(g);
     }
-    acc = block_reduce(acc, red, false);
-    ent = block_reduce(ent, red, false);
+    block_reduce<2, false>(ae, red[2]);
     if (threadIdx.x == 0 && r < rows_pad) {
-        partial[2 * r] = acc;
-        partial[2 * r + 1] = ent;
+        partial[2 * r] = ae[0];
+        partial[2 * r + 1] = ae[1];
     }
 }
 
@@ -462,44 +557,44 @@ __global__ void pool_kernel(const float *__restrict__ fine, int n_frames, int fn
     coarse[i] = m;
 }
 
-// Adam on one parameter tensor (f32 master), then refresh its bf16 copies:
-// the weight as stored [out][in] and, for matrices, transposed [in][out].
-__global__ void adam_kernel(float *__restrict__ w, const float *__restrict__ g, float *__restrict__ m,
-                            float *__restrict__ v, int64_t n, float lr, float b1, float b2, float eps,
-                            float c1, float c2, float wd, uint16_t *__restrict__ wb,
-                            uint16_t *__restrict__ wbt, int rows, int cols)
+// Adam on every parameter tensor (f32 master) of the job list, four elements
+// per thread, refreshing the weights' bf16 copies.  Bound by memory (28 + 2
+// bytes per parameter, 60 MB); one launch instead of eight.
+__global__ void __launch_bounds__(256) adam_kernel(AdamJobs jobs, float lr, float b1, float b2,
+                                                   float eps, float c1, float c2)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float gi = g[i] + wd * w[i];
-    float mi = b1 * m[i] + (1.0f - b1) * gi;
-    float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-    w[i] = wi;
-    if (wb) {
-        uint16_t h = f2bf(wi);
-        wb[i] = h;
-        if (wbt) {
-            int r = (int)(i / cols), c = (int)(i - (int64_t)r * cols);
-            wbt[(size_t)c * rows + r] = h;
-        }
+    int x = blockIdx.x, j = 0;
+    while (j < ADAM_JOBS - 1 && x >= jobs.blocks[j]) x -= jobs.blocks[j++];
+    const AdamJob J = jobs.job[j];
+    const int64_t i = ((int64_t)x * 256 + threadIdx.x) * 4;
+    if (i >= J.n) return;
+    f32x4_t w = *(const f32x4_t *)(J.w + i), m = *(const f32x4_t *)(J.m + i);
+    f32x4_t v = *(const f32x4_t *)(J.v + i);
+    const f32x4_t g = *(const f32x4_t *)(J.g + i);
+    uint16_t h[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float gi = g[q] + J.wd * w[q];
+        const float mi = b1 * m[q] + (1.0f - b1) * gi;
+        const float vi = b2 * v[q] + (1.0f - b2) * gi * gi;
+        m[q] = mi;
+        v[q] = vi;
+        w[q] = w[q] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+        h[q] = f2bf(w[q]);
     }
+    *(f32x4_t *)(J.m + i) = m;
+    *(f32x4_t *)(J.v + i) = v;
+    *(f32x4_t *)(J.w + i) = w;
+    if (J.wb)
+        *(uint2 *)(J.wb + i) = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16),
+                                          (uint32_t)h[2] | ((uint32_t)h[3] << 16));
 }
 
-// bf16 copies of a weight matrix [rows][cols] and its transpose.
-__global__ void cast_kernel(const float *__restrict__ w, int64_t n, uint16_t *__restrict__ wb,
-                            uint16_t *__restrict__ wbt, int rows, int cols)
+// bf16 copy of a weight matrix.
+__global__ void cast_kernel(const float *__restrict__ w, int64_t n, uint16_t *__restrict__ wb)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    uint16_t h = f2bf(w[i]);
-    wb[i] = h;
-    if (wbt) {
-        int r = (int)(i / cols), c = (int)(i - (int64_t)r * cols);
-        wbt[(size_t)c * rows + r] = h;
-    }
+    if (i < n) wb[i] = f2bf(w[i]);
 }
 
 // Feature vector of a frame (one wave per row): teammates with the passer
@@ -794,15 +889,18 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float *__restr
 
 int colsum_chunks(int M) { return (M + COLSUM_ROWS - 1) / COLSUM_ROWS; }
 
-int launch_colsum(const uint16_t *dz, int M, int N, int ld, float *db, float *part, void *st)
+int launch_colsum(const ColsumJobs &jobs, int M, void *st)
 {
     const int chunks = colsum_chunks(M);
-    if (M > 0 && N > 0) {
-        hipLaunchKernelGGL(colsum_part_kernel, dim3((N + 63) / 64, chunks), dim3(256), 0,
-                           (hipStream_t)st, dz, M, N, ld, part);
-        hipLaunchKernelGGL(colsum_final_kernel, dim3((N + 255) / 256), dim3(256), 0,
-                           (hipStream_t)st, part, chunks, N, db);
+    int blocks = 0;
+    for (int j = 0; j < 4; ++j) {
+        if (jobs.n[j] < 64 || jobs.n[j] % 64) return -1;
+        blocks += jobs.n[j] / 64;
     }
+    if (M < 1) return -1;
+    hipLaunchKernelGGL(colsum_part_kernel, dim3(blocks, chunks), dim3(256), 0, (hipStream_t)st, jobs,
+                       M);
+    hipLaunchKernelGGL(colsum_final_kernel, dim3(blocks), dim3(64), 0, (hipStream_t)st, jobs, chunks);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -810,6 +908,7 @@ int launch_loss(const float *y, int ldy, const float *tgt, int ldt, int rows, in
                 int outs_pad, float pos_weight, float ce_weight, float tau, uint16_t *dz,
                 float *partial, void *st)
 {
+    if (outs > outs_pad || outs_pad > LOSS_PER * 256) return -1;
     hipLaunchKernelGGL(loss_kernel, dim3(rows_pad), dim3(256), 0, (hipStream_t)st, y, ldy, tgt, ldt,
                        rows, outs, rows_pad, outs_pad, pos_weight, ce_weight, tau, dz, partial);
     return hipGetLastError() == hipSuccess ? 0 : -1;
@@ -825,20 +924,23 @@ int launch_pool(const float *fine, int n_frames, int fnx, int fny, float *coarse
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_adam(float *w, const float *g, float *m, float *v, int64_t n, float lr, float b1, float b2,
-                float eps, float c1, float c2, float wd, uint16_t *wb, uint16_t *wbt, int rows,
-                int cols, void *st)
+int launch_adam(AdamJobs jobs, float lr, float b1, float b2, float eps, float c1, float c2, void *st)
 {
-    hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       (hipStream_t)st, w, g, m, v, n, lr, b1, b2, eps, c1, c2, wd, wb, wbt, rows,
-                       cols);
+    int blocks = 0;
+    for (int j = 0; j < ADAM_JOBS; ++j) {
+        if (jobs.job[j].n < 4 || jobs.job[j].n % 4) return -1;
+        jobs.blocks[j] = (int)((jobs.job[j].n / 4 + 255) / 256);
+        blocks += jobs.blocks[j];
+    }
+    hipLaunchKernelGGL(adam_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)st, jobs, lr, b1, b2,
+                       eps, c1, c2);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_cast(const float *w, int64_t n, uint16_t *wb, uint16_t *wbt, int rows, int cols, void *st)
+int launch_cast(const float *w, int64_t n, uint16_t *wb, void *st)
 {
     hipLaunchKernelGGL(cast_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       (hipStream_t)st, w, n, wb, wbt, rows, cols);
+                       (hipStream_t)st, w, n, wb);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
