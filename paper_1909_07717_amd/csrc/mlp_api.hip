@@ -72,6 +72,7 @@ struct dpps_mlp {
     int32_t *fcount;
     uint32_t *fcounter;
     int32_t *h_count = nullptr;  // pinned landing word of the fallback count
+    float *h_params = nullptr;   // pinned buffer of the real parameters (first use)
 };
 
 // Points per tile of the device-side exact fallback (its tiles are implicit).
@@ -97,23 +98,32 @@ static int refresh_bf16(dpps_mlp *m, hipStream_t st)
 }
 
 // copy between the real parameter layout on the host (W0 [512][66], b0,
-// W1, b1, W2, b2, W3 [2806][512], b3 [2806]) and the padded device tensors
+// W1, b1, W2, b2, W3 [2806][512], b3 [2806]) and the padded device tensors,
+// through the network's pinned buffer; synchronous, on the legacy default
+// stream (ordered after the work of every blocking stream, as a plain copy is)
 static int params_xfer(dpps_mlp *m, float *const *dw, float *const *db, float *host, bool to_dev)
 {
+    const size_t bytes = (size_t)real_count() * sizeof(float);
+    HIP_OK(hipSetDevice(m->ctx->device));
+    if (!m->h_params &&
+        hipHostMalloc((void **)&m->h_params, bytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        m->h_params = nullptr;
+        return fail(DPPS_E_NOMEM, "hipHostMalloc of the parameter buffer failed");
+    }
+    ParamJobs jobs;
     int64_t o = 0;
     for (int l = 0; l < NL; ++l) {
-        size_t wrow = (size_t)IN_REAL[l] * 4, dpitch = (size_t)IN_DIM[l] * 4;
-        if (to_dev)
-            HIP_OK(hipMemcpy2D(dw[l], dpitch, host + o, wrow, wrow, OUT_REAL[l], hipMemcpyHostToDevice));
-        else
-            HIP_OK(hipMemcpy2D(host + o, wrow, dw[l], dpitch, wrow, OUT_REAL[l], hipMemcpyDeviceToHost));
+        jobs.job[2 * l] = {dw[l], o, OUT_REAL[l], IN_REAL[l], IN_DIM[l]};
         o += (int64_t)OUT_REAL[l] * IN_REAL[l];
-        if (to_dev)
-            HIP_OK(hipMemcpy(db[l], host + o, (size_t)OUT_REAL[l] * 4, hipMemcpyHostToDevice));
-        else
-            HIP_OK(hipMemcpy(host + o, db[l], (size_t)OUT_REAL[l] * 4, hipMemcpyDeviceToHost));
+        jobs.job[2 * l + 1] = {db[l], o, 1, OUT_REAL[l], OUT_REAL[l]};
         o += OUT_REAL[l];
     }
+    if (to_dev) memcpy(m->h_params, host, bytes);
+    if (launch_params(jobs, m->h_params, to_dev, nullptr))
+        return fail(DPPS_E_DEVICE, "parameter copy launch failed");
+    HIP_OK(hipStreamSynchronize(nullptr));
+    if (!to_dev) memcpy(host, m->h_params, bytes);
     return DPPS_OK;
 }
 
@@ -379,6 +389,7 @@ void dpps_mlp_destroy(dpps_mlp *m)
         if (m->ctx) m->ctx->budget_used -= m->arena_bytes;
     }
     if (m->h_count) (void)hipHostFree(m->h_count);
+    if (m->h_params) (void)hipHostFree(m->h_params);
     delete m;
 }
 

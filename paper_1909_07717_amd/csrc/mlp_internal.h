@@ -64,6 +64,18 @@ struct AdamJobs {
     int blocks[ADAM_JOBS];  // set by the launcher
 };
 int launch_adam(AdamJobs jobs, float lr, float b1, float b2, float eps, float c1, float c2, void *st);
+// Copies of padded device tensors (dev, pitch floats a row) and their real
+// rows x cols elements at off in the host's parameter vector (pinned memory).
+struct ParamJob {
+    float *dev;
+    int64_t off;
+    int rows, cols, pitch;
+};
+struct ParamJobs {
+    ParamJob job[ADAM_JOBS];
+    int blocks[ADAM_JOBS];  // set by the launcher
+};
+int launch_params(ParamJobs jobs, float *host, bool to_dev, void *st);
 int launch_cast(const float *w, int64_t n, uint16_t *wb, void *st);
 int launch_featurize(const FrameDev *frames, const dpps_robot *robots, int n_frames, int rows_pad,
                      int in_pad, float inv_hl, float inv_hw, float inv_v, uint16_t *x, void *st);

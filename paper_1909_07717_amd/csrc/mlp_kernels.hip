@@ -590,6 +590,31 @@ __global__ void __launch_bounds__(256) adam_kernel(AdamJobs jobs, float lr, floa
                                           (uint32_t)h[2] | ((uint32_t)h[3] << 16));
 }
 
+// Parameters between the real layout in pinned host memory (per layer the
+// matrix [rows][cols], then the bias [rows]) and the padded device tensors, in
+// one pass over the host link; one block per 1024 real elements of a layer's
+// matrix or bias.  Copies row by row through pageable memory took 29 ms for
+// the 8 MB.
+template <bool TO_DEV>
+__global__ void __launch_bounds__(256) params_kernel(ParamJobs jobs, float *__restrict__ host)
+{
+    int x = blockIdx.x, j = 0;
+    while (j < ADAM_JOBS - 1 && x >= jobs.blocks[j]) x -= jobs.blocks[j++];
+    const ParamJob J = jobs.job[j];
+    const unsigned n = (unsigned)J.rows * (unsigned)J.cols;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const unsigned i = (unsigned)x * 1024u + (unsigned)q * 256u + threadIdx.x;
+        if (i >= n) return;
+        const unsigned r = i / (unsigned)J.cols, c = i - r * (unsigned)J.cols;
+        float *const d = J.dev + (size_t)r * J.pitch + c;
+        if (TO_DEV)
+            *d = host[J.off + i];
+        else
+            host[J.off + i] = *d;
+    }
+}
+
 // bf16 copy of a weight matrix.
 __global__ void cast_kernel(const float *__restrict__ w, int64_t n, uint16_t *__restrict__ wb)
 {
@@ -934,6 +959,21 @@ int launch_adam(AdamJobs jobs, float lr, float b1, float b2, float eps, float c1
     }
     hipLaunchKernelGGL(adam_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)st, jobs, lr, b1, b2,
                        eps, c1, c2);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_params(ParamJobs jobs, float *host, bool to_dev, void *st)
+{
+    int blocks = 0;
+    for (int j = 0; j < ADAM_JOBS; ++j) {
+        if (jobs.job[j].rows < 1 || jobs.job[j].cols < 1) return -1;
+        jobs.blocks[j] = (int)(((int64_t)jobs.job[j].rows * jobs.job[j].cols + 1023) / 1024);
+        blocks += jobs.blocks[j];
+    }
+    if (to_dev)
+        hipLaunchKernelGGL(params_kernel<true>, dim3(blocks), dim3(256), 0, (hipStream_t)st, jobs, host);
+    else
+        hipLaunchKernelGGL(params_kernel<false>, dim3(blocks), dim3(256), 0, (hipStream_t)st, jobs, host);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
