@@ -172,7 +172,7 @@ static int forward(dpps_mlp *m, const dpps_batch *bt, hipStream_t st, bool train
             g.out_n = OUT;
             epi = EPI_BIAS;
         }
-        if (small ? gemm_rows(g, epi, (void *)st) : gemm(g, true, true, epi, (void *)st))
+        if (small ? gemm_rows(g, epi, (void *)st) : gemm(g, epi, (void *)st))
             return fail(DPPS_E_DEVICE, "gemm launch failed");
     }
     return DPPS_OK;
@@ -209,13 +209,15 @@ static int backward_loss(dpps_mlp *m, int nf, const float *tgt, int64_t ld_t, Lo
         g.Cf = m->gw[l];
         g.work = m->gwork;  // the reduction over the batch may be split
         g.work_elems = GWORK_ELEMS;
-        if (gemm(g, false, false, EPI_NONE, (void *)st)) return fail(DPPS_E_DEVICE, "gemm failed");
         cs.dz[l] = dz_top;
         cs.db[l] = m->gb[l];
         cs.n[l] = OUT_DIM[l];
         cs.part[l] = part;
         part += (size_t)colsum_chunks(R) * OUT_DIM[l];
-        if (l == 0) break;
+        if (l == 0) {
+            if (gemm_backward(nullptr, g, (void *)st)) return fail(DPPS_E_DEVICE, "gemm failed");
+            break;
+        }
         // dZ_{l-1} = (dZ_l W_l) * gelu'(Z_{l-1})
         GemmArgs h;
         memset(&h, 0, sizeof h);
@@ -229,7 +231,7 @@ static int backward_loss(dpps_mlp *m, int nf, const float *tgt, int64_t ld_t, Lo
         h.ldc = IN_DIM[l];
         h.Zin = m->z[l - 1];
         h.Cb = m->dz[l - 1];
-        if (gemm(h, true, false, EPI_GELU_GRAD, (void *)st)) return fail(DPPS_E_DEVICE, "gemm failed");
+        if (gemm_backward(&h, g, (void *)st)) return fail(DPPS_E_DEVICE, "gemm failed");
         dz_top = m->dz[l - 1];
     }
     if (launch_colsum(cs, R, (void *)st)) return fail(DPPS_E_DEVICE, "colsum failed");

@@ -7,7 +7,7 @@
 
 namespace dpps {
 
-enum { EPI_NONE = 0, EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_GRAD = 3, EPI_PARTIAL = 4 };
+enum { EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_GRAD = 3, EPI_PARTIAL = 4 };
 
 #define TOPK_SORT 4096   // most cells per frame for the top-k (>= coarse lattice size)
 #define TOPK_MAX 256     // largest k (one workgroup thread per winner)
@@ -21,7 +21,7 @@ struct GemmArgs {
     const float *Zin;    // EPI_GELU_GRAD: pre-activation, [M][ldc]
     float *Cf;           // f32 output (EPI_BIAS_GELU: may be NULL)
     uint16_t *Cb;        // bf16 output
-    float *work;         // optional workspace for a K split (EPI_NONE only), work_elems floats
+    float *work;         // workspace of a K split (weight gradients), work_elems floats
     int64_t work_elems;
     int k_slice;         // set by the dispatcher
     float *out;          // EPI_BIAS: a second copy of rows < out_m, columns < out_n (may be NULL)
@@ -29,11 +29,16 @@ struct GemmArgs {
     int out_m, out_n;
 };
 
-int gemm(const GemmArgs &g, bool a_k, bool b_k, int epi, void *stream);
+// A layer's product (A, B k-contiguous; EPI_BIAS or EPI_BIAS_GELU).
+int gemm(const GemmArgs &g, int epi, void *stream);
+// The two products of a backward layer: x (may be NULL), the input gradient
+// (A k-contiguous, B as [k][n]; GELU-gradient epilogue), and w, the weight
+// gradient (A as [k][m], B as [k][n]) into w.Cf through the workspace w.work.
+int gemm_backward(const GemmArgs *x, const GemmArgs &w, void *stream);
 // Inference GEMM of a few rows (A, B k-contiguous; EPI_BIAS or EPI_BIAS_GELU),
-// bit-identical per element to gemm(g, true, true, epi, stream).
+// bit-identical per element to gemm(g, epi, stream).
 int gemm_rows(const GemmArgs &g, int epi, void *stream);
-// Column sums of the layers' output gradients dz [M][n] (n a multiple of 64):
+// Column sums of the layers' output gradients dz [M][n] (n a multiple of 256):
 // db; part holds colsum_chunks(M) x n floats.
 struct ColsumJobs {
     const uint16_t *dz[4];

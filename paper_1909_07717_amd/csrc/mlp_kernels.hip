@@ -13,6 +13,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
+
 #include "mlp_internal.h"
 
 namespace dpps {
@@ -45,7 +47,7 @@ __device__ __forceinline__ float gelu_grad(float x)
 // A(m, k) = A[m*lda + k] when A_K (k contiguous), else A[k*lda + m].
 // B(k, n) = B[n*ldb + k] when B_K (k contiguous), else B[k*ldb + n].
 // M, N are multiples of 8, K and every K slice multiples of 32.
-// Block tile BM x BN (128 x 128 or 64 x 64), K step 64, 256 threads: four
+// Block tile BM x BN (128 x 64 or 64 x 64), K step 64, 256 threads: four
 // waves in a 2 x 2 arrangement, each owning a (BM/2) x (BN/2) quarter as
 // (BM/32) x (BN/32) MFMA tiles of 16 x 16 (v_mfma_f32_16x16x32_bf16, k
 // ascending from 0, so an output element has the same bits whatever the tile).
@@ -56,8 +58,10 @@ __device__ __forceinline__ float gelu_grad(float x)
 // that is not k-contiguous (the weight gradients) stays as it lies in memory
 // and is transposed by the LDS reads (ds_read_b64_tr_b16).  16-byte chunks
 // are permuted within LDS so that a read's lanes spread over the banks.
-// blockIdx.z splits K into slices of g.k_slice; with EPI_PARTIAL slice z
-// writes its partial product to Cf + z * M * ldc (summed by gemm_reduce).
+// K may be split into slices of g.k_slice; with EPI_PARTIAL slice z writes its
+// partial product to Cf + z * M * ldc (summed by gemm_reduce).  (Four buffers
+// instead of two gained nothing: the waits before LDS reads are not told
+// apart by buffer, and two leave room for five workgroups a CU.)
 // ---------------------------------------------------------------------------
 #define GK 64
 
@@ -153,14 +157,29 @@ __device__ __forceinline__ void gemm_store(const GemmArgs &g, float *part, int m
     }
 }
 
+// LDS of a workgroup: two buffers of each operand.
+constexpr int gemm_lds(int BM, int BN) { return 2 * (BM + BN) * GK; }
+
+// Output tile `id` of the (gx column tiles) x (gy row tiles) x (gz K slices) of
+// a product.
 template <int BM, int BN, bool A_K, bool B_K, int EPI>
-__global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g)
+__device__ __forceinline__ void gemm_block(const GemmArgs &g, int id, int gx, int gy, int gz,
+                                           uint16_t *lds)
 {
     constexpr int TM = BM / 32, TN = BN / 32;
-    __shared__ __attribute__((aligned(16))) uint16_t As[2][BM * GK];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][BN * GK];
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-    const int kb = blockIdx.z * g.k_slice;
+    uint16_t *const As = lds, *const Bs = lds + 2 * BM * GK;
+    // Workgroups go to the 8 XCDs in turn, each with its own L2: the column
+    // tiles of one panel (the rows of a tile, one K slice) are given to one
+    // XCD, so that a panel of A is read from memory once and not by all eight.
+    int panel = id / gx, n_tile = id % gx;
+    const int even = gy * gz / 8 * 8;
+    if (id < even * gx) {
+        panel = (id / 8) / gx * 8 + id % 8;
+        n_tile = (id / 8) % gx;
+    }
+    const int z = panel / gy;
+    const int m0 = (panel - z * gy) * BM, n0 = n_tile * BN;
+    const int kb = z * g.k_slice;
     const int ke = min(kb + g.k_slice, g.K);
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int wm = (w >> 1) * (BM / 2), wn = (w & 1) * (BN / 2);
@@ -169,25 +188,26 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g)
     for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b) acc[a][b] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-    load_tile<BM, A_K>(g.A, g.lda, g.M, g.K, m0, kb, As[0]);
-    load_tile<BN, B_K>(g.B, g.ldb, g.N, g.K, n0, kb, Bs[0]);
+    load_tile<BM, A_K>(g.A, g.lda, g.M, g.K, m0, kb, As);
+    load_tile<BN, B_K>(g.B, g.ldb, g.N, g.K, n0, kb, Bs);
     int cur = 0;
     for (int k0 = kb; k0 < ke; k0 += GK, cur ^= 1) {
         // this wave's part of the step has landed; after the barrier all of
         // it has, and every wave is done with the other buffer
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
+        const uint16_t *const ta = As + cur * BM * GK, *const tb = Bs + cur * BN * GK;
         bf16x8_t af[2][TM], bfr[2][TN];
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-            for (int a = 0; a < TM; ++a) af[kk][a] = load_frag<BM, A_K>(As[cur], wm + a * 16, kk);
+            for (int a = 0; a < TM; ++a) af[kk][a] = load_frag<BM, A_K>(ta, wm + a * 16, kk);
 #pragma unroll
-            for (int b = 0; b < TN; ++b) bfr[kk][b] = load_frag<BN, B_K>(Bs[cur], wn + b * 16, kk);
+            for (int b = 0; b < TN; ++b) bfr[kk][b] = load_frag<BN, B_K>(tb, wn + b * 16, kk);
         }
         if (k0 + GK < ke) {
-            load_tile<BM, A_K>(g.A, g.lda, g.M, g.K, m0, k0 + GK, As[cur ^ 1]);
-            load_tile<BN, B_K>(g.B, g.ldb, g.N, g.K, n0, k0 + GK, Bs[cur ^ 1]);
+            load_tile<BM, A_K>(g.A, g.lda, g.M, g.K, m0, k0 + GK, As + (cur ^ 1) * BM * GK);
+            load_tile<BN, B_K>(g.B, g.ldb, g.N, g.K, n0, k0 + GK, Bs + (cur ^ 1) * BN * GK);
         }
         // operands swapped: the lane then holds four consecutive columns n of
         // one row m
@@ -202,7 +222,7 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g)
                                                                         acc[a][b], 0, 0, 0);
         }
     }
-    float *part = g.Cf + (size_t)blockIdx.z * g.M * g.ldc;
+    float *part = g.Cf + (size_t)z * g.M * g.ldc;
 #pragma unroll
     for (int a = 0; a < TM; ++a) {
         const int m = m0 + wm + a * 16 + (l & 15);
@@ -213,6 +233,28 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g)
             if (n < g.N) gemm_store<EPI>(g, part, m, n, acc[a][b]);
         }
     }
+}
+
+template <int BM, int BN, bool A_K, bool B_K, int EPI>
+__global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g, int gx, int gy, int gz)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t lds[gemm_lds(BM, BN)];
+    gemm_block<BM, BN, A_K, B_K, EPI>(g, blockIdx.x, gx, gy, gz, lds);
+}
+
+// The two products of a backward layer that need only its output gradient, in
+// one launch: blocks below nx form the input gradient's tiles (few, with long
+// reductions), the others the weight gradient's (split reductions).  Alone
+// the former leave most of the chip idle.
+__global__ void __launch_bounds__(256) gemm_backward_kernel(GemmArgs gx, GemmArgs gw, int nx,
+                                                            int xgx, int xgy, int wgx, int wgy,
+                                                            int wgz)
+{
+    __shared__ __attribute__((aligned(16))) uint16_t lds[gemm_lds(64, 64)];
+    if ((int)blockIdx.x < nx)
+        gemm_block<64, 64, true, false, EPI_GELU_GRAD>(gx, blockIdx.x, xgx, xgy, 1, lds);
+    else
+        gemm_block<64, 64, false, false, EPI_PARTIAL>(gw, (int)blockIdx.x - nx, wgx, wgy, wgz, lds);
 }
 
 // out[e] = sum over z of part[z][e], in order of z; four elements per thread,
@@ -239,40 +281,56 @@ __global__ void __launch_bounds__(256) gemm_reduce_kernel(const f32x4_t *__restr
 template <int BM, int BN, bool A_K, bool B_K, int EPI>
 static void launch_gemm(const GemmArgs &g, int splits, hipStream_t st)
 {
-    dim3 grid((g.N + BN - 1) / BN, (g.M + BM - 1) / BM, splits);
-    hipLaunchKernelGGL((gemm_kernel<BM, BN, A_K, B_K, EPI>), grid, dim3(256), 0, st, g);
+    const int gx = (g.N + BN - 1) / BN, gy = (g.M + BM - 1) / BM;
+    hipLaunchKernelGGL((gemm_kernel<BM, BN, A_K, B_K, EPI>), dim3(gx * gy * splits), dim3(256), 0, st,
+                       g, gx, gy, splits);
 }
 
+// Tiles of 64 x 64, or 128 x 64 where that still gives every CU two: the layer
+// 4096 x 2816 x 512 takes 25 us with 128 x 64, 29 with 128 x 128 or 64 x 64.
 template <bool A_K, bool B_K, int EPI>
 static void launch_shape(GemmArgs g, hipStream_t st)
 {
-    const int64_t t128 = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-    const int64_t t64 = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64);
-    if (EPI == EPI_NONE && g.work && t64 < 512 && g.K >= 1024) {
-        // few output tiles and a long reduction (weight gradients over the
-        // batch): split K into slices of a multiple of the K step, partial
-        // products into the workspace, then a fixed-order sum
-        int splits = (int)((512 + t64 - 1) / t64);
-        splits = min(splits, g.K / 256);
-        const int64_t mn = (int64_t)g.M * g.ldc;
-        while (splits > 1 && (int64_t)splits * mn > g.work_elems) --splits;
-        if (splits > 1) {
-            const int slice = ((g.K + splits - 1) / splits + 31) / 32 * 32;
-            splits = (g.K + slice - 1) / slice;
-            GemmArgs h = g;
-            h.k_slice = slice;
-            h.Cf = g.work;
-            launch_gemm<64, 64, A_K, B_K, EPI_PARTIAL>(h, splits, st);
-            hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)((mn / 4 + 255) / 256)), dim3(256),
-                               0, st, (const f32x4_t *)g.work, splits, mn / 4, (f32x4_t *)g.Cf);
-            return;
-        }
-    }
     g.k_slice = g.K;
-    if (t128 >= 256)
-        launch_gemm<128, 128, A_K, B_K, EPI>(g, 1, st);
+    const int64_t t = (int64_t)((g.M + 127) / 128) * ((g.N + 63) / 64);
+    if (t >= 512)
+        launch_gemm<128, 64, A_K, B_K, EPI>(g, 1, st);
     else
         launch_gemm<64, 64, A_K, B_K, EPI>(g, 1, st);
+}
+
+int gemm_backward(const GemmArgs *x, const GemmArgs &w, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    if ((w.M | w.N) & 7 || w.K & 31 || w.M < 8 || w.N < 8 || w.K < 32 || !w.work) return -1;
+    if (x && ((x->M | x->N) & 7 || x->K & 31 || x->M < 8 || x->N < 8 || x->K < 32)) return -1;
+    // the weight gradient has few output tiles and a long reduction (the
+    // batch): split K into slices of a multiple of 32, partial products into
+    // the workspace, then a fixed-order sum
+    GemmArgs h = w;
+    const int wgx = (w.N + 63) / 64, wgy = (w.M + 63) / 64;
+    const int64_t t64 = (int64_t)wgx * wgy, mn = (int64_t)w.M * w.ldc;
+    int splits = 1;
+    if (t64 < 512 && w.K >= 1024) splits = std::min((int)((512 + t64 - 1) / t64), w.K / 256);
+    while (splits > 1 && (int64_t)splits * mn > w.work_elems) --splits;
+    h.k_slice = splits > 1 ? ((w.K + splits - 1) / splits + 31) / 32 * 32 : w.K;
+    splits = (w.K + h.k_slice - 1) / h.k_slice;
+    h.Cf = splits > 1 ? w.work : w.Cf;
+    const int nw = wgx * wgy * splits;
+    if (x) {
+        GemmArgs g = *x;
+        g.k_slice = g.K;
+        const int xgx = (g.N + 63) / 64, xgy = (g.M + 63) / 64;
+        hipLaunchKernelGGL(gemm_backward_kernel, dim3(xgx * xgy + nw), dim3(256), 0, st, g, h,
+                           xgx * xgy, xgx, xgy, wgx, wgy, splits);
+    } else {
+        hipLaunchKernelGGL((gemm_kernel<64, 64, false, false, EPI_PARTIAL>), dim3(nw), dim3(256), 0,
+                           st, h, wgx, wgy, splits);
+    }
+    if (splits > 1)
+        hipLaunchKernelGGL(gemm_reduce_kernel, dim3((unsigned)((mn / 4 + 255) / 256)), dim3(256), 0,
+                           st, (const f32x4_t *)w.work, splits, mn / 4, (f32x4_t *)w.Cf);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // Few-row GEMM for inference on small batches (A and B k-contiguous): one
@@ -342,20 +400,14 @@ int gemm_rows(const GemmArgs &g, int epi, void *stream)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int gemm(const GemmArgs &g, bool a_k, bool b_k, int epi, void *stream)
+int gemm(const GemmArgs &g, int epi, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
     if ((g.M | g.N) & 7 || g.K & 31 || g.M < 8 || g.N < 8 || g.K < 32) return -1;
-    // the operand orders in use: layers (both k-contiguous), input gradients
-    // (the weights as stored), weight gradients (neither)
-    if (a_k && b_k && epi == EPI_BIAS)
+    if (epi == EPI_BIAS)
         launch_shape<true, true, EPI_BIAS>(g, st);
-    else if (a_k && b_k && epi == EPI_BIAS_GELU)
+    else if (epi == EPI_BIAS_GELU)
         launch_shape<true, true, EPI_BIAS_GELU>(g, st);
-    else if (a_k && !b_k && epi == EPI_GELU_GRAD)
-        launch_shape<true, false, EPI_GELU_GRAD>(g, st);
-    else if (!a_k && !b_k && epi == EPI_NONE)
-        launch_shape<false, false, EPI_NONE>(g, st);
     else
         return -1;
     return hipGetLastError() == hipSuccess ? 0 : -1;
@@ -367,44 +419,50 @@ int gemm(const GemmArgs &g, bool a_k, bool b_k, int epi, void *stream)
 
 // Column sums of every layer's dz [M][N] (bias gradients), in two deterministic
 // passes over one job list: block (x, y) sums rows [y * COLSUM_ROWS, (y + 1) *
-// COLSUM_ROWS) of 64 columns of one layer (lanes = columns, four row phases,
+// COLSUM_ROWS) of 256 columns of one layer (lanes = 4 columns, four row phases,
 // each phase's 32 loads in flight together, combined in a fixed order) into
 // part[y][n]; then each column adds its chunks in order.  One launch per pass
 // for all layers: 16 us for what took 8 launches of 8 to 9 us each.
 #define COLSUM_ROWS 128
-__device__ __forceinline__ int colsum_job(const ColsumJobs &jobs, int &x)
+__device__ __forceinline__ int colsum_job(const ColsumJobs &jobs, int cols, int &x)
 {
     int j = 0;
-    while (j < 3 && x >= jobs.n[j] / 64) x -= jobs.n[j++] / 64;
+    while (j < 3 && x >= jobs.n[j] / cols) x -= jobs.n[j++] / cols;
     return j;
 }
 
 __global__ void __launch_bounds__(256) colsum_part_kernel(ColsumJobs jobs, int M)
 {
-    __shared__ float red[4][64];
+    __shared__ f32x4_t red[4][64];
     int x = blockIdx.x;
-    const int j = colsum_job(jobs, x);
+    const int j = colsum_job(jobs, 256, x);
     const int c = threadIdx.x & 63, r = threadIdx.x >> 6;
-    const int n = x * 64 + c, N = jobs.n[j];
+    const int n = x * 256 + 4 * c, N = jobs.n[j];
     const int m0 = blockIdx.y * COLSUM_ROWS;
     const uint16_t *p = jobs.dz[j] + (size_t)(m0 + r) * N + n;
-    uint16_t v[COLSUM_ROWS / 4];
+    uint2 v[COLSUM_ROWS / 4];
 #pragma unroll
     for (int i = 0; i < COLSUM_ROWS / 4; ++i)
-        v[i] = m0 + r + 4 * i < M ? p[(size_t)(4 * i) * N] : 0;
-    float s = 0.0f;
+        v[i] = m0 + r + 4 * i < M ? *(const uint2 *)(p + (size_t)(4 * i) * N) : make_uint2(0u, 0u);
+    f32x4_t s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int i = 0; i < COLSUM_ROWS / 4; ++i) s += bf2f(v[i]);
+    for (int i = 0; i < COLSUM_ROWS / 4; ++i) {
+        s[0] += bf2f((uint16_t)v[i].x);
+        s[1] += bf2f((uint16_t)(v[i].x >> 16));
+        s[2] += bf2f((uint16_t)v[i].y);
+        s[3] += bf2f((uint16_t)(v[i].y >> 16));
+    }
     red[r][c] = s;
     __syncthreads();
     if (r == 0)
-        jobs.part[j][(size_t)blockIdx.y * N + n] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
+        *(f32x4_t *)(jobs.part[j] + (size_t)blockIdx.y * N + n) =
+            ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }
 
 __global__ void __launch_bounds__(64) colsum_final_kernel(ColsumJobs jobs, int chunks)
 {
     int x = blockIdx.x;
-    const int j = colsum_job(jobs, x);
+    const int j = colsum_job(jobs, 64, x);
     const int n = x * 64 + threadIdx.x, N = jobs.n[j];
     float s = 0.0f;
     for (int k0 = 0; k0 < chunks; k0 += 16) {
@@ -919,13 +977,13 @@ int launch_colsum(const ColsumJobs &jobs, int M, void *st)
     const int chunks = colsum_chunks(M);
     int blocks = 0;
     for (int j = 0; j < 4; ++j) {
-        if (jobs.n[j] < 64 || jobs.n[j] % 64) return -1;
-        blocks += jobs.n[j] / 64;
+        if (jobs.n[j] < 256 || jobs.n[j] % 256) return -1;
+        blocks += jobs.n[j] / 256;
     }
     if (M < 1) return -1;
     hipLaunchKernelGGL(colsum_part_kernel, dim3(blocks, chunks), dim3(256), 0, (hipStream_t)st, jobs,
                        M);
-    hipLaunchKernelGGL(colsum_final_kernel, dim3(blocks), dim3(64), 0, (hipStream_t)st, jobs, chunks);
+    hipLaunchKernelGGL(colsum_final_kernel, dim3(4 * blocks), dim3(64), 0, (hipStream_t)st, jobs, chunks);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
