@@ -2190,7 +2190,7 @@ int launch_shot(const ShotArgs &a, int waves_per_wg, void *stream)
 // lanes are points, the opponents are looped over from LDS.
 // ----------------------------------------------------------------------------
 
-// Arrival time (seconds) of staged robot r = (x, y, vx, vy) at (px, py): the
+// Arrival time (A T / 2) of staged robot r = (x, y, vx, vy) at (px, py): the
 // scaled model of robot_time_h with the offset taken directly.
 __device__ __forceinline__ float robot_time_pt(const DevParams &P, float4 r, float px, float py)
 {
@@ -2205,7 +2205,7 @@ __device__ __forceinline__ float robot_time_pt(const DevParams &P, float4 r, flo
     const float Dp = fabsf(ss) + (over ? -del : del);
     const float sg = over ? u : -u;
     const float rh = Dp > P.V2 ? fmaf(Dp, P.inv2V, P.halfV) : hsqrt(Dp);
-    return fmaf(sg, 0.70710678118654752f, rh) * P.invA2;
+    return fmaf(sg, 0.70710678118654752f, rh);
 }
 
 // Entry parameter of the segment from c along (dx, dy) into the rectangle
@@ -2222,10 +2222,60 @@ __device__ __forceinline__ double slab_enter(double cx, double cy, double dx, do
     return fmin(t, 1.0);
 }
 
+// What the points of a zone share: the opponents (bit o) that can be the
+// earliest at some point of the defense area, and those within the marking
+// radius of some point of the zone.
+struct RunZone {
+    uint32_t guard, mark;
+};
+
+// Lanes are opponents.  P and Q lie in the (closed) defense area, so an
+// opponent whose arrival bound over the whole area is past the latest arrival
+// of another one anywhere in it never sets t_P or t_Q.  With D the least and
+// E the greatest distance to the area (widened by 1 mm for the rounding of P
+// and Q), less the radius, both scaled by amax: whatever its velocity the
+// robot needs at least sqrt(D / 2) (D <= vmax^2 / 2) or D / 2vmax + vmax / 4,
+// and at most the time when it first stops moving away at its full speed,
+// |w| / sqrt 2 + R(|w|^2 + E), in the robot stage's units; 2^-12 apart for
+// rounding.  About three of eight opponents are left in random frames.  The
+// marking weight is 0 beyond mark_radius.
+__device__ __forceinline__ RunZone run_zone(const StageLDS &S, const DevParams &P,
+                                            const dpps_run_params &R, const WinDev &W, int ny,
+                                            int n_tm, int n_op)
+{
+    const int l = lane_id();
+    const float4 r = S.rob[n_tm + (l < n_op ? l : 0)];
+    const float x0 = P.goal_x - R.def_depth, x1 = P.goal_x, hw = 0.5f * R.def_width;
+    const float nx = fmaxf(fmaxf(x0 - r.x, r.x - x1), 0.0f), nyd = fmaxf(fabsf(r.y) - hw, 0.0f);
+    const float fx = fmaxf(fabsf(r.x - x0), fabsf(r.x - x1)), fy = fabsf(r.y) + hw;
+    const float D = P.A * fmaxf(hsqrt(fmaf(nx, nx, nyd * nyd)) - 1e-3f - P.R, 0.0f);
+    const float E = P.A * (hsqrt(fmaf(fx, fx, fy * fy)) + 1e-3f);
+    const float w2 = fminf(0.5f * fmaf(r.z, r.z, r.w * r.w), 0.5f * P.V2);
+    const float F = w2 + E;
+    float lb = D <= 0.5f * P.V2 ? hsqrt(0.5f * D) : fmaf(D, P.inv2V, 0.25f * P.V);
+    float ub = fmaf(0.70710678118654752f, hsqrt(w2),
+                    F > P.V2 ? fmaf(F, P.inv2V, P.halfV) : hsqrt(F));
+    lb *= 1.0f - 1.0f / 4096.0f;
+    ub = l < n_op ? ub * (1.0f + 1.0f / 4096.0f) : INFINITY;
+    const float latest = wave_min_dpp(ub);
+    // the zone's rectangle
+    const float zx0 = W.h * ((float)W.i0 - W.halfNx), zx1 = W.h * ((float)(W.i0 + W.nx - 1) - W.halfNx);
+    const float zy0 = W.h * ((float)W.j0 - W.halfNy), zy1 = W.h * ((float)(W.j0 + ny - 1) - W.halfNy);
+    const float mx = fmaxf(fmaxf(zx0 - r.x, r.x - zx1), 0.0f);
+    const float my = fmaxf(fmaxf(zy0 - r.y, r.y - zy1), 0.0f);
+    RunZone z;
+    z.guard = (uint32_t)__ballot(l < n_op && lb <= latest);
+    z.mark = (uint32_t)__ballot(l < n_op && hsqrt(fmaf(mx, mx, my * my)) - 1e-3f <= R.mark_radius);
+    return z;
+}
+
 // The five criteria and the score at (cx, cy); returns -inf inside the
-// defense area (crit untouched).
-__device__ float run_eval(const StageLDS &S, const DevParams &P, const dpps_run_params &R,
-                          double cx, double cy, int n_tm, int n_op, float (&crit)[5])
+// defense area (crit untouched).  ball2: each opponent's squared distance to
+// the ball.
+__device__ __forceinline__ float run_eval(const StageLDS &S, const DevParams &P,
+                                          const dpps_run_params &R, const double *ball2,
+                                          const RunZone &z, double cx, double cy, int n_tm,
+                                          int n_op, float (&crit)[5])
 {
     const double x0d = (double)P.goal_x - (double)R.def_depth;
     const double hwd = 0.5 * (double)R.def_width;
@@ -2247,66 +2297,94 @@ __device__ float run_eval(const StageLDS &S, const DevParams &P, const dpps_run_
     const double tq_ = slab_enter(cx, cy, gxd, dqy, x0d, (double)P.goal_x, -hwd, hwd);
     const float px = (float)(cx + tp_ * gxd), py = (float)(cy + tp_ * dpy);
     const float qx = (float)(cx + tq_ * gxd), qy = (float)(cy + tq_ * dqy);
-    float tP = INFINITY, tQ = INFINITY, mark = 0.0f;
-    for (int o = 0; o < n_op; ++o) {
-        const float4 r = S.rob[n_tm + o];
+    float tP = INFINITY, tQ = INFINITY;
+    for (uint32_t m = z.guard; m; m &= m - 1) {
+        const float4 r = S.rob[n_tm + __builtin_ctz(m)];
         tP = fminf(tP, robot_time_pt(P, r, px, py));
         tQ = fminf(tQ, robot_time_pt(P, r, qx, qy));
-        const double ox = (double)r.x - (double)S.bx, oy = (double)r.y - (double)S.by;
-        const float ex = r.x - fx, ey = r.y - fy;
-        const float wgt = fmaxf(1.0f - sqrtf(fmaf(ex, ex, ey * ey)) / R.mark_radius, 0.0f);
-        mark = (ox * ox + oy * oy < db2) ? fmaxf(mark, wgt) : mark;
     }
-    crit[3] = n_op > 0 ? fminf((tP + tQ) / R.guard_norm, 1.0f) : 1.0f;
+    // the largest marking weight is that of the nearest opponent that counts
+    // (sqrt, division and subtraction are monotone)
+    float near2 = INFINITY;
+    for (uint32_t m = z.mark; m; m &= m - 1) {
+        const int o = __builtin_ctz(m);
+        const float4 r = S.rob[n_tm + o];
+        const float ex = r.x - fx, ey = r.y - fy;
+        near2 = ball2[o] < db2 ? fminf(near2, fmaf(ex, ex, ey * ey)) : near2;
+    }
+    const float mark = fmaxf(1.0f - sqrtf(near2) / R.mark_radius, 0.0f);
+    crit[3] = n_op > 0 ? fminf((tP * P.invA2 + tQ * P.invA2) / R.guard_norm, 1.0f) : 1.0f;
     crit[4] = 1.0f - mark;
     return fmaf(R.w_goal, crit[0],
                 fmaf(R.w_ball, crit[1],
                      fmaf(R.w_angle, crit[2], fmaf(R.w_guard, crit[3], R.w_defense * crit[4]))));
 }
 
+// One workgroup per zone, lanes = points.  Bound by VALU issue (float64
+// geometry, three divisions and the transcendentals of a point, two arrival
+// times per opponent): the opponents that cannot matter in the zone are left
+// out, squared ball distances are formed once, the marking weight once per
+// point from the nearest opponent, and the best point's criteria stay with
+// its lane instead of being computed again.  2048 frames x 4 zones (10.2 M
+// points): 315 -> 187 us.
 __global__ void __launch_bounds__(256) run_kernel(RunArgs a)
 {
     __shared__ StageLDS S;
+    __shared__ double ball2[DPPS_MAX_SIDE];
     __shared__ unsigned long long red[4];
     const DevParams &P = a.P;
     const WinDev W = a.wins[blockIdx.x];
     stage_frame(P, a.frames[W.frame], a.robots, a.variants, W.frame, S);
     __syncthreads();
-    const int n_tm = S.n_tm, n_op = S.n_op;
+    const int n_tm = uni(S.n_tm), n_op = uni(S.n_op);
+    if ((int)threadIdx.x < n_op) {
+        const float4 r = S.rob[n_tm + threadIdx.x];
+        const double ox = (double)r.x - (double)S.bx, oy = (double)r.y - (double)S.by;
+        ball2[threadIdx.x] = ox * ox + oy * oy;
+    }
+    const int ny = W.nx > 0 ? W.npts / W.nx : 0;
+    const RunZone z = run_zone(S, P, a.R, W, ny, n_tm, n_op);
+    __syncthreads();
     unsigned long long best = 0ull;
+    float bc[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
     for (int p = threadIdx.x; p < W.npts; p += blockDim.x) {
-        const int j = p / W.nx, i = p - j * W.nx;
+        const int j = (int)((unsigned)p / (unsigned)W.nx), i = p - j * W.nx;
         const double cx = (double)W.h * ((double)(W.i0 + i) - (double)W.halfNx);
         const double cy = (double)W.h * ((double)(W.j0 + j) - (double)W.halfNy);
         float crit[5];
-        const float sc = run_eval(S, P, a.R, cx, cy, n_tm, n_op, crit);
+        const float sc = run_eval(S, P, a.R, ball2, z, cx, cy, n_tm, n_op, crit);
         if (a.score) a.score[W.out_base + p] = sc;
         if (sc > -INFINITY) {
             const unsigned long long k = ((unsigned long long)ordered_bits(sc) << 32) |
                                          (unsigned long long)(0xFFFFFFFFu - (uint32_t)p);
-            best = k > best ? k : best;
+            if (k > best) {
+                best = k;
+#pragma unroll
+                for (int q = 0; q < 5; ++q) bc[q] = crit[q];
+            }
         }
     }
-    best = wave_max_u64(best);
-    if (lane_id() == 0) red[threadIdx.x >> 6] = best;
+    const unsigned long long wb = wave_max_u64(best);
+    if (lane_id() == 0) red[threadIdx.x >> 6] = wb;
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) best = red[w] > best ? red[w] : best;
+    unsigned long long top = red[0];
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) top = red[w] > top ? red[w] : top;
+    // the lane that holds the best point (keys are unique), or the first
+    // thread when no point is usable
+    if (top != 0ull ? best != top : threadIdx.x != 0) return;
     dpps_run_best r;
     r.found = 0; r.i = -1; r.j = -1; r.reserved = 0;
     r.x = 0.0f; r.y = 0.0f; r.score = -INFINITY;
     r.goal = r.ball = r.angle = r.guard = r.defense = 0.0f;
-    if (best != 0ull) {
-        const int p = (int)(0xFFFFFFFFu - (uint32_t)best);
+    if (top != 0ull) {
+        const int p = (int)(0xFFFFFFFFu - (uint32_t)top);
         const int j = p / W.nx, i = p - j * W.nx;
-        const double cx = (double)W.h * ((double)(W.i0 + i) - (double)W.halfNx);
-        const double cy = (double)W.h * ((double)(W.j0 + j) - (double)W.halfNy);
-        float crit[5];
-        r.score = run_eval(S, P, a.R, cx, cy, n_tm, n_op, crit);
+        r.score = unordered_bits((uint32_t)(top >> 32));
         r.found = 1; r.i = i; r.j = j;
-        r.x = (float)cx; r.y = (float)cy;
-        r.goal = crit[0]; r.ball = crit[1]; r.angle = crit[2]; r.guard = crit[3];
-        r.defense = crit[4];
+        r.x = (float)((double)W.h * ((double)(W.i0 + i) - (double)W.halfNx));
+        r.y = (float)((double)W.h * ((double)(W.j0 + j) - (double)W.halfNy));
+        r.goal = bc[0]; r.ball = bc[1]; r.angle = bc[2]; r.guard = bc[3];
+        r.defense = bc[4];
     }
     a.best[blockIdx.x] = r;
 }
