@@ -155,6 +155,19 @@ DevParams derive(const dpps_params *p)
     return P;
 }
 
+// Whether n floats are all finite (an exponent of all ones anywhere marks inf
+// or NaN); a plain loop over the bits that the compiler vectorises.
+static bool all_finite(const float *x, size_t n)
+{
+    uint32_t bad = 0;
+    for (size_t i = 0; i < n; ++i) {
+        uint32_t u;
+        memcpy(&u, x + i, sizeof u);
+        bad |= (uint32_t)((u & 0x7F800000u) == 0x7F800000u);
+    }
+    return bad == 0;
+}
+
 int build_tables(const dpps_params *p, int32_t n_frames, const dpps_frame *frames,
                  const dpps_robot *robots, const dpps_window *windows,
                  const dpps_variant *variants, int tile_points, HostTables &T)
@@ -172,6 +185,8 @@ int build_tables(const dpps_params *p, int32_t n_frames, const dpps_frame *frame
     T.max_variants = 1;
     T.frames.reserve(n_frames);
     const bool reduced = (p->out_flags & DPPS_OUT_REDUCED) != 0;
+    float last_h = 0.0f;  // the windows' spacings repeat: its lattice is kept
+    int32_t last_Nx = 0, last_Ny = 0;
     for (int32_t f = 0; f < n_frames; ++f) {
         const dpps_frame &F = frames[f];
         if (F.n_team < 1 || F.n_team > DPPS_MAX_SIDE || F.n_opp < 0 || F.n_opp > DPPS_MAX_SIDE)
@@ -203,29 +218,36 @@ int build_tables(const dpps_params *p, int32_t n_frames, const dpps_frame *frame
         D.variant_off = (int32_t)T.variants.size();
         D.ball_x = F.ball_x;
         D.ball_y = F.ball_y;
-        for (int r = 0; r < F.n_team + F.n_opp; ++r) {
-            const dpps_robot &R = robots[F.robot_off + r];
-            if (!isfinite(R.x) || !isfinite(R.y) || !isfinite(R.vx) || !isfinite(R.vy))
-                return fail(DPPS_E_INVALID, "frame %d robot %d: not finite", f, r);
-            T.robots.push_back(R);
-        }
+        const dpps_robot *const rb = robots + F.robot_off;
+        const int nrob = F.n_team + F.n_opp;
+        static_assert(sizeof(dpps_robot) == 4 * sizeof(float), "four floats");
+        if (!all_finite(&rb->x, 4 * (size_t)nrob))
+            for (int r = 0; r < nrob; ++r)
+                if (!all_finite(&rb[r].x, 4))
+                    return fail(DPPS_E_INVALID, "frame %d robot %d: not finite", f, r);
+        T.robots.insert(T.robots.end(), rb, rb + nrob);
         for (int v = 0; v < F.n_variants; ++v) {
             const dpps_variant &Vv = variants[F.variant_off + v];
             if (Vv.type != DPPS_FLAT && Vv.type != DPPS_CHIP)
                 return fail(DPPS_E_INVALID, "frame %d variant %d: bad type %d", f, v, Vv.type);
             if (!finite_pos(Vv.v0) || Vv.v0 > 100.0f)
                 return fail(DPPS_E_INVALID, "frame %d variant %d: v0 must be in (0, 100]", f, v);
-            T.variants.push_back(Vv);
         }
+        T.variants.insert(T.variants.end(), variants + F.variant_off,
+                          variants + F.variant_off + F.n_variants);
         int64_t elem = 0;
         const int32_t tile_begin = (int32_t)T.tiles.size();
         for (int w = 0; w < F.n_windows; ++w) {
             const dpps_window &Wn = windows[F.window_off + w];
-            int32_t Nx, Ny;
-            if (!finite_pos(Wn.h) || lattice_dim(p->field_len, Wn.h, &Nx) ||
-                lattice_dim(p->field_wid, Wn.h, &Ny))
-                return fail(DPPS_E_INVALID, "frame %d window %d: spacing %g does not divide the field",
-                            f, w, (double)Wn.h);
+            if (Wn.h != last_h || last_Nx == 0) {
+                if (!finite_pos(Wn.h) || lattice_dim(p->field_len, Wn.h, &last_Nx) ||
+                    lattice_dim(p->field_wid, Wn.h, &last_Ny))
+                    return fail(DPPS_E_INVALID,
+                                "frame %d window %d: spacing %g does not divide the field", f, w,
+                                (double)Wn.h);
+                last_h = Wn.h;
+            }
+            const int32_t Nx = last_Nx, Ny = last_Ny;
             if (Wn.nx < 0 || Wn.ny < 0 || Wn.i0 < 0 || Wn.j0 < 0 || Wn.i0 + Wn.nx > Nx ||
                 Wn.j0 + Wn.ny > Ny)
                 return fail(DPPS_E_INVALID, "frame %d window %d: outside the %dx%d lattice", f, w,
@@ -998,10 +1020,11 @@ int dpps_running_points(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
         F.variant_off = 0;
     }
     dpps_batch *b = &c->runs;
-    int rc = build_tables(&c->p, n_frames, fr.data(), robots, zones, &one, 256, b->T);
+    // (one workgroup per zone: no tiles)
+    int rc = build_tables(&c->p, n_frames, fr.data(), robots, zones, &one, 0, b->T);
     if (rc) return rc;
     b->n_frames = n_frames;
-    b->tile_points = 256;
+    b->tile_points = 0;
     rc = stage_tables(c, b, st);
     if (rc) return rc;
     RunArgs a;
