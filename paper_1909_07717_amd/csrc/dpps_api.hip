@@ -425,12 +425,23 @@ int batch_upload(dpps_ctx *c, dpps_batch *b)
     return DPPS_OK;
 }
 
+void one_frame(const HostTables &T, OneFrame &o)
+{
+    o.on = 1;
+    o.frame = T.frames[0];
+    if (!T.wins.empty()) o.win = T.wins[0];
+    memcpy(o.robots, T.robots.data(), T.robots.size() * sizeof(dpps_robot));
+    memcpy(o.variants, T.variants.data(), T.variants.size() * sizeof(dpps_variant));
+}
+
 int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t st,
-                     bool timed, const dpps_power_params *power, float *v0_out)
+                     bool timed, const dpps_power_params *power, float *v0_out, bool inl,
+                     dpps_best *best_host)
 {
     if (!out) return fail(DPPS_E_INVALID, "outputs is NULL");
-    LaunchArgs a;
-    memset(&a, 0, sizeof a);
+    SearchLaunch s;
+    memset(&s, 0, sizeof s);
+    LaunchArgs &a = s.a;
     a.P = c->P;
     a.frames = b->d_frames;
     a.robots = b->d_robots;
@@ -439,6 +450,11 @@ int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t s
     a.tiles = b->d_tiles;
     a.n_tiles = (int32_t)b->T.tiles.size();
     a.n_frames = b->n_frames;
+    if (inl) {  // the tables go with the launch, the tiles are implicit
+        one_frame(b->T, s.one);
+        a.tiles_per_frame = a.n_tiles;
+    }
+    a.best_host = best_host;
     a.tile_points = b->tile_points;
     a.max_variants = b->T.max_variants;
     // the search kernel cuts a tile into chunks of 4 points
@@ -474,7 +490,7 @@ int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t s
         e1 = (void *)c->ring1[c->ring_used];
         ++c->ring_used;
     }
-    int rc = launch_search(a, c->waves, grid, (void *)st, e0, e1);
+    int rc = launch_search(s, c->waves, grid, (void *)st, e0, e1);
     c->timed = timed && e1 == (void *)c->ev1;
     if (rc) {
         hipError_t e = hipGetLastError();
@@ -540,7 +556,6 @@ int dpps_create(dpps_ctx **out, const dpps_params *p, int device, void *hip_stre
         c->own_stream = true;
     }
     if (hipEventCreateWithFlags(&c->staged, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->landed, hipEventDisableTiming) != hipSuccess ||
         hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) {
         dpps_destroy(c);
         return fail(DPPS_E_DEVICE, "hipEventCreate failed");
@@ -581,7 +596,6 @@ void dpps_destroy(dpps_ctx *c)
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->pinned_best) (void)hipHostFree(c->pinned_best);
     if (c->staged) (void)hipEventDestroy(c->staged);
-    if (c->landed) (void)hipEventDestroy(c->landed);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
@@ -741,24 +755,26 @@ int stage_batch(dpps_ctx *c, dpps_batch *b, int32_t n_frames, const dpps_frame *
     return stage_tables(c, b, st);
 }
 
-int read_best(dpps_ctx *c, dpps_best *h, const dpps_best *d, int n, hipStream_t st)
+// Room for n best records in the context's pinned landing buffer.
+int best_landing(dpps_ctx *c, int n)
+{
+    if (n <= c->pinned_best_cap) return DPPS_OK;
+    // the previous read has completed (every read waits for its records)
+    if (c->pinned_best) HIP_OK(hipHostFree(c->pinned_best));
+    c->pinned_best = nullptr;
+    c->pinned_best_cap = 0;
+    const int64_t want = n < 64 ? 64 : n;
+    if (hipHostMalloc((void **)&c->pinned_best, (size_t)want * sizeof(dpps_best),
+                      hipHostMallocDefault) != hipSuccess)
+        return fail(DPPS_E_NOMEM, "hipHostMalloc of %lld best records failed", (long long)want);
+    c->pinned_best_cap = want;
+    return DPPS_OK;
+}
+
+int read_best(dpps_ctx *c, dpps_best *h, int n, hipStream_t st)
 {
     if (n <= 0) return DPPS_OK;
-    if (n > c->pinned_best_cap) {
-        // the previous read has completed (every read waits for its copy)
-        if (c->pinned_best) HIP_OK(hipHostFree(c->pinned_best));
-        c->pinned_best = nullptr;
-        c->pinned_best_cap = 0;
-        const int64_t want = n < 64 ? 64 : n;
-        if (hipHostMalloc((void **)&c->pinned_best, (size_t)want * sizeof(dpps_best),
-                          hipHostMallocDefault) != hipSuccess)
-            return fail(DPPS_E_NOMEM, "hipHostMalloc of %lld best records failed", (long long)want);
-        c->pinned_best_cap = want;
-    }
-    HIP_OK(hipMemcpyAsync(c->pinned_best, d, (size_t)n * sizeof(dpps_best), hipMemcpyDeviceToHost,
-                          st));
-    HIP_OK(hipEventRecord(c->landed, st));
-    const hipError_t e = hipEventSynchronize(c->landed);
+    const hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(DPPS_E_DEVICE, "waiting for the best records: %s", hipGetErrorString(e));
     memcpy(h, c->pinned_best, (size_t)n * sizeof(dpps_best));
     return DPPS_OK;
@@ -1050,19 +1066,28 @@ int dpps_search(dpps_ctx *c, const dpps_frame *frame, const dpps_robot *robots,
     dpps_outputs o = *out;
     o.best = nullptr;
     HIP_OK(hipSetDevice(c->device));
-    int rc = stage_batch(c, &c->scratch, 1, frame, robots, windows, variants, c->stream);
+    int rc = best_landing(c, 1);
+    if (rc) return rc;
+    // a frame with one window goes with the launch itself; the best record is
+    // written to host memory by the finalize kernel: no copies on the way
+    dpps_batch *b = &c->scratch;
+    const int tp = request_tile(c, 1, frame, windows);
+    rc = build_tables(&c->p, 1, frame, robots, windows, variants, tp, b->T);
+    if (rc) return rc;
+    b->n_frames = 1;
+    b->tile_points = tp;
+    const bool inl = b->T.wins.size() == 1;
+    if (inl) {
+        graph_drop(b);
+        rc = batch_reserve(c, b, table_layout(b->T));
+    } else {
+        rc = stage_tables(c, b, c->stream);
+    }
     if (rc) return rc;
     // no timing events around the kernel of a single synchronous search
-    rc = run_batch(c, &c->scratch, &o, c->stream, false);
+    rc = run_batch(c, b, &o, c->stream, false, nullptr, nullptr, inl, c->pinned_best);
     if (rc) return rc;
-    // a direct copy and a stream synchronisation: over 2 x 3000 frames this
-    // gave a shorter tail (p99 0.245 vs 0.305 ms for the full frame) than the
-    // pinned read-back that the surrogate path uses (which there gives the
-    // lower median)
-    HIP_OK(hipMemcpyAsync(h_best, c->scratch.d_best, sizeof(dpps_best), hipMemcpyDeviceToHost,
-                          c->stream));
-    HIP_OK(hipStreamSynchronize(c->stream));
-    return DPPS_OK;
+    return read_best(c, h_best, 1, c->stream);
 }
 
 int dpps_batch_create(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,

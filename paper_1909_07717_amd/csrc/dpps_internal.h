@@ -149,6 +149,31 @@ struct LaunchArgs {
     // own entry of `frames` is copied)
     int32_t fb_on;
     FallbackArgs fb;
+    // copies in pinned host memory (may be NULL): the best records by frame,
+    // and the number of frames of a launch that reads it on the device
+    dpps_best *best_host;
+    int32_t *count_host;
+};
+
+// The tables of a request of one frame and one window, carried by the launch
+// itself (on != 0) instead of device memory: no copy goes ahead of it, and the
+// kernel that reduces the frame writes its record to pinned host memory, so
+// none follows.  What bounds a small frame is this chain of copies and
+// launches: 57 -> 42 us for the whole call of 6 + 6 robots on 61 x 46 points,
+// 159 -> 130 us for the 0.05 m frame.  Several windows would need a list of
+// unknown length: those requests are staged as before.
+struct OneFrame {
+    int32_t on, pad;
+    FrameDev frame;
+    WinDev win;
+    dpps_robot robots[2 * DPPS_MAX_SIDE];
+    dpps_variant variants[DPPS_MAX_VARIANTS];
+};
+
+// Arguments of the search and finalize kernels.
+struct SearchLaunch {
+    LaunchArgs a;
+    OneFrame one;
 };
 
 // Best pass of one tile of the direction x variant search.
@@ -210,7 +235,7 @@ struct RunArgs {
 
 // host-side launchers (dpps_kernels.hip)
 // ev_start / ev_stop (hipEvent_t or NULL) bracket the search kernel only.
-int launch_search(const LaunchArgs &a, int waves_per_wg, int grid, void *stream, void *ev_start,
+int launch_search(const SearchLaunch &s, int waves_per_wg, int grid, void *stream, void *ev_start,
                   void *ev_stop);
 // Zero n 32-bit words of device memory on `stream` (a kernel, no memset).
 int launch_zero_words(uint32_t *p, int n, void *stream);

@@ -914,7 +914,7 @@ __device__ __forceinline__ void pair_crossings(const StageLDS &S, const float4 *
         To[q] = INFINITY;
     }
     {
-    const RobotK rk(fresh_args<LaunchArgs>().P);
+    const RobotK rk(fresh_args<SearchLaunch>().a.P);
     const bool split = n_tm + n_op <= SPLIT_ROB;
     // arrival limits of the lane's quarter of the path and the other of its
     // row; with POWER the team's minimum at the last sample is the
@@ -932,7 +932,7 @@ __device__ __forceinline__ void pair_crossings(const StageLDS &S, const float4 *
         robot_stage<KPH, true, HALF_WAVE>(pr, rk, n_tm, n_op, split, lim, limx, fs, LA, To);
     }
     }
-    const LaunchArgs &a = fresh_args<LaunchArgs>();
+    const LaunchArgs &a = fresh_args<SearchLaunch>().a;
     const float invA2 = a.P.invA2;
     float sk[KPH];
 #pragma unroll
@@ -947,7 +947,7 @@ __device__ __forceinline__ void pair_crossings(const StageLDS &S, const float4 *
     }
     kt[0] = kt[1] = ko[0] = ko[1] = K;
     if (POWER || uni(S.has_flat)) {
-        const DevParams &P = fresh_args<LaunchArgs>().P;
+        const DevParams &P = fresh_args<SearchLaunch>().a.P;
         float vc[KPH];
         const SampleTerms<KPH, false, true> st(P, sk);
         wave_lds_sync();  // the previous searches are done with the rows
@@ -966,7 +966,7 @@ __device__ __forceinline__ void pair_crossings(const StageLDS &S, const float4 *
         }
     }
     if (!POWER && uni(S.has_chip)) {
-        const DevParams &P = fresh_args<LaunchArgs>().P;
+        const DevParams &P = fresh_args<SearchLaunch>().a.P;
         float vc[KPH], vair[KPH];
 #pragma unroll
         for (int q = 0; q < KPH; ++q) vair[q] = hsqrt(sk[q] * P.lam1_inv);
@@ -1021,11 +1021,12 @@ __device__ __forceinline__ TileDev tile_at(const LaunchArgs &a, int t)
 }
 
 // Word l of a window's record in lane l.
-__device__ __forceinline__ int window_words(const LaunchArgs &a, int win)
+__device__ __forceinline__ int window_words(const LaunchArgs &a, bool inl, int win)
 {
     static_assert(sizeof(WinDev) == 48, "12 words");
     const int l = lane_id();
-    return l < 12 ? ((const int *)(a.wins + win))[l] : 0;
+    const WinDev *const w = inl ? &fresh_args<SearchLaunch>().one.win : a.wins + win;
+    return l < 12 ? ((const int *)w)[l] : 0;
 }
 
 // Bound by VALU issue.  One point per half of a wave rather than per wave: the
@@ -1042,8 +1043,9 @@ __device__ __forceinline__ int window_words(const LaunchArgs &a, int win)
 // frame, 16.2 -> 19.0 us, and K >= 192 does not fit).  POWER: one flat pass
 // per point at the point's own passing power (Eq. 1-2).
 template <int KPH, bool POWER>
-__global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(LaunchArgs args)
+__global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLaunch launch)
 {
+    const LaunchArgs &args = launch.a;
     __shared__ StageLDS S;
     __shared__ OutLDS O;
     // dynamic: each wave's running maxima (two rows of K for each half), its
@@ -1090,22 +1092,25 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(LaunchArg
     float btt = INFINITY, bto = INFINITY, bv0 = 0.0f;
     // the next own tile and its window's record (word i in lane i) are loaded
     // while the current tile is searched
+    const bool inl = launch.one.on != 0;  // the tables come with the launch
     TileDev ta = {0, 0}, tb = {0, 0};
     int words = 0;
     if (n_own > 0) {
         ta = tile_at(args, first);
         if (n_own > 1) tb = tile_at(args, first + stride);
-        words = window_words(args, ta.win);
+        words = window_words(args, inl, ta.win);
     }
     if (args.n_frames == 1 && !args.n_frames_dev) {  // known without the tile: one round trip less
-        stage_frame(args.P, args.frames[0], args.robots, args.variants, 0, S);
+        const OneFrame &o = fresh_args<SearchLaunch>().one;
+        stage_frame(args.P, inl ? o.frame : args.frames[0], inl ? o.robots : args.robots,
+                    inl ? o.variants : args.variants, 0, S);
         cur_frame = 0;
     }
     int it = 0, pull = 0, pull_end = 0;
     while (true) {
         // the previous tile (its staged results and records) is finished
         __syncthreads();
-        const LaunchArgs &a = fresh_args<LaunchArgs>();
+        const LaunchArgs &a = fresh_args<SearchLaunch>().a;
         int t, at, cw;
         if (it < n_own) {
             t = first + it * stride;
@@ -1114,7 +1119,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(LaunchArg
             ++it;
             if (it < n_own) {
                 ta = tb;
-                words = window_words(a, ta.win);
+                words = window_words(a, inl, ta.win);
                 if (it + 1 < n_own) tb = tile_at(a, first + (it + 1) * stride);
             }
         } else {
@@ -1133,7 +1138,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(LaunchArg
             if (t >= n_tiles) break;
             const TileDev tile = tile_at(a, t);
             at = tile.at;
-            cw = window_words(a, tile.win);
+            cw = window_words(a, inl, tile.win);
         }
         const int tk = uni(at);
         WinDev W;  // the same for every lane: scalar
@@ -1192,7 +1197,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(LaunchArg
             const float bx = unif(S.bx), by = unif(S.by);
             const int n_tm = uni(S.n_tm), n_op = uni(S.n_op);
             float4 *const pr = PR + (w * 2 + h) * PR_ENTRIES;
-            const float LA = path_frame(S, fresh_args<LaunchArgs>().P, pr, n_tm + n_op, n_tm, cx64, cy64, (double)bx,
+            const float LA = path_frame(S, fresh_args<SearchLaunch>().a.P, pr, n_tm + n_op, n_tm, cx64, cy64, (double)bx,
                                         (double)by, hl);
             const float ex = cx - bx, ey = cy - by;
             const float d = hsqrt(fmaf(ex, ex, ey * ey));
@@ -1202,7 +1207,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(LaunchArg
             double v0 = 0.0;
             pair_crossings<KPH, POWER>(S, pr, PMX + (w * 2 + h) * HROWS, d, LA, kt, ko, d64, v0);
             // finish: the lanes of a half are its point's variants
-            const LaunchArgs &a = fresh_args<LaunchArgs>();
+            const LaunchArgs &a = fresh_args<SearchLaunch>().a;
             const DevParams &P = a.P;
             float tt[2], to[2], mc[2];
             bool feas[2];
@@ -1294,7 +1299,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(LaunchArg
             // one variant's piece of one chunk per thread: four scores in one
             // store and their flags in another (the last chunk of the window
             // may be short)
-            const LaunchArgs &a = fresh_args<LaunchArgs>();
+            const LaunchArgs &a = fresh_args<SearchLaunch>().a;
             const float rn = hrcp((float)nch);
             for (int e = threadIdx.x; e < n_var * nch; e += blockDim.x) {
                 const int v = (int)(((float)e + 0.5f) * rn), c = e - v * nch;
@@ -1325,15 +1330,21 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(LaunchArg
 
 // One workgroup per frame: reduce the frame's tile records to its best pass;
 // block 0 also rearms the persistent work counter for the next launch.
-__global__ void __launch_bounds__(256) finalize_kernel(LaunchArgs a)
+__global__ void __launch_bounds__(256) finalize_kernel(SearchLaunch launch)
 {
+    const LaunchArgs &a = launch.a;
+    const bool inl = launch.one.on != 0;
+    const OneFrame &one = fresh_args<SearchLaunch>().one;
+    const WinDev *const wins = inl ? &one.win : a.wins;
+    const dpps_variant *const variants = inl ? one.variants : a.variants;
     __shared__ TileRec red[256 / 64];
     __shared__ int s_wi;
     const int f = blockIdx.x;
     const int tid = threadIdx.x;
     if (f == 0 && tid < 8 && a.counter) a.counter[tid] = 0u;  // the search's 8 counters
+    if (f == 0 && tid == 0 && a.count_host) *a.count_host = *a.n_frames_dev;
     if (a.n_frames_dev && f >= *a.n_frames_dev) return;
-    const FrameDev F = a.frames[f];
+    const FrameDev F = inl ? one.frame : a.frames[f];
     // the frame's tile records, or one record per workgroup of a one-frame
     // launch
     const int rc = a.wg_records ? a.wg_records : F.tile_count;
@@ -1371,7 +1382,7 @@ __global__ void __launch_bounds__(256) finalize_kernel(LaunchArgs a)
     const uint32_t lin = 0xFFFFFFFFu - (uint32_t)bestr.key;
     if (bestr.key != 0ull)
         for (int k = tid; k < F.n_windows; k += blockDim.x)
-            if ((uint32_t)a.wins[F.win_off + k].elem_base <= lin) atomicMax(&s_wi, k);
+            if ((uint32_t)wins[F.win_off + k].elem_base <= lin) atomicMax(&s_wi, k);
     __syncthreads();
     if (tid != 0) return;
     dpps_best b;
@@ -1381,14 +1392,14 @@ __global__ void __launch_bounds__(256) finalize_kernel(LaunchArgs a)
     b.pad = 0;
     if (bestr.key != 0ull) {
         const int wi = s_wi;
-        const WinDev W = a.wins[F.win_off + wi];
+        const WinDev W = wins[F.win_off + wi];
         const uint32_t rel = lin - (uint32_t)W.elem_base;
         const int v = (int)(rel / (uint32_t)W.npts);
         const int p = (int)(rel - (uint32_t)v * (uint32_t)W.npts);
         const int j = p / W.nx, i = p - j * W.nx;
         const float mi = (float)(W.i0 + i) - W.halfNx;
         const float mj = (float)(W.j0 + j) - W.halfNy;
-        const dpps_variant var = a.variants[F.variant_off + v];
+        const dpps_variant var = variants[F.variant_off + v];
         // the per-point power search passes one flat kick at the point's power
         const int ptype = a.power ? DPPS_FLAT : var.type;
         const float pv0 = a.power ? bestr.v0 : var.v0;
@@ -1409,7 +1420,9 @@ __global__ void __launch_bounds__(256) finalize_kernel(LaunchArgs a)
         b.t_opp = bestr.t_opp;
         b.t_ball = (float)ball_time64(c, sqrt(ex64 * ex64 + ey64 * ey64));
     }
-    a.best[a.best_map ? a.best_map[f] : f] = b;
+    const int slot_b = a.best_map ? a.best_map[f] : f;
+    a.best[slot_b] = b;
+    if (a.best_host) a.best_host[slot_b] = b;
     if (a.fb_on && (!b.found || b.score < a.fb.below)) {
         // this frame takes the exact fallback: one window over the whole lattice
         const int slot = atomicAdd(a.fb.count, 1);
@@ -1438,23 +1451,24 @@ __global__ void __launch_bounds__(256) finalize_kernel(LaunchArgs a)
 
 
 template <int KPL>
-static int launch_kpl(const LaunchArgs &a, int waves_per_wg, int grid, hipStream_t st,
+static int launch_kpl(const SearchLaunch &s, int waves_per_wg, int grid, hipStream_t st,
                       hipEvent_t e0, hipEvent_t e1)
 {
+    const LaunchArgs &a = s.a;
     if (e0) (void)hipEventRecord(e0, st);
     if (a.n_tiles > 0 && grid > 0) {
         const size_t lds = search_lds_bytes(KPL * 64, waves_per_wg, a.tile_points,
                                             a.max_variants);
         if (a.power)
             hipLaunchKernelGGL((search_kernel<2 * KPL, true>), dim3(grid), dim3(64 * waves_per_wg),
-                               lds, st, a);
+                               lds, st, s);
         else
             hipLaunchKernelGGL((search_kernel<2 * KPL, false>), dim3(grid), dim3(64 * waves_per_wg),
-                               lds, st, a);
+                               lds, st, s);
     }
     if (e1) (void)hipEventRecord(e1, st);
     if (a.n_frames > 0)
-        hipLaunchKernelGGL(finalize_kernel, dim3(a.n_frames), dim3(256), 0, st, a);
+        hipLaunchKernelGGL(finalize_kernel, dim3(a.n_frames), dim3(256), 0, st, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -2412,16 +2426,16 @@ int launch_zero_words(uint32_t *p, int n, void *stream)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_search(const LaunchArgs &a, int waves_per_wg, int grid, void *stream, void *ev_start,
+int launch_search(const SearchLaunch &s, int waves_per_wg, int grid, void *stream, void *ev_start,
                   void *ev_stop)
 {
     hipStream_t st = (hipStream_t)stream;
     hipEvent_t e0 = (hipEvent_t)ev_start, e1 = (hipEvent_t)ev_stop;
-    switch (a.P.K / 64) {
-    case 1: return launch_kpl<1>(a, waves_per_wg, grid, st, e0, e1);
-    case 2: return launch_kpl<2>(a, waves_per_wg, grid, st, e0, e1);
-    case 3: return launch_kpl<3>(a, waves_per_wg, grid, st, e0, e1);
-    case 4: return launch_kpl<4>(a, waves_per_wg, grid, st, e0, e1);
+    switch (s.a.P.K / 64) {
+    case 1: return launch_kpl<1>(s, waves_per_wg, grid, st, e0, e1);
+    case 2: return launch_kpl<2>(s, waves_per_wg, grid, st, e0, e1);
+    case 3: return launch_kpl<3>(s, waves_per_wg, grid, st, e0, e1);
+    case 4: return launch_kpl<4>(s, waves_per_wg, grid, st, e0, e1);
     default: return -2;
     }
 }

@@ -133,17 +133,22 @@ static int params_xfer(dpps_mlp *m, float *const *dw, float *const *db, float *h
 // every padded row and uses the tiled GEMM.
 constexpr int SMALL_ROWS = 64;
 
+// one (may be NULL): the batch's single frame, not yet in device memory (the
+// feature kernel puts it there).
 // out (may be NULL): the caller's copy of the predicted maps, ld_out floats a row.
 static int forward(dpps_mlp *m, const dpps_batch *bt, hipStream_t st, bool training,
-                   float *out = nullptr, int64_t ld_out = 0)
+                   float *out = nullptr, int64_t ld_out = 0, const OneFrame *one = nullptr)
 {
     const int nf = bt->n_frames, R = rows_pad(nf);
     const bool small = !training && nf >= 1 && nf <= SMALL_ROWS;
     if (nf > m->rows_cap) return fail(DPPS_E_INVALID, "batch of %d frames exceeds the network's %d",
                                       nf, m->rows_cap);
     const dpps_params &p = m->ctx->p;
-    if (launch_featurize(bt->d_frames, bt->d_robots, nf, R, IN_PAD, 2.0f / p.field_len,
-                         2.0f / p.field_wid, 1.0f / p.vmax, m->x0, (void *)st))
+    // few frames: only the rows that the few-row GEMM reads
+    const int xr = small ? (nf + 15) / 16 * 16 : R;
+    if (launch_featurize(bt->d_frames, bt->d_robots, bt->d_variants, nf, xr, IN_PAD,
+                         2.0f / p.field_len, 2.0f / p.field_wid, 1.0f / p.vmax, m->x0, one,
+                         (void *)st))
         return fail(DPPS_E_DEVICE, "featurize launch failed");
     const uint16_t *in = m->x0;
     for (int l = 0; l < NL; ++l) {
@@ -527,8 +532,9 @@ int dpps_mlp_features(dpps_mlp *m, dpps_batch *b, uint16_t *d_x, void *hip_strea
     const int nf = b->n_frames;
     if (nf > m->rows_cap) return fail(DPPS_E_INVALID, "batch too large");
     const dpps_params &p = m->ctx->p;
-    if (launch_featurize(b->d_frames, b->d_robots, nf, rows_pad(nf), IN_PAD, 2.0f / p.field_len,
-                         2.0f / p.field_wid, 1.0f / p.vmax, m->x0, (void *)st))
+    if (launch_featurize(b->d_frames, b->d_robots, b->d_variants, nf, rows_pad(nf), IN_PAD,
+                         2.0f / p.field_len, 2.0f / p.field_wid, 1.0f / p.vmax, m->x0, nullptr,
+                         (void *)st))
         return fail(DPPS_E_DEVICE, "featurize launch failed");
     if (nf > 0)
         HIP_OK(hipMemcpy2DAsync(d_x, IN * 2, m->x0, IN_PAD * 2, IN * 2, nf, hipMemcpyDeviceToDevice, st));
@@ -551,10 +557,11 @@ int dpps_mlp_topk(dpps_mlp *m, int32_t n_frames, int32_t k, int32_t *d_cells, vo
 // Forward pass, top-k cells, re-score tables and the exact re-score of the
 // proposed windows (kernel launches only), best records into res.
 static int propose(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dpps_best *res,
-                   hipStream_t st, bool fallback = false, float fallback_below = -INFINITY)
+                   hipStream_t st, bool fallback, float fallback_below, dpps_best *best_host,
+                   const OneFrame *one)
 {
     const int nf = b->n_frames;
-    int rc = forward(m, b, st, false);
+    int rc = forward(m, b, st, false, nullptr, 0, one);
     if (rc) return rc;
     // top-k cells and, in the same kernel, their re-score tables
     RescoreTables rt;
@@ -570,8 +577,10 @@ static int propose(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dpps_best
     if (launch_topk(m->y, OUT_PAD, nf, OUT, k, m->cells, &rt, (void *)st))
         return fail(DPPS_E_DEVICE, "top-k launch failed");
     // exact re-score of the proposed windows: one 16-point tile per window
-    LaunchArgs a;
-    memset(&a, 0, sizeof a);
+    SearchLaunch s;
+    memset(&s, 0, sizeof s);
+    LaunchArgs &a = s.a;
+    a.best_host = best_host;
     a.P = c->P;
     a.P.out_flags = 0;
     a.frames = m->rf;
@@ -607,7 +616,7 @@ static int propose(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dpps_best
     int per_cu = search_occupancy(c->p.n_samples, wv, a.tile_points, a.max_variants);
     int64_t cap = (int64_t)c->n_cu * per_cu;
     int grid = (int)(a.n_tiles < cap ? a.n_tiles : cap);
-    if (launch_search(a, wv, grid, (void *)st, nullptr, nullptr))
+    if (launch_search(s, wv, grid, (void *)st, nullptr, nullptr))
         return fail(DPPS_E_DEVICE, "re-score launch failed");
     return DPPS_OK;
 }
@@ -616,7 +625,7 @@ static int propose(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dpps_best
 // host memory and the call returns after the stream has finished them.
 static int surrogate_core(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dpps_best *d_best,
                           int fallback, float fallback_below, int32_t *n_fallback,
-                          dpps_best *h_best, void *hip_stream)
+                          dpps_best *h_best, const OneFrame *one, void *hip_stream)
 {
     if (!c || !m || !b || !d_best) return fail(DPPS_E_INVALID, "NULL argument");
     if (fallback_below != fallback_below) return fail(DPPS_E_INVALID, "fallback_below is NaN");
@@ -627,16 +636,23 @@ static int surrogate_core(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dp
     const int nf = b->n_frames;
     if (n_fallback) *n_fallback = 0;
     if (nf == 0) return DPPS_OK;
-    int rc = propose(c, m, b, k, d_best, st, fallback != 0, fallback_below);
+    // records for the host are written to pinned memory by the finalize kernels
+    int rc = h_best ? best_landing(c, nf) : DPPS_OK;
     if (rc) return rc;
-    if (!fallback) return h_best ? read_best(c, h_best, d_best, nf, st) : DPPS_OK;
+    dpps_best *const best_host = h_best ? c->pinned_best : nullptr;
+    rc = propose(c, m, b, k, d_best, st, fallback != 0, fallback_below, best_host, one);
+    if (rc) return rc;
+    if (!fallback) return h_best ? read_best(c, h_best, nf, st) : DPPS_OK;
     // frames whose proposals are all infeasible (or score below the
     // threshold), listed by the re-score's finalize: the exact search of the
     // full fine lattice with the frame's own variants, its records placed on
     // the device in stream order (no host round trip)
     const int tpf = (m->fine_nx * m->fine_ny + FB_TILE - 1) / FB_TILE;
-    LaunchArgs a;
-    memset(&a, 0, sizeof a);
+    SearchLaunch s;
+    memset(&s, 0, sizeof s);
+    LaunchArgs &a = s.a;
+    a.best_host = best_host;
+    a.count_host = n_fallback ? m->h_count : nullptr;
     a.P = c->P;
     a.P.out_flags = 0;
     a.frames = m->ff;
@@ -658,12 +674,10 @@ static int surrogate_core(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dp
     const int per_cu = search_occupancy(c->p.n_samples, c->waves, a.tile_points, a.max_variants);
     const int64_t cap = (int64_t)c->n_cu * per_cu;
     const int grid = (int)((int64_t)a.n_tiles < cap ? a.n_tiles : cap);
-    if (launch_search(a, c->waves, grid, (void *)st, nullptr, nullptr))
+    if (launch_search(s, c->waves, grid, (void *)st, nullptr, nullptr))
         return fail(DPPS_E_DEVICE, "fallback search launch failed");
-    if (n_fallback)
-        HIP_OK(hipMemcpyAsync(m->h_count, m->fcount, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     if (h_best) {
-        rc = read_best(c, h_best, d_best, nf, st);
+        rc = read_best(c, h_best, nf, st);
         if (rc) return rc;
     } else if (n_fallback) {
         HIP_OK(hipStreamSynchronize(st));
@@ -678,7 +692,7 @@ int dpps_surrogate_search(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dp
                           int fallback, float fallback_below, int32_t *n_fallback,
                           void *hip_stream)
 {
-    return surrogate_core(c, m, b, k, d_best, fallback, fallback_below, n_fallback, nullptr,
+    return surrogate_core(c, m, b, k, d_best, fallback, fallback_below, n_fallback, nullptr, nullptr,
                           hip_stream);
 }
 
@@ -698,10 +712,19 @@ int dpps_surrogate_search_frames(dpps_ctx *c, dpps_mlp *m, int32_t n_frames,
     if (rc) return rc;
     b->n_frames = n_frames;
     b->tile_points = c->tile_points;
-    rc = stage_tables(c, b, st);
+    // one frame goes with the feature kernel's launch instead of a copy
+    OneFrame one;
+    if (n_frames == 1) {
+        memset(&one, 0, sizeof one);
+        one_frame(b->T, one);
+        graph_drop(b);
+        rc = batch_reserve(c, b, table_layout(b->T));
+    } else {
+        rc = stage_tables(c, b, st);
+    }
     if (rc) return rc;
     return surrogate_core(c, m, b, k, d_best, fallback, fallback_below, n_fallback, h_best,
-                          hip_stream);
+                          n_frames == 1 ? &one : nullptr, hip_stream);
 }
 
 }  // extern "C"

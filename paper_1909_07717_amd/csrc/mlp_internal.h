@@ -82,8 +82,10 @@ struct ParamJobs {
 };
 int launch_params(ParamJobs jobs, float *host, bool to_dev, void *st);
 int launch_cast(const float *w, int64_t n, uint16_t *wb, void *st);
-int launch_featurize(const FrameDev *frames, const dpps_robot *robots, int n_frames, int rows_pad,
-                     int in_pad, float inv_hl, float inv_hw, float inv_v, uint16_t *x, void *st);
+// one (may be NULL): the only frame, written to frames, robots and variants.
+int launch_featurize(FrameDev *frames, dpps_robot *robots, dpps_variant *variants, int n_frames,
+                     int rows_pad, int in_pad, float inv_hl, float inv_hw, float inv_v, uint16_t *x,
+                     const OneFrame *one, void *st);
 // Re-score tables written by the top-k kernel: per frame f, its copy
 // frames[f] (n_windows = tile_count = k), k windows and k tiles.
 struct RescoreTables {

@@ -680,6 +680,16 @@ __global__ void cast_kernel(const float *__restrict__ w, int64_t n, uint16_t *__
     if (i < n) wb[i] = f2bf(w[i]);
 }
 
+struct FeatureArgs {
+    FrameDev *frames;
+    dpps_robot *robots;
+    dpps_variant *variants;
+    uint16_t *x;
+    int n_frames, in_pad;
+    float inv_hl, inv_hw, inv_v;
+    OneFrame one;
+};
+
 // Feature vector of a frame (one wave per row): teammates with the passer
 // first and the rest by distance to the ball, zero-padded to 8 slots; then
 // the opponents by distance to the ball in slots 8-15; then the ball.
@@ -688,20 +698,29 @@ __global__ void cast_kernel(const float *__restrict__ w, int64_t n, uint16_t *__
 // Lanes 0-15 rank the team, lanes 16-31 the opponents (ties to the lower
 // robot index); the slot table goes through LDS; each lane then writes
 // columns l and l + 64 of the row.
-__global__ void __launch_bounds__(64) featurize_kernel(const FrameDev *__restrict__ frames,
-                                                       const dpps_robot *__restrict__ robots,
-                                                       int n_frames, int rows_pad, int in_pad,
-                                                       float inv_hl, float inv_hw, float inv_v,
-                                                       uint16_t *__restrict__ x)
+__global__ void __launch_bounds__(64) featurize_kernel(FeatureArgs args)
 {
+    // the launch-carried frame is read from the kernel's arguments in memory
+    // (an indexed by-value struct would be copied to scratch)
+    typedef const __attribute__((address_space(4))) FeatureArgs *KernArgs;
+    const FeatureArgs &A = *(const FeatureArgs *)(KernArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    const bool inl = args.one.on != 0;
+    const int n_frames = args.n_frames, in_pad = args.in_pad;
+    const float inv_hl = args.inv_hl, inv_hw = args.inv_hw, inv_v = args.inv_v;
+    const FrameDev *const frames = inl ? &A.one.frame : args.frames;
+    const dpps_robot *const robots = inl ? A.one.robots : args.robots;
     __shared__ int slot_robot[16];
     const int f = blockIdx.x;
     const int l = threadIdx.x;
-    if (f >= rows_pad) return;
-    uint16_t *row = x + (size_t)f * in_pad;
+    uint16_t *row = args.x + (size_t)f * in_pad;
     const bool real = f < n_frames;
     FrameDev F;
     if (real) F = frames[f];
+    if (inl && real) {  // one frame: its tables for the kernels that follow
+        if (l < F.n_team + F.n_opp) args.robots[l] = robots[l];
+        if (l < F.n_variants) args.variants[l] = A.one.variants[l];
+        if (l == 0) args.frames[0] = F;
+    }
     if (l < 16) slot_robot[l] = -1;
     __syncthreads();
     if (real) {
@@ -1042,12 +1061,24 @@ int launch_cast(const float *w, int64_t n, uint16_t *wb, void *st)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_featurize(const FrameDev *frames, const dpps_robot *robots, int n_frames, int rows_pad,
-                     int in_pad, float inv_hl, float inv_hw, float inv_v, uint16_t *x, void *st)
+int launch_featurize(FrameDev *frames, dpps_robot *robots, dpps_variant *variants, int n_frames,
+                     int rows_pad, int in_pad, float inv_hl, float inv_hw, float inv_v, uint16_t *x,
+                     const OneFrame *one, void *st)
 {
     if (rows_pad == 0) return 0;
-    hipLaunchKernelGGL(featurize_kernel, dim3(rows_pad), dim3(64), 0, (hipStream_t)st, frames,
-                       robots, n_frames, rows_pad, in_pad, inv_hl, inv_hw, inv_v, x);
+    FeatureArgs a;
+    memset(&a, 0, sizeof a);
+    a.frames = frames;
+    a.robots = robots;
+    a.variants = variants;
+    a.n_frames = n_frames;
+    a.in_pad = in_pad;
+    a.inv_hl = inv_hl;
+    a.inv_hw = inv_hw;
+    a.inv_v = inv_v;
+    a.x = x;
+    if (one) a.one = *one;
+    hipLaunchKernelGGL(featurize_kernel, dim3(rows_pad), dim3(64), 0, (hipStream_t)st, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

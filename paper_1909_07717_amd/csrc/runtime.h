@@ -101,9 +101,8 @@ struct dpps_ctx {
     void *pinned = nullptr;
     size_t pinned_cap = 0;
     hipEvent_t staged = nullptr;   // pinned staging consumed
-    dpps_best *pinned_best = nullptr;  // pinned landing buffer of best records read back
+    dpps_best *pinned_best = nullptr;  // best records written by the kernels
     int64_t pinned_best_cap = 0;
-    hipEvent_t landed = nullptr;   // best records in pinned_best
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool timed = false;
     uint64_t budget_used = 0;
@@ -132,7 +131,10 @@ void pack_tables(const dpps::HostTables &T, const Layout &L, char *dst);
 int batch_reserve(dpps_ctx *c, dpps_batch *b, const Layout &L);
 int batch_upload(dpps_ctx *c, dpps_batch *b);
 int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t st, bool timed,
-              const dpps_power_params *power = nullptr, float *v0_out = nullptr);
+              const dpps_power_params *power = nullptr, float *v0_out = nullptr, bool inl = false,
+              dpps_best *best_host = nullptr);
+// The launch-carried tables of a request of one frame (and at most one window).
+void one_frame(const dpps::HostTables &T, dpps::OneFrame &o);
 int stage_batch(dpps_ctx *c, dpps_batch *b, int32_t n_frames, const dpps_frame *frames,
                 const dpps_robot *robots, const dpps_window *windows,
                 const dpps_variant *variants, hipStream_t st);
@@ -140,7 +142,7 @@ int stage_tables(dpps_ctx *c, dpps_batch *b, hipStream_t st);
 // Set up the fixed-array search on the context's (current) device.
 int noalloc_setup(dpps_ctx *c);
 void noalloc_release(dpps_ctx *c);
-// Copy n best records from device memory to h (host) after the work queued
-// on st, through the context's pinned buffer (no staging of pageable memory),
-// waiting on an event recorded after the copy.
-int read_best(dpps_ctx *c, dpps_best *h, const dpps_best *d, int n, hipStream_t st);
+// Best records that the kernels write to the context's pinned landing buffer:
+// room for n of them, and their copy to h after the work queued on st.
+int best_landing(dpps_ctx *c, int n);
+int read_best(dpps_ctx *c, dpps_best *h, int n, hipStream_t st);
