@@ -1330,13 +1330,15 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
 
 // One workgroup per frame: reduce the frame's tile records to its best pass;
 // block 0 also rearms the persistent work counter for the next launch.
+// INL: the tables come with the launch (a kernel of its own: pointers that may
+// lead to either memory would be slower for both).
+template <bool INL>
 __global__ void __launch_bounds__(256) finalize_kernel(SearchLaunch launch)
 {
     const LaunchArgs &a = launch.a;
-    const bool inl = launch.one.on != 0;
     const OneFrame &one = fresh_args<SearchLaunch>().one;
-    const WinDev *const wins = inl ? &one.win : a.wins;
-    const dpps_variant *const variants = inl ? one.variants : a.variants;
+    const WinDev *const wins = INL ? &one.win : a.wins;
+    const dpps_variant *const variants = INL ? one.variants : a.variants;
     __shared__ TileRec red[256 / 64];
     __shared__ int s_wi;
     const int f = blockIdx.x;
@@ -1344,7 +1346,7 @@ __global__ void __launch_bounds__(256) finalize_kernel(SearchLaunch launch)
     if (f == 0 && tid < 8 && a.counter) a.counter[tid] = 0u;  // the search's 8 counters
     if (f == 0 && tid == 0 && a.count_host) *a.count_host = *a.n_frames_dev;
     if (a.n_frames_dev && f >= *a.n_frames_dev) return;
-    const FrameDev F = inl ? one.frame : a.frames[f];
+    const FrameDev F = INL ? one.frame : a.frames[f];
     // the frame's tile records, or one record per workgroup of a one-frame
     // launch
     const int rc = a.wg_records ? a.wg_records : F.tile_count;
@@ -1468,7 +1470,8 @@ static int launch_kpl(const SearchLaunch &s, int waves_per_wg, int grid, hipStre
     }
     if (e1) (void)hipEventRecord(e1, st);
     if (a.n_frames > 0)
-        hipLaunchKernelGGL(finalize_kernel, dim3(a.n_frames), dim3(256), 0, st, s);
+        hipLaunchKernelGGL(s.one.on ? finalize_kernel<true> : finalize_kernel<false>,
+                           dim3(a.n_frames), dim3(256), 0, st, s);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
