@@ -425,18 +425,9 @@ int batch_upload(dpps_ctx *c, dpps_batch *b)
     return DPPS_OK;
 }
 
-void one_frame(const HostTables &T, OneFrame &o)
-{
-    o.on = 1;
-    o.frame = T.frames[0];
-    if (!T.wins.empty()) o.win = T.wins[0];
-    memcpy(o.robots, T.robots.data(), T.robots.size() * sizeof(dpps_robot));
-    memcpy(o.variants, T.variants.data(), T.variants.size() * sizeof(dpps_variant));
-}
-
 int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t st,
-                     bool timed, const dpps_power_params *power, float *v0_out, bool inl,
-                     dpps_best *best_host)
+                     bool timed, const dpps_power_params *power, float *v0_out,
+                     const OneFrame *one, dpps_best *best_host)
 {
     if (!out) return fail(DPPS_E_INVALID, "outputs is NULL");
     SearchLaunch s;
@@ -450,8 +441,8 @@ int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t s
     a.tiles = b->d_tiles;
     a.n_tiles = (int32_t)b->T.tiles.size();
     a.n_frames = b->n_frames;
-    if (inl) {  // the tables go with the launch, the tiles are implicit
-        one_frame(b->T, s.one);
+    if (one && one->on) {  // the tables go with the launch, the tiles are implicit
+        s.one = *one;
         a.tiles_per_frame = a.n_tiles;
     }
     a.best_host = best_host;
@@ -739,20 +730,35 @@ static int request_tile(const dpps_ctx *c, int32_t n_frames, const dpps_frame *f
     return c->tile_points;
 }
 
+int stage_or_carry(dpps_ctx *c, dpps_batch *b, OneFrame &one, hipStream_t st, bool windows)
+{
+    one.on = 0;
+    if (b->n_frames != 1 || (windows && b->T.wins.size() > 1)) return stage_tables(c, b, st);
+    graph_drop(b);
+    const int rc = batch_reserve(c, b, table_layout(b->T));
+    if (rc) return rc;
+    one.on = 1;
+    one.frame = b->T.frames[0];
+    if (!b->T.wins.empty()) one.win = b->T.wins[0];
+    memcpy(one.robots, b->T.robots.data(), b->T.robots.size() * sizeof(dpps_robot));
+    memcpy(one.variants, b->T.variants.data(), b->T.variants.size() * sizeof(dpps_variant));
+    return DPPS_OK;
+}
+
 // Validate host frames and copy their tables into a batch the context owns
 // (c->scratch or c->fallback), through the pinned staging buffer and an
 // asynchronous copy on st; device memory grows only when a request is larger
 // than any before.
 int stage_batch(dpps_ctx *c, dpps_batch *b, int32_t n_frames, const dpps_frame *frames,
                 const dpps_robot *robots, const dpps_window *windows,
-                const dpps_variant *variants, hipStream_t st)
+                const dpps_variant *variants, OneFrame &one, hipStream_t st)
 {
     const int tp = request_tile(c, n_frames, frames, windows);
     int rc = build_tables(&c->p, n_frames, frames, robots, windows, variants, tp, b->T);
     if (rc) return rc;
     b->n_frames = n_frames;
     b->tile_points = tp;
-    return stage_tables(c, b, st);
+    return stage_or_carry(c, b, one, st);
 }
 
 // Room for n best records in the context's pinned landing buffer.
@@ -817,9 +823,10 @@ int dpps_search_batch(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
     if (!out) return fail(DPPS_E_INVALID, "outputs is NULL");
     HIP_OK(hipSetDevice(c->device));
     hipStream_t st = hip_stream ? (hipStream_t)hip_stream : c->stream;
-    int rc = stage_batch(c, &c->scratch, n_frames, frames, robots, windows, variants, st);
+    OneFrame one;
+    int rc = stage_batch(c, &c->scratch, n_frames, frames, robots, windows, variants, one, st);
     if (rc) return rc;
-    return run_batch(c, &c->scratch, out, st, true);
+    return run_batch(c, &c->scratch, out, st, true, nullptr, nullptr, &one);
 }
 
 int dpps_search_power(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
@@ -846,9 +853,11 @@ int dpps_search_power(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
         F.n_variants = 1;
         F.variant_off = 0;
     }
-    int rc = stage_batch(c, &c->scratch, n_frames, fr.data(), robots, windows, one.data(), st);
+    OneFrame carried;
+    int rc = stage_batch(c, &c->scratch, n_frames, fr.data(), robots, windows, one.data(), carried,
+                         st);
     if (rc) return rc;
-    return run_batch(c, &c->scratch, out, st, true, pp, d_v0);
+    return run_batch(c, &c->scratch, out, st, true, pp, d_v0, &carried);
 }
 
 int dpps_ray_search(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
@@ -982,14 +991,15 @@ int dpps_shot_decision(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
     const dpps_window no_window = {0.0f, 0, 0, 0, 0};
     dpps_batch *b = &c->shots;
     int rc = build_tables(&c->p, n_frames, fr.data(), robots, d_map ? windows : &no_window, &one,
-                          c->shot_tile, b->T);
+                          SHOT_TILE, b->T);
     if (rc) return rc;
     b->n_frames = n_frames;
-    b->tile_points = c->shot_tile;
-    rc = stage_tables(c, b, st);
+    b->tile_points = SHOT_TILE;
+    ShotLaunch s;
+    memset(&s, 0, sizeof s);
+    rc = stage_or_carry(c, b, s.one, st);
     if (rc) return rc;
-    ShotArgs a;
-    memset(&a, 0, sizeof a);
+    ShotArgs &a = s.a;
     a.P = c->P;
     a.frames = b->d_frames;
     a.robots = b->d_robots;
@@ -998,13 +1008,11 @@ int dpps_shot_decision(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
     a.tiles = b->d_tiles;
     a.n_tiles = (int32_t)b->T.tiles.size();
     a.n_frames = n_frames;
-    a.tile_points = c->shot_tile;
-    a.v_shot = sp->v_shot;
     a.min_angle = sp->min_angle;
     a.margin = sp->margin_s;
     a.ball = d_ball;
     a.map = d_map;
-    if (launch_shot(a, c->shot_waves, (void *)st)) return fail(DPPS_E_DEVICE, "shot launch failed");
+    if (launch_shot(s, (void *)st)) return fail(DPPS_E_DEVICE, "shot launch failed");
     return DPPS_OK;
 }
 
@@ -1070,22 +1078,11 @@ int dpps_search(dpps_ctx *c, const dpps_frame *frame, const dpps_robot *robots,
     if (rc) return rc;
     // a frame with one window goes with the launch itself; the best record is
     // written to host memory by the finalize kernel: no copies on the way
-    dpps_batch *b = &c->scratch;
-    const int tp = request_tile(c, 1, frame, windows);
-    rc = build_tables(&c->p, 1, frame, robots, windows, variants, tp, b->T);
-    if (rc) return rc;
-    b->n_frames = 1;
-    b->tile_points = tp;
-    const bool inl = b->T.wins.size() == 1;
-    if (inl) {
-        graph_drop(b);
-        rc = batch_reserve(c, b, table_layout(b->T));
-    } else {
-        rc = stage_tables(c, b, c->stream);
-    }
+    OneFrame one;
+    rc = stage_batch(c, &c->scratch, 1, frame, robots, windows, variants, one, c->stream);
     if (rc) return rc;
     // no timing events around the kernel of a single synchronous search
-    rc = run_batch(c, b, &o, c->stream, false, nullptr, nullptr, inl, c->pinned_best);
+    rc = run_batch(c, &c->scratch, &o, c->stream, false, nullptr, nullptr, &one, c->pinned_best);
     if (rc) return rc;
     return read_best(c, h_best, 1, c->stream);
 }

@@ -106,6 +106,21 @@ struct FallbackArgs {
     int32_t *count;
 };
 
+// The tables of a request of one frame and one window, carried by the launch
+// itself (on != 0) instead of device memory: no copy goes ahead of it, and the
+// kernel that reduces the frame writes its record to pinned host memory, so
+// none follows.  What bounds a small frame is this chain of copies and
+// launches: 57 -> 42 us for the whole call of 6 + 6 robots on 61 x 46 points,
+// 159 -> 130 us for the 0.05 m frame.  Several windows would need a list of
+// unknown length: those requests are staged as before.
+struct OneFrame {
+    int32_t on, pad;
+    FrameDev frame;
+    WinDev win;
+    dpps_robot robots[2 * DPPS_MAX_SIDE];
+    dpps_variant variants[DPPS_MAX_VARIANTS];
+};
+
 struct LaunchArgs {
     DevParams P;
     const FrameDev *frames;
@@ -153,21 +168,6 @@ struct LaunchArgs {
     // and the number of frames of a launch that reads it on the device
     dpps_best *best_host;
     int32_t *count_host;
-};
-
-// The tables of a request of one frame and one window, carried by the launch
-// itself (on != 0) instead of device memory: no copy goes ahead of it, and the
-// kernel that reduces the frame writes its record to pinned host memory, so
-// none follows.  What bounds a small frame is this chain of copies and
-// launches: 57 -> 42 us for the whole call of 6 + 6 robots on 61 x 46 points,
-// 159 -> 130 us for the 0.05 m frame.  Several windows would need a list of
-// unknown length: those requests are staged as before.
-struct OneFrame {
-    int32_t on, pad;
-    FrameDev frame;
-    WinDev win;
-    dpps_robot robots[2 * DPPS_MAX_SIDE];
-    dpps_variant variants[DPPS_MAX_VARIANTS];
 };
 
 // Arguments of the search and finalize kernels.
@@ -219,6 +219,12 @@ struct ShotArgs {
     dpps_shot *ball;        // one record per frame
     dpps_shot *map;         // one record per window point (may be NULL)
 };
+struct ShotLaunch {
+    ShotArgs a;
+    OneFrame one;           // on: tile t is the window's t-th
+};
+// Window points per workgroup of the shot map.
+constexpr int SHOT_TILE = 32;
 
 // Running points: one workgroup per zone (window).
 struct RunArgs {
@@ -248,8 +254,8 @@ int launch_ray_dirs(double2 *dirs, int n, void *stream);
 int launch_ray(const RayArgs &a, int waves_per_wg, int grid, void *stream, void *ev_start,
                void *ev_stop);
 int ray_occupancy(int K, int waves_per_wg);
-// Shooting decisions: the ball kernel, then (with a.map) the window kernel.
-int launch_shot(const ShotArgs &a, int waves_per_wg, void *stream);
+// Shooting decisions: every frame's ball and (with a.map) its window points.
+int launch_shot(const ShotLaunch &s, void *stream);
 int launch_run(const RunArgs &a, void *stream);
 
 }  // namespace dpps

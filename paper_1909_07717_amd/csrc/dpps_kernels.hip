@@ -294,9 +294,8 @@ __device__ __forceinline__ float robot_time_h(float4 r, float fq, float LA, cons
 }
 
 // How a wave's lanes hold a path's samples: HALF_WAVE, lanes 0-31 one
-// point's and lanes 32-63 another's; FULL_WAVE, all 64 lanes one path's;
-// PLAIN, all 64 lanes in another order (bounds over the whole path only).
-enum { HALF_WAVE, FULL_WAVE, PLAIN };
+// point's and lanes 32-63 another's; FULL_WAVE, all 64 lanes one path's.
+enum { HALF_WAVE, FULL_WAVE };
 
 // Greatest of the lanes' values over groups of 8 lanes (8: row_half_mirror
 // last) or rows of 16, on every lane of the group.
@@ -431,6 +430,22 @@ __device__ __forceinline__ float arrival_bound(const RobotK &P, double t, double
     return (U * fabsf(U) < del ? lb0 : lb1) * (1.0f - 1.0f / 4096.0f);
 }
 
+// A robot in the frame of a path from (bx, by) along (ux, uy), in units of
+// its acceleration: (along, across^2, velocity along, across x velocity
+// across); t, q and wn are the unrounded along and across and the velocity
+// across.
+__device__ __forceinline__ float4 robot_frame(const float4 &r, double A, double bx, double by,
+                                              double ux, double uy, double &t, double &q,
+                                              double &wn)
+{
+    const double ax = bx - (double)r.x, ay = by - (double)r.y;
+    t = -(ax * ux + ay * uy) * A;
+    q = (ay * ux - ax * uy) * A;
+    const double we = ((double)r.z * ux + (double)r.w * uy) * 0.70710678118654752;
+    wn = ((double)r.w * ux - (double)r.z * uy) * 0.70710678118654752;
+    return make_float4((float)t, (float)(q * q + 1e-30), (float)we, (float)(q * wn));
+}
+
 // Path frame of a ball path along the unit direction e = (ux, uy) for the
 // staged robots, in float64 and then rounded once: for robot j with offset a
 // = ball - x_j and normal n = (-e_y, e_x): t = -a.e and q = a.n (scaled by
@@ -443,14 +458,13 @@ __device__ __forceinline__ float arrival_bound(const RobotK &P, double t, double
 // b-th quarter, with HALF_WAVE row b the quarters 2b and 2b + 1; the bounds
 // go to the key block as [quarter][rank], and the order is by the least.
 // Otherwise lane l takes robot l and bounds it over the whole path; keys by
-// rank (PLAIN: by robot, with the side in the top bit and the robot in the
-// low bits).  Every lane of the wave takes part (the syncs are wave-wide).
+// rank.  Every lane of the wave takes part (the syncs are wave-wide).
 template <int MODE>
 __device__ __forceinline__ void path_frame_dir(const StageLDS &S, const DevParams &P, float4 *pr,
                                                int n_rob, int n_tm, double LA, double ux,
                                                double uy, double bx, double by, int l)
 {
-    const bool split = MODE != PLAIN && n_rob <= SPLIT_ROB;
+    const bool split = n_rob <= SPLIT_ROB;
     const int r0 = split ? l & 15 : l, row = l >> 4;
     const RobotK rk(P);
     uint32_t *const pk = bound_keys(pr);
@@ -459,21 +473,16 @@ __device__ __forceinline__ void path_frame_dir(const StageLDS &S, const DevParam
     float lb0 = INFINITY, lb1 = INFINITY;  // the row's bounds (split)
     if (r0 < n_rob) {
         const float4 r = S.rob[r0];
-        const double A = (double)P.A;
-        const double ax = bx - (double)r.x, ay = by - (double)r.y;
-        const double t = -(ax * ux + ay * uy) * A;
-        const double q = (ay * ux - ax * uy) * A;
-        const double we = ((double)r.z * ux + (double)r.w * uy) * 0.70710678118654752;
-        const double wn = ((double)r.w * ux - (double)r.z * uy) * 0.70710678118654752;
-        fr = make_float4((float)t, (float)(q * q + 1e-30), (float)we, (float)(q * wn));
+        double t, q, wn;
+        fr = robot_frame(r, (double)P.A, bx, by, ux, uy, t, q, wn);
         double s0 = 0.0, s1 = LA;
         if (split) {
             s0 = 0.25 * LA * (double)(MODE == HALF_WAVE ? 2 * row : row);
             s1 = s0 + 0.25 * LA;
         }
-        lb0 = arrival_bound(rk, t, q, (float)we, (float)wn, s0, s1);
+        lb0 = arrival_bound(rk, t, q, fr.z, (float)wn, s0, s1);
         if (MODE == HALF_WAVE && split)
-            lb1 = arrival_bound(rk, t, q, (float)we, (float)wn, s1, s1 + 0.25 * LA);
+            lb1 = arrival_bound(rk, t, q, fr.z, (float)wn, s1, s1 + 0.25 * LA);
     }
     if (split) {
         // the robot's least bound over the rows
@@ -496,17 +505,15 @@ __device__ __forceinline__ void path_frame_dir(const StageLDS &S, const DevParam
         rank += (k4.x < key) + (k4.y < key) + (k4.z < key) + (k4.w < key);
     }
     if (r0 < n_rob && (!split || row == 0)) pr[rank] = fr;
-    if (MODE != PLAIN) {
-        wave_lds_sync();  // the ranks are formed: the key block takes the bounds by rank
-        if (r0 < n_rob) {
-            if (!split) {
-                pk[rank] = __float_as_uint(lb0) & ~(uint32_t)(MAX_ROB - 1);
-            } else if (MODE == HALF_WAVE) {
-                pk[(2 * row) * 16 + rank] = __float_as_uint(lb0);
-                pk[(2 * row + 1) * 16 + rank] = __float_as_uint(lb1);
-            } else {
-                pk[row * 16 + rank] = __float_as_uint(lb0);
-            }
+    wave_lds_sync();  // the ranks are formed: the key block takes the bounds by rank
+    if (r0 < n_rob) {
+        if (!split) {
+            pk[rank] = __float_as_uint(lb0) & ~(uint32_t)(MAX_ROB - 1);
+        } else if (MODE == HALF_WAVE) {
+            pk[(2 * row) * 16 + rank] = __float_as_uint(lb0);
+            pk[(2 * row + 1) * 16 + rank] = __float_as_uint(lb1);
+        } else {
+            pk[row * 16 + rank] = __float_as_uint(lb0);
         }
     }
     // the row is written and read by this wave only
@@ -1521,6 +1528,19 @@ __device__ __forceinline__ float group_sum(float c)
     return c;
 }
 
+// Least of the lanes' values over each half of the wave, on all its lanes.
+__device__ __forceinline__ float half_min(float x)
+{
+    x = fminf(x, quad_xor<1>(x));
+    x = fminf(x, quad_xor<2>(x));
+    x = fminf(x, half_mirror(x));
+    x = fminf(x, row_mirror(x));
+    // rows 0 and 1 (2 and 3) exchanged
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false,
+                                                    false);
+    return fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // Least / greatest value over the wave (DPP within each row of 16 lanes,
 // then the four rows), on every lane.
 __device__ __forceinline__ float wave_min_dpp(float x)
@@ -1975,231 +1995,293 @@ int ray_occupancy(int K, int waves_per_wg)
 // the opponents' interception along a flat shot through its centre.
 // ----------------------------------------------------------------------------
 
-// Ball time (float32) to distance s of a staged variant.
-__device__ __forceinline__ float ball_time32(const VarConst &c, float s)
-{
-    const bool ph1 = s <= (float)c.split;
-    const float va = ph1 ? (float)c.va1 : (float)c.va2;
-    const float ac = ph1 ? (float)c.a1 : (float)c.a2;
-    const float x = s - (ph1 ? 0.0f : (float)c.soff2);
-    const float to = ph1 ? 0.0f : (float)c.toff2;
-    const float q = fmaxf(fmaf(-2.0f * ac, x, va * va), 0.0f);
-    return fmaf(2.0f * x, hrcp(va + hsqrt(q)), to);
-}
+// A kick's ball-time constants in float32.
+struct BallTime {
+    float split, va1, va2, na1, na2, so2, to2;  // na = -2 a
+    __device__ __forceinline__ explicit BallTime(const VarConst &c)
+        : split(unif((float)c.split)), va1(unif((float)c.va1)), va2(unif((float)c.va2)),
+          na1(unif(-2.0f * (float)c.a1)), na2(unif(-2.0f * (float)c.a2)),
+          so2(unif((float)c.soff2)), to2(unif((float)c.toff2))
+    {
+    }
+    __device__ __forceinline__ float at(float s) const
+    {
+        const bool ph1 = s <= split;
+        const float va = ph1 ? va1 : va2;
+        const float x = s - (ph1 ? 0.0f : so2);
+        const float q = fmaxf(fmaf(ph1 ? na1 : na2, x, va * va), 0.0f);
+        return fmaf(2.0f * x, hrcp(va + hsqrt(q)), ph1 ? 0.0f : to2);
+    }
+};
 
-// Earliest arrival (A T / 2), at each of the lane's samples, of the
-// opponents [n_tm, n_tm + n_op) of a shot's path frame, sorted by ascending
-// lower bound on their arrival over the path -- for the shot's least slack
-// only.  After the first two opponents, and again after the next two, the
-// slack so far is taken: the least, over the samples the ball reaches
-// (sk <= D), of the arrival less the ball's time tb there; tbm is the latest
-// of those ball times.  An opponent whose bound less tbm is not below that
-// slack cannot lower it at any sample (its arrival is at least the bound, the
-// ball's time at most tbm, and both roundings are monotone; the bound is
-// shaved by 2^-16 and tbm raised by 2^-18 to cover the two forms'
-// roundings), nor can the opponents after it in the sorted order: they are
-// left out.  The minima can then differ at some samples; the least slack
-// cannot.
-template <int KPL>
-__device__ __forceinline__ void shot_opponents(const float4 *pr, const DevParams &P, int n_tm,
-                                               int n_op, const float (&fs)[KPL],
-                                               const float (&sk)[KPL], const float (&tb)[KPL],
-                                               float D, float LA, float tbm, float (&T)[KPL])
-{
-    const float tbh = tbm * (1.0f + 1.0f / 262144.0f);
-    const RobotK rk(P);
-    int need = n_op;
-    int j = 0;
-    for (; j + 1 < need; j += 2) {
-        const float4 ra = pr[n_tm + j], rb = pr[n_tm + j + 1];
-#pragma unroll
-        for (int q = 0; q < KPL; ++q)
-            T[q] = fminf(T[q], fminf(robot_time_h<true>(ra, fs[q], LA, rk),
-                                     robot_time_h<true>(rb, fs[q], LA, rk)));
-        if (j < 4 && need > j + 2) {
-            float m = INFINITY;
-#pragma unroll
-            for (int q = 0; q < KPL; ++q) {
-                const float d = T[q] * P.invA2 - tb[q];
-                m = sk[q] <= D ? fminf(m, d) : m;
-            }
-            m = wave_min_dpp(m);
-            const int l = lane_id();
-            const uint32_t k = l < MAX_ROB ? bound_keys(pr)[l] : 0xFFFFFFFFu;
-            const float kv = __uint_as_float(k & 0x7FFFFFFFu & ~(uint32_t)(MAX_ROB - 1));
-            const bool opp = k != 0xFFFFFFFFu && (k & 0x80000000u) != 0u;
-            const bool out = fmaf(kv * (1.0f - 1.0f / 65536.0f), P.invA2, -tbh) >= m;
-            need = min(max((int)__builtin_popcountll(__ballot(opp && !out)), j + 2), need);
-        }
-    }
-    if (j < need) {
-        const float4 r = pr[n_tm + j];
-#pragma unroll
-        for (int q = 0; q < KPL; ++q) T[q] = fminf(T[q], robot_time_h<true>(r, fs[q], LA, rk));
-    }
-}
+// Staging of up to SHOT_TILE shooter positions of one frame.
+struct ShotLDS {
+    double cx[SHOT_TILE], cy[SHOT_TILE], ux[SHOT_TILE], uy[SHOT_TILE], L[SHOT_TILE];
+    // each opponent's shadow (start and end angle, empty: start > end), later
+    // its bound; the gap behind each shadow and (last) above the lower post
+    float s[DPPS_MAX_SIDE][SHOT_TILE], e[DPPS_MAX_SIDE][SHOT_TILE];
+    float w[DPPS_MAX_SIDE + 1][SHOT_TILE];
+    float lo[SHOT_TILE], hi[SHOT_TILE];
+    float tb[4][SHOT_TILE];                      // latest ball time of each quarter
+    int blocked[SHOT_TILE];                      // the position is inside an opponent
+    dpps_shot rec[SHOT_TILE];
+    float4 fr[SHOT_TILE][DPPS_MAX_SIDE + 1];     // opponents by ascending bound (a column
+    float sl[SHOT_TILE][DPPS_MAX_SIDE + 1];      // more: rows on different banks)
+};
 
-// Open gaps of the goal mouth seen from (cx, cy); lanes are opponents, lane 62
-// the lower post.  A gap starts at the lower post or at the end of a shadow
-// that no other shadow covers, and runs to the next shadow start (or the
-// upper post).  Returns the widest gap and its start (ties to the lower
-// start) and the sum of the gaps; the same values on every lane.
-__device__ __forceinline__ void shot_gaps(const StageLDS &S, const DevParams &P, float cx,
-                                          float cy, int n_op, int n_tm, float &gap, float &g0,
-                                          float &open)
+// The least, over the lane's samples, of the opponents' earliest arrival less
+// the ball's time; lanes of one half share a position (row of H) and have its
+// least slack.  Opponents are taken by ascending lower bound on the slack they
+// leave; one whose bound is not below the slack so far cannot lower it, nor
+// can those after it (every rounding in between is monotone): they are left
+// out.  1.8 of 8 opponents per position are evaluated on average.
+template <int KPH, bool CLAMP>
+__device__ __forceinline__ float shot_slack(const ShotLDS &H, const RobotK &rk, const BallTime &bt,
+                                            float D, float A, float invA2, int n_op, int p)
 {
-    const int l = lane_id();
-    const float dxg = fmaxf(P.goal_x - cx, P.goal_eps);
-    const float4 o = S.rob[n_tm + (l < n_op ? l : 0)];
-    const float ox = o.x - cx, oy = o.y - cy;
-    const float Y = l < n_op ? oy : (l == 62 ? -P.half_goal_w - cy : P.half_goal_w - cy);
-    const float X = l < n_op ? ox : dxg;
-    const float ang = atan2f(Y, X);
-    const float lo = readlane_f(ang, 62);
-    const float hi = readlane_f(ang, 63);
-    const bool valid = l < n_op && o.x < P.goal_x;
-    const float rho2 = fmaf(ox, ox, oy * oy);
-    gap = 0.0f;
-    g0 = lo;
-    open = 0.0f;
-    if (__ballot(valid && rho2 <= P.R * P.R)) return;
-    const float al = asinf(fminf(P.R * rsq(fmaxf(rho2, 1e-30f)), 1.0f));
-    const float s = fmaxf(ang - al, lo);
-    const float e = fminf(ang + al, hi);
-    const bool has = valid && e > s;
-    const unsigned long long hm = __ballot(has);
-    const bool cand = has || l == 62;
-    const float st = l == 62 ? lo : e;
-    bool cov = false;
-    float nxt = hi;
-    for (unsigned long long m = hm; m; m &= m - 1) {
-        const int k = __builtin_ctzll(m);
-        const float sk = readlane_f(s, k);
-        const float ek = readlane_f(e, k);
-        cov = cov || (sk <= st && ek > st);
-        nxt = sk > st ? fminf(nxt, sk) : nxt;
-    }
-    const float w = cand && !cov ? fmaxf(nxt - st, 0.0f) : 0.0f;
-    const unsigned long long cm = __ballot(cand);
-    for (unsigned long long m = cm; m; m &= m - 1) {
-        const int k = __builtin_ctzll(m);
-        const float wk = readlane_f(w, k);
-        const float sk = readlane_f(st, k);
-        open += wk;
-        if (wk > gap || (wk == gap && wk > 0.0f && sk < g0)) {
-            gap = wk;
-            g0 = sk;
-        }
-    }
-}
-
-// The decision from shooter position (cx, cy) of the staged frame; lane 0's
-// record is the result.
-template <int KPL>
-__device__ dpps_shot shot_origin(const StageLDS &S, const DevParams &P, float4 *pr, double cx,
-                                 double cy, const VarConst &vc, float min_angle, float margin)
-{
-    const int l = lane_id();
-    const int K = KPL * 64;
-    const int n_tm = uni(S.n_tm), n_op = uni(S.n_op);
-    const float fx = (float)cx, fy = (float)cy;
-    float gap, g0, open;
-    shot_gaps(S, P, fx, fy, n_op, n_tm, gap, g0, open);
-    const double dxg = fmax((double)P.goal_x - cx, (double)P.goal_eps);
-    const float aim = gap > 0.0f ? fmaf(0.5f, gap, g0) : atan2f(-fy, (float)dxg);
-    const double ux = (double)cosf(aim), uy = (double)sinf(aim);
-    const double L = dxg / ux;
-    path_frame_dir<PLAIN>(S, P, pr, n_tm + n_op, n_tm, L * (double)P.A, ux, uy, cx, cy, l);
-    const float Lf = (float)L, LA = (float)(L * (double)P.A);
-    const float D = (float)vc.D;
-    float fs[KPL], sk[KPL], tb[KPL], T[KPL];
-    float tbm = -INFINITY;
+    const int hl = lane_id() & 31;
+    const float Lf = (float)H.L[p], LA = (float)(H.L[p] * (double)A);
+    float fs[KPH], tb[KPH];
 #pragma unroll
-    for (int q = 0; q < KPL; ++q) {
-        fs[q] = (float)(q * 64 + l + 1) * (1.0f / (float)K);
-        sk[q] = fs[q] * Lf;
-        tb[q] = ball_time32(vc, sk[q]);
-        T[q] = INFINITY;
-        tbm = sk[q] <= D ? fmaxf(tbm, tb[q]) : tbm;
+    for (int q = 0; q < KPH; ++q) {
+        fs[q] = (float)(q * 32 + hl + 1) * (1.0f / (float)(KPH * 32));
+        const float sk = fs[q] * Lf;
+        const float t = bt.at(sk);
+        tb[q] = sk <= D ? t : -INFINITY;  // past the ball's reach: no slack
     }
-    shot_opponents<KPL>(pr, P, n_tm, n_op, fs, sk, tb, D, LA, wave_max_dpp(tbm), T);
+    const float bound = hl < n_op ? H.sl[p][hl] : INFINITY;
     float m = INFINITY;
+    for (int j = 0; j < n_op; ++j) {
+        const float4 r = H.fr[p][j];
 #pragma unroll
-    for (int q = 0; q < KPL; ++q) {
-        const float d = T[q] * P.invA2 - tb[q];
-        m = sk[q] <= D ? fminf(m, d) : m;
+        for (int q = 0; q < KPH; ++q) {
+            const float d = robot_time_h<CLAMP>(r, fs[q], LA, rk) * invA2 - tb[q];
+            m = fminf(m, d);
+        }
+        m = half_min(m);
+        if (__ballot(hl > j && bound < m) == 0ull) break;
     }
-    m = wave_min_dpp(m);
-    dpps_shot r;
-    r.reachable = L <= vc.D;
-    r.aim = aim;
-    r.gap = gap;
-    r.open_angle = open;
-    r.length = Lf;
-    r.t_goal = r.reachable ? (float)ball_time64(vc, L) : INFINITY;
-    r.slack = m;
-    r.shoot = gap >= min_angle && r.reachable && m > margin;
-    return r;
+    return m;
 }
 
-// BALL: one single-wave workgroup per frame, from the frame's ball.  MAP:
-// one workgroup per tile of window points, each wave one point at a time.
-template <int KPL, bool MAP>
-__global__ void __launch_bounds__(512) shot_kernel(ShotArgs a)
+// Shooting decisions of one frame per workgroup: a tile of its window's
+// points, or (the first n_frames workgroups) its ball.
+//
+// Bound by VALU issue.  What differs by position and opponent -- the shadow's
+// angles, the opponent in the shot's frame, its bounds -- has a lane per
+// (position, opponent), and what differs by position only -- the widest gap,
+// the aim's sine and cosine, the path's length -- a lane per position, rather
+// than a wave per position with a lane per opponent; the samples of two
+// positions share a wave, one per half.  The bounds are on the slack of each
+// quarter of the path.  241 x 181 positions, 8 opponents, K = 256:
+// 84 -> 35 us (profiled), the whole call 51 -> 18 us.  Tiles of 16: 35 us too,
+// but 64 frames of 61 x 46 positions 197 us a call against 176.
+template <int KPH, bool INL>
+__global__ void __launch_bounds__(256) shot_kernel(ShotLaunch launch)
 {
     __shared__ StageLDS S;
-    __shared__ float4 PR[MAX_WAVES][PR_ENTRIES];
-    const DevParams &P = a.P;
-    const int w = threadIdx.x >> 6;
-    const int l = lane_id();
-    const int t = blockIdx.x;
-    const TileDev tile = MAP ? a.tiles[t] : TileDev{0, 0};
-    const WinDev W = MAP ? a.wins[tile.win] : WinDev{};
-    const int f = MAP ? W.frame : t;
-    stage_frame(P, a.frames[f], a.robots, a.variants, f, S);
+    __shared__ ShotLDS H;
+    const ShotArgs &a = launch.a;
+    const OneFrame &one = fresh_args<ShotLaunch>().one;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const bool map = (int)blockIdx.x >= a.n_frames;
+    const int t = map ? (int)blockIdx.x - a.n_frames : (int)blockIdx.x;
+    WinDev W = {};
+    int f = t, p0 = 0, np = 1;
+    if (map) {
+        const TileDev tile = INL ? TileDev{0, t} : a.tiles[t];
+        W = INL ? one.win : a.wins[tile.win];
+        f = W.frame;
+        p0 = tile.at * SHOT_TILE;
+        np = min(SHOT_TILE, W.npts - p0);
+    }
+    const FrameDev F = INL ? one.frame : a.frames[f];
+    stage_frame(a.P, F, INL ? one.robots : a.robots, INL ? one.variants : a.variants, f, S);
+    // (the last threads: the first wave stages the frame)
+    for (int p = nt - 1 - tid; p < np; p += nt) {
+        const int j = map ? (p0 + p) / W.nx : 0, i = p0 + p - j * W.nx;
+        H.cx[p] = map ? (double)W.h * ((double)(W.i0 + i) - (double)W.halfNx) : (double)F.ball_x;
+        H.cy[p] = map ? (double)W.h * ((double)(W.j0 + j) - (double)W.halfNy) : (double)F.ball_y;
+        H.blocked[p] = 0;
+    }
     __syncthreads();
-    const VarConst vc = var_const(P.bp, DPPS_FLAT, a.v_shot);
-    if (!MAP) {
-        const dpps_shot r = shot_origin<KPL>(S, P, PR[0], (double)S.bx, (double)S.by, vc,
-                                             a.min_angle, a.margin);
-        if (l == 0) a.ball[f] = r;
-        return;
+    const DevParams &P = a.P;
+    const int n_tm = uni(S.n_tm), n_op = uni(S.n_op);
+    // pairs (position, row): a power of two of lanes per row
+    const int sh = np > 1 ? 32 - __builtin_clz(np - 1) : 0, pm = (1 << sh) - 1;
+    // Shadows seen from the position: angle of the opponent, -+ asin(R / distance)
+    // (rows n_op and n_op + 1: the posts).
+    for (int x = tid; x < (n_op + 2) << sh; x += nt) {
+        const int p = x & pm, o = x >> sh;
+        if (p >= np) continue;
+        const float cx = (float)H.cx[p], cy = (float)H.cy[p];
+        const float dxg = fmaxf(P.goal_x - cx, P.goal_eps);
+        const float4 r = S.rob[n_tm + (o < n_op ? o : 0)];
+        const float ox = r.x - cx, oy = r.y - cy;
+        const float Y = o < n_op ? oy : (o == n_op ? -P.half_goal_w - cy : P.half_goal_w - cy);
+        const float X = o < n_op ? ox : dxg;
+        const float ang = atan2f(Y, X);
+        if (o >= n_op) {
+            (o == n_op ? H.lo : H.hi)[p] = ang;
+            continue;
+        }
+        const bool valid = r.x < P.goal_x;
+        const float rho2 = fmaf(ox, ox, oy * oy);
+        if (valid && rho2 <= P.R * P.R) H.blocked[p] = 1;
+        const float al = asinf(fminf(P.R * rsq(fmaxf(rho2, 1e-30f)), 1.0f));
+        H.s[o][p] = valid ? ang - al : INFINITY;
+        H.e[o][p] = valid ? ang + al : -INFINITY;
     }
-    const int p0 = tile.at * a.tile_points;
-    const int np = min(a.tile_points, W.npts - p0);
-    const int nw = blockDim.x >> 6;
-    for (int slot = w; slot < np; slot += nw) {
-        const int p = p0 + slot;
-        const int j = p / W.nx, i = p - j * W.nx;
-        const double cx = (double)W.h * ((double)(W.i0 + i) - (double)W.halfNx);
-        const double cy = (double)W.h * ((double)(W.j0 + j) - (double)W.halfNy);
-        const dpps_shot r = shot_origin<KPL>(S, P, PR[w], cx, cy, vc, a.min_angle, a.margin);
-        if (l == 0) a.map[W.out_base + p] = r;
+    __syncthreads();
+    // Gap behind each shadow within the mouth, and above the lower post (row
+    // n_op): none if another shadow covers its start, else up to the next
+    // shadow's start or the upper post.
+    for (int x = tid; x < (n_op + 1) << sh; x += nt) {
+        const int p = x & pm, o = x >> sh;
+        if (p >= np) continue;
+        const float lo = H.lo[p], hi = H.hi[p];
+        bool cand = true;
+        float st = lo;
+        if (o < n_op) {
+            st = fminf(H.e[o][p], hi);
+            cand = st > fmaxf(H.s[o][p], lo);
+        }
+        bool cov = false;
+        float nxt = hi;
+        for (int k = 0; k < n_op; ++k) {
+            const float sk = fmaxf(H.s[k][p], lo), ek = fminf(H.e[k][p], hi);
+            const bool has = ek > sk;
+            cov = cov || (has && sk <= st && ek > st);
+            nxt = has && sk > st ? fminf(nxt, sk) : nxt;
+        }
+        H.w[o][p] = cand && !cov ? fmaxf(nxt - st, 0.0f) : 0.0f;
     }
+    __syncthreads();
+    const VarConst &vc = S.vc[0];  // the shot: the frame's only variant
+    const BallTime bt(vc);
+    const float D = unif((float)vc.D);
+    for (int p = tid; p < np; p += nt) {
+        const double cx = H.cx[p], cy = H.cy[p];
+        const float lo = H.lo[p], hi = H.hi[p];
+        // widest gap (ties to the lower start) and the sum of the gaps
+        float gap = 0.0f, g0 = lo, open = 0.0f;
+        if (!H.blocked[p]) {
+            for (int o = 0; o <= n_op; ++o) {
+                const float wk = H.w[o][p];
+                const float sk = o < n_op ? fminf(H.e[o][p], hi) : lo;
+                open += wk;
+                if (wk > gap || (wk == gap && wk > 0.0f && sk < g0)) {
+                    gap = wk;
+                    g0 = sk;
+                }
+            }
+        }
+        const double dxg = fmax((double)P.goal_x - cx, (double)P.goal_eps);
+        const float aim = gap > 0.0f ? fmaf(0.5f, gap, g0) : atan2f(-(float)cy, (float)dxg);
+        const double ux = (double)cosf(aim), uy = (double)sinf(aim);
+        const double L = dxg / ux;
+        const float Lf = (float)L;
+        H.ux[p] = ux;
+        H.uy[p] = uy;
+        H.L[p] = L;
+        // Latest ball time over each quarter's samples, raised by 2^-16 for the
+        // float form's roundings; -inf where the ball stops before the quarter.
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const float s1 = fminf(0.25f * (float)(b + 1) * Lf * (1.0f + 1.0f / 1048576.0f), D);
+            const bool in = 0.25f * (float)b * Lf * (1.0f - 1.0f / 1048576.0f) <= D;
+            H.tb[b][p] = in ? bt.at(s1) * (1.0f + 1.0f / 65536.0f) : -INFINITY;
+        }
+        dpps_shot r;
+        r.reachable = L <= vc.D;
+        r.aim = aim;
+        r.gap = gap;
+        r.open_angle = open;
+        r.length = Lf;
+        r.t_goal = r.reachable ? (float)ball_time64(vc, L) : INFINITY;
+        r.slack = INFINITY;
+        r.shoot = 0;
+        H.rec[p] = r;
+    }
+    __syncthreads();
+    // The opponents in the shot's frame and their bounds: on the arrival over
+    // each quarter (shaved by 2^-16) less the latest ball time there.
+    const RobotK rk(P);
+    float4 fr[2];  // 16 x 32 pairs on 256 threads, 16 on 64
+    float bd[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int x = tid + q * nt, p = x & pm, o = x >> sh;
+        if (o >= n_op || p >= np) continue;
+        double tq, qq, wn;
+        const double ux = H.ux[p], uy = H.uy[p], LA = H.L[p] * (double)P.A;
+        fr[q] = robot_frame(S.rob[n_tm + o], (double)P.A, H.cx[p], H.cy[p], ux, uy, tq, qq,
+                            wn);
+        float b = INFINITY;
+        for (int k = 0; k < 4; ++k) {
+            const double s0 = 0.25 * LA * (double)k;
+            const float lb = arrival_bound(rk, tq, qq, fr[q].z, (float)wn, s0, s0 + 0.25 * LA);
+            b = fminf(b, fmaf(lb * (1.0f - 1.0f / 65536.0f), P.invA2, -H.tb[k][p]));
+        }
+        bd[q] = b;
+        H.s[o][p] = b;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int x = tid + q * nt, p = x & pm, o = x >> sh;
+        if (o >= n_op || p >= np) continue;
+        const uint32_t key = ordered_bits(bd[q]);
+        int rank = 0;
+        for (int k = 0; k < n_op; ++k) {
+            const uint32_t y = ordered_bits(H.s[k][p]);
+            rank += y < key || (y == key && k < o);
+        }
+        H.fr[p][rank] = fr[q];
+        H.sl[p][rank] = bd[q];
+    }
+    __syncthreads();
+    const int h = lane_id() >> 5;
+    for (int p2 = 2 * (tid >> 6); p2 < np; p2 += 2 * (nt >> 6)) {
+        const int p = min(p2 + h, np - 1);
+        const float m = uni(S.vel_ok)
+                            ? shot_slack<KPH, false>(H, rk, bt, D, P.A, P.invA2, n_op, p)
+                            : shot_slack<KPH, true>(H, rk, bt, D, P.A, P.invA2, n_op, p);
+        if ((tid & 31) == 0 && p2 + h < np) {
+            H.rec[p].slack = m;
+            H.rec[p].shoot = H.rec[p].gap >= a.min_angle && H.rec[p].reachable && m > a.margin;
+        }
+    }
+    __syncthreads();
+    static_assert(sizeof(dpps_shot) == 32, "eight words");
+    int *const out = (int *)(map ? a.map + W.out_base + p0 : a.ball + f);
+    for (int x = tid; x < 8 * np; x += nt) out[x] = ((const int *)H.rec)[x];
 }
 
-template <int KPL>
-static int launch_shot_kpl(const ShotArgs &a, int waves_per_wg, hipStream_t st)
+// Workgroups of four waves, one per tile; of one wave where only the balls are
+// asked for.
+template <int KPH>
+static void launch_shot_kph(const ShotLaunch &s, hipStream_t st)
 {
-    if (a.n_frames > 0)
-        hipLaunchKernelGGL((shot_kernel<KPL, false>), dim3(a.n_frames), dim3(64), 0, st, a);
-    if (a.map && a.n_tiles > 0)
-        hipLaunchKernelGGL((shot_kernel<KPL, true>), dim3(a.n_tiles), dim3(64 * waves_per_wg), 0,
-                           st, a);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    const dim3 grid(s.a.n_frames + (s.a.map ? s.a.n_tiles : 0)), block(s.a.map ? 256 : 64);
+    if (s.one.on)
+        hipLaunchKernelGGL((shot_kernel<KPH, true>), grid, block, 0, st, s);
+    else
+        hipLaunchKernelGGL((shot_kernel<KPH, false>), grid, block, 0, st, s);
 }
 
-int launch_shot(const ShotArgs &a, int waves_per_wg, void *stream)
+int launch_shot(const ShotLaunch &s, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    if (waves_per_wg < 1 || waves_per_wg > MAX_WAVES) return -2;
-    switch (a.P.K / 64) {
-    case 1: return launch_shot_kpl<1>(a, waves_per_wg, st);
-    case 2: return launch_shot_kpl<2>(a, waves_per_wg, st);
-    case 3: return launch_shot_kpl<3>(a, waves_per_wg, st);
-    case 4: return launch_shot_kpl<4>(a, waves_per_wg, st);
-    default: return -2;
+    if (s.a.n_frames <= 0) return 0;
+    switch (s.a.P.K / 64) {
+    case 1: launch_shot_kph<2>(s, st); break;
+    case 2: launch_shot_kph<4>(s, st); break;
+    case 3: launch_shot_kph<6>(s, st); break;
+    case 4: launch_shot_kph<8>(s, st); break;
+    default: return -1;
     }
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 // ----------------------------------------------------------------------------

@@ -714,17 +714,10 @@ int dpps_surrogate_search_frames(dpps_ctx *c, dpps_mlp *m, int32_t n_frames,
     b->tile_points = c->tile_points;
     // one frame goes with the feature kernel's launch instead of a copy
     OneFrame one;
-    if (n_frames == 1) {
-        memset(&one, 0, sizeof one);
-        one_frame(b->T, one);
-        graph_drop(b);
-        rc = batch_reserve(c, b, table_layout(b->T));
-    } else {
-        rc = stage_tables(c, b, st);
-    }
+    rc = stage_or_carry(c, b, one, st, false);
     if (rc) return rc;
     return surrogate_core(c, m, b, k, d_best, fallback, fallback_below, n_fallback, h_best,
-                          n_frames == 1 ? &one : nullptr, hip_stream);
+                          one.on ? &one : nullptr, hip_stream);
 }
 
 }  // extern "C"

@@ -95,8 +95,6 @@ struct dpps_ctx {
     int ray_waves = 4;       // waves per workgroup of dpps_ray_search (4: 0.260 ms per
                              // 512-frame call, 8: 0.272 ms)
     dpps_batch shots;        // tables of dpps_shot_decision
-    int shot_tile = 16;      // window points per workgroup of the shot map
-    int shot_waves = 4;      // waves per workgroup of the shot map
     dpps_batch runs;         // tables of dpps_running_points
     void *pinned = nullptr;
     size_t pinned_cap = 0;
@@ -131,14 +129,17 @@ void pack_tables(const dpps::HostTables &T, const Layout &L, char *dst);
 int batch_reserve(dpps_ctx *c, dpps_batch *b, const Layout &L);
 int batch_upload(dpps_ctx *c, dpps_batch *b);
 int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t st, bool timed,
-              const dpps_power_params *power = nullptr, float *v0_out = nullptr, bool inl = false,
-              dpps_best *best_host = nullptr);
-// The launch-carried tables of a request of one frame (and at most one window).
-void one_frame(const dpps::HostTables &T, dpps::OneFrame &o);
+              const dpps_power_params *power = nullptr, float *v0_out = nullptr,
+              const dpps::OneFrame *one = nullptr, dpps_best *best_host = nullptr);
 int stage_batch(dpps_ctx *c, dpps_batch *b, int32_t n_frames, const dpps_frame *frames,
                 const dpps_robot *robots, const dpps_window *windows,
-                const dpps_variant *variants, hipStream_t st);
+                const dpps_variant *variants, dpps::OneFrame &one, hipStream_t st);
 int stage_tables(dpps_ctx *c, dpps_batch *b, hipStream_t st);
+// The tables of a request of one frame (and at most one window, unless its
+// windows are not searched) into `one`, on = 1; any other request is staged in
+// device memory.
+int stage_or_carry(dpps_ctx *c, dpps_batch *b, dpps::OneFrame &one, hipStream_t st,
+                   bool windows = true);
 // Set up the fixed-array search on the context's (current) device.
 int noalloc_setup(dpps_ctx *c);
 void noalloc_release(dpps_ctx *c);
