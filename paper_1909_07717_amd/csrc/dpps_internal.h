@@ -168,6 +168,11 @@ struct LaunchArgs {
     // and the number of frames of a launch that reads it on the device
     dpps_best *best_host;
     int32_t *count_host;
+    // With frame_best (launches without maps, tiles of at most 64 points, the
+    // angle's and the margin's weights not negative; 0 before the launch): the
+    // greatest score found so far by frame (ordered bits).  Points that cannot
+    // be the frame's best are left out.
+    uint32_t *frame_best;
 };
 
 // Arguments of the search and finalize kernels.

@@ -1010,13 +1010,14 @@ __device__ __forceinline__ void wave_best(OutLDS &O, int w, unsigned long long k
 
 // The largest of the waves' records (keys of different waves differ unless
 // both are 0), written by one wave.
-__device__ __forceinline__ void group_best(const OutLDS &O, int nw, TileRec *rec)
+__device__ __forceinline__ unsigned long long group_best(const OutLDS &O, int nw, TileRec *rec)
 {
     const int l = lane_id();
     const unsigned long long k = l < nw ? O.wbest[l].key : 0ull;
     const unsigned long long tk = wave_max_u64(k);
     const unsigned long long at = __ballot(k == tk && l < nw);
     if (l == (int)__builtin_ctzll(at)) *rec = O.wbest[l];
+    return tk;
 }
 
 // Tile t of the launch: from the list, or implicit (tables built on the device).
@@ -1025,6 +1026,31 @@ __device__ __forceinline__ TileDev tile_at(const LaunchArgs &a, int t)
     if (a.tiles_per_frame == 0) return a.tiles[t];
     const int win = (int)((unsigned)t / (unsigned)a.tiles_per_frame);
     return TileDev{win, t - win * a.tiles_per_frame};
+}
+
+// The greatest score found so far of a frame, -inf if none.
+__device__ __forceinline__ float frame_best_score(const uint32_t *p)
+{
+    const uint32_t b = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return b ? unordered_bits(b) : -INFINITY;
+}
+
+// The score that no pass to (cx, cy) exceeds: the goal's whole angle open and
+// the greatest margin (the same operations as the score's).
+__device__ __forceinline__ float score_bound(const DevParams &P, float cx, float cy)
+{
+    const float dxg = fmaxf(P.goal_x - cx, P.goal_eps);
+    const float ang = atan2f(P.half_goal_w - cy, dxg) - atan2f(-P.half_goal_w - cy, dxg);
+    const float gx = cx - P.goal_x;
+    const float dg = hsqrt(fmaf(gx, gx, cy * cy));
+    const float dterm = fmaf(-dg, P.inv_dist_norm, 1.0f);
+    return fmaf(P.w_ang_pi, ang, fmaf(P.w_dist, dterm, P.w_margin * P.margin_cap));
+}
+
+// Greatest of the lanes' values, none negative.
+__device__ __forceinline__ float wave_max_pos(float x)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(wave_prefix_imax(__float_as_int(x)), 63));
 }
 
 // Word l of a window's record in lane l.
@@ -1049,7 +1075,7 @@ __device__ __forceinline__ int window_words(const LaunchArgs &a, bool inl, int w
 // five (256 windows 3.56 -> 3.39 ms; at K = 64 five were slower for one small
 // frame, 16.2 -> 19.0 us, and K >= 192 does not fit).  POWER: one flat pass
 // per point at the point's own passing power (Eq. 1-2).
-template <int KPH, bool POWER>
+template <int KPH, bool POWER, bool BEST>
 __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLaunch launch)
 {
     const LaunchArgs &args = launch.a;
@@ -1059,6 +1085,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
     // path frames of two points, the tile's staged score and mask maps
     extern __shared__ float PMX[];
     __shared__ int s_tile;
+    __shared__ float s_least[2];  // least score worth finding (this tile's, the next's)
     const int nw = blockDim.x >> 6;
     const int w = threadIdx.x >> 6;
     const int l = lane_id();
@@ -1113,7 +1140,11 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
                     inl ? o.variants : args.variants, 0, S);
         cur_frame = 0;
     }
-    int it = 0, pull = 0, pull_end = 0;
+    if (BEST) {
+        if (n_tiles == 0) return;  // no frame took the fallback
+        if (threadIdx.x == 0) s_least[0] = s_least[1] = -INFINITY;
+    }
+    int it = 0, pull = 0, pull_end = 0, turn = 0;
     while (true) {
         // the previous tile (its staged results and records) is finished
         __syncthreads();
@@ -1163,6 +1194,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
                                (uint32_t)readlane_i(cw, 10));
         if (W.frame != cur_frame) {
             stage_frame(a.P, a.frames[W.frame], a.robots, a.variants, W.frame, S);
+            if (BEST && threadIdx.x == 0) s_least[turn] = frame_best_score(a.frame_best + W.frame);
             __syncthreads();
             cur_frame = W.frame;
         }
@@ -1190,11 +1222,50 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
             btt = bto = INFINITY;
             bv0 = 0.0f;
         }
+        // The tile's points that are worth evaluating, slot list[k] in lane k:
+        // all of them, or, where only the frame's best is asked for, those
+        // within some variant's reach whose score with an open goal and the
+        // greatest margin is not below the best found so far (the score's
+        // roundings are monotone in both terms).  Every wave forms the same
+        // list.
+        int n_list = npts, list = 0;
+        float least = -INFINITY;
+        uint32_t others = 0u;
+        if (BEST) {
+            least = s_least[turn];
+            const int p = (pk + (l / CH) * Tw) * CH + (l & (CH - 1));
+            const int j = (int)((unsigned)p / (unsigned)W.nx), i = p - j * W.nx;
+            const float cx = W.h * ((float)(W.i0 + i) - W.halfNx);
+            const float cy = W.h * ((float)(W.j0 + j) - W.halfNy);
+            const float ex = cx - unif(S.bx), ey = cy - unif(S.by);
+            const float reach =
+                wave_max_pos(l < n_var ? (float)S.vc[l].D : 0.0f) * (1.0f + 1.0f / 65536.0f);
+            const bool in = l < npts && hsqrt(fmaf(ex, ex, ey * ey)) <= reach &&
+                            score_bound(fresh_args<SearchLaunch>().a.P, cx, cy) >= least;
+            const unsigned long long m = __ballot(in);
+            n_list = __builtin_popcountll(m);
+            const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            list = __builtin_amdgcn_ds_permute((in ? before : n_list + l - before) << 2, l);
+            turn ^= 1;
+            if (n_list == 0) {
+                if (threadIdx.x == 0) {
+                    s_least[turn] = least;
+                    const TileRec none = {0ull, INFINITY, INFINITY, 0.0f, 0.0f};
+                    args.tile_rec[t] = none;
+                }
+                continue;
+            }
+            if (threadIdx.x == 0)
+                others = __hip_atomic_load(args.frame_best + W.frame, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+        }
         // the wave's points in pairs of neighbours, slots s0 and s0 + 1, one
         // per half of the wave (a lone last point is taken by both halves,
         // which write the same values)
-        for (int s0 = 2 * w; s0 < npts; s0 += 2 * nw) {
-            const int slot = min(s0 + h, npts - 1);
+        for (int s0 = 2 * w; s0 < n_list; s0 += 2 * nw) {
+            const int k = min(s0 + h, n_list - 1);
+            const int slot = BEST ? __builtin_amdgcn_ds_bpermute(k << 2, list) : k;
             const int p = (pk + (slot / CH) * Tw) * CH + (slot & (CH - 1));
             const int j = (int)((unsigned)p / (unsigned)W.nx), i = p - j * W.nx;
             const float mi = (float)(W.i0 + i) - W.halfNx;
@@ -1274,7 +1345,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
                 }
                 if (reduced) {
                     pkey = key > pkey ? key : pkey;
-                } else if (v < n_var) {
+                } else if (!BEST && v < n_var) {
                     OS[vid * TP + slot] = sc;
                     OM[vid * TP + slot] = (uint8_t)feas[c];
                     const int64_t e = W.out_base + (int64_t)vid * W.npts + p;
@@ -1301,8 +1372,15 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
         // waves' best passes
         if (!args.wg_records) wave_best(O, w, bkey, btt, bto, bv0);
         __syncthreads();
-        if (!args.wg_records && w == 0) group_best(O, nw, args.tile_rec + t);
-        if (!reduced) {
+        if (!args.wg_records && w == 0) {
+            const uint32_t found = (uint32_t)(group_best(O, nw, args.tile_rec + t) >> 32);
+            if (BEST && l == 0) {
+                if (found > others) atomicMax(args.frame_best + W.frame, found);
+                others = max(others, found);
+                s_least[turn] = others ? fmaxf(least, unordered_bits(others)) : least;
+            }
+        }
+        if (!reduced && !BEST) {
             // one variant's piece of one chunk per thread: four scores in one
             // store and their flags in another (the last chunk of the window
             // may be short)
@@ -1469,11 +1547,14 @@ static int launch_kpl(const SearchLaunch &s, int waves_per_wg, int grid, hipStre
         const size_t lds = search_lds_bytes(KPL * 64, waves_per_wg, a.tile_points,
                                             a.max_variants);
         if (a.power)
-            hipLaunchKernelGGL((search_kernel<2 * KPL, true>), dim3(grid), dim3(64 * waves_per_wg),
-                               lds, st, s);
+            hipLaunchKernelGGL((search_kernel<2 * KPL, true, false>), dim3(grid),
+                               dim3(64 * waves_per_wg), lds, st, s);
+        else if (a.frame_best)
+            hipLaunchKernelGGL((search_kernel<2 * KPL, false, true>), dim3(grid),
+                               dim3(64 * waves_per_wg), lds, st, s);
         else
-            hipLaunchKernelGGL((search_kernel<2 * KPL, false>), dim3(grid), dim3(64 * waves_per_wg),
-                               lds, st, s);
+            hipLaunchKernelGGL((search_kernel<2 * KPL, false, false>), dim3(grid),
+                               dim3(64 * waves_per_wg), lds, st, s);
     }
     if (e1) (void)hipEventRecord(e1, st);
     if (a.n_frames > 0)
@@ -2532,10 +2613,10 @@ int search_occupancy(int K, int waves_per_wg, int tile_points, int max_variants)
     const int bs = 64 * waves_per_wg;
     const size_t lds = search_lds_bytes(K, waves_per_wg, tile_points, max_variants);
     switch (K / 64) {
-    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<2, false>, bs, lds); break;
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<4, false>, bs, lds); break;
-    case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<6, false>, bs, lds); break;
-    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<8, false>, bs, lds); break;
+    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<2, false, false>, bs, lds); break;
+    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<4, false, false>, bs, lds); break;
+    case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<6, false, false>, bs, lds); break;
+    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<8, false, false>, bs, lds); break;
     default: break;
     }
     return e == hipSuccess && n > 0 ? n : 1;

@@ -71,6 +71,7 @@ struct dpps_mlp {
     int32_t *fmap;
     int32_t *fcount;
     uint32_t *fcounter;
+    uint32_t *frame_best;      // greatest score so far by frame, re-score then fallback
     int32_t *h_count = nullptr;  // pinned landing word of the fallback count
     float *h_params = nullptr;   // pinned buffer of the real parameters (first use)
 };
@@ -316,6 +317,7 @@ int dpps_mlp_create(dpps_ctx *c, int32_t max_frames, int32_t max_k, uint64_t see
     size_t off_fmap = carve(off, R * sizeof(int32_t));
     size_t off_fcnt = carve(off, 256);
     size_t off_fctr = carve(off, 256);
+    size_t off_fbest = carve(off, 2 * R * sizeof(uint32_t));
     if (c->p.hbm_budget_bytes && c->budget_used + off > c->p.hbm_budget_bytes) {
         delete m;
         return fail(DPPS_E_BUDGET, "network needs %zu device bytes", off);
@@ -358,6 +360,7 @@ int dpps_mlp_create(dpps_ctx *c, int32_t max_frames, int32_t max_k, uint64_t see
     m->fmap = (int32_t *)(A + off_fmap);
     m->fcount = (int32_t *)(A + off_fcnt);
     m->fcounter = (uint32_t *)(A + off_fctr);
+    m->frame_best = (uint32_t *)(A + off_fbest);
     if (hipMemset(m->arena, 0, off) != hipSuccess) {
         dpps_mlp_destroy(m);
         return fail(DPPS_E_DEVICE, "hipMemset failed");
@@ -554,6 +557,10 @@ int dpps_mlp_topk(dpps_mlp *m, int32_t n_frames, int32_t k, int32_t *d_cells, vo
 
 }  // extern "C"
 
+// The search may leave out points by the score that none of their passes can
+// exceed (LaunchArgs::frame_best).
+static bool bounded_score(const DevParams &P) { return P.w_ang_pi >= 0.0f && P.w_margin >= 0.0f; }
+
 // Forward pass, top-k cells, re-score tables and the exact re-score of the
 // proposed windows (kernel launches only), best records into res.
 static int propose(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dpps_best *res,
@@ -574,6 +581,7 @@ static int propose(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dpps_best
     rt.wins = m->rw;
     rt.tiles = m->rt;
     rt.zero_word = m->fcount;  // the fallback list starts empty
+    rt.frame_best = m->frame_best;
     if (launch_topk(m->y, OUT_PAD, nf, OUT, k, m->cells, &rt, (void *)st))
         return fail(DPPS_E_DEVICE, "top-k launch failed");
     // exact re-score of the proposed windows: one 16-point tile per window
@@ -593,6 +601,7 @@ static int propose(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dpps_best
     a.tile_points = 16;
     a.persistent = 1;
     a.counter = m->rcounter;
+    if (bounded_score(c->P)) a.frame_best = m->frame_best;
     a.tile_rec = m->rrec;
     a.best = res;
     if (fallback) {
@@ -668,6 +677,7 @@ static int surrogate_core(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dp
     a.tile_points = FB_TILE;
     a.persistent = 1;
     a.counter = m->fcounter;
+    if (bounded_score(c->P)) a.frame_best = m->frame_best + nf;
     a.tile_rec = m->frec;
     a.best = d_best;
     a.max_variants = b->T.max_variants;

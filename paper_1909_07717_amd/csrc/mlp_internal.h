@@ -96,6 +96,7 @@ struct RescoreTables {
     WinDev *wins;
     TileDev *tiles;
     int32_t *zero_word;     // cleared by the kernel (may be NULL)
+    uint32_t *frame_best;   // 2 n_frames words cleared by the kernel (may be NULL)
 };
 // Top-k cells of each frame's map into out [n_frames][k]; with rt, also the
 // re-score tables of those cells.

@@ -1000,6 +1000,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) topk_kernel(const float *__restr
     }
     if (rt.frames) rescore_windows(rt, f, k, cell, scan_sh);
     if (rt.zero_word && f == 0 && threadIdx.x == 0) *rt.zero_word = 0;
+    if (rt.frame_best && threadIdx.x < 2) rt.frame_best[threadIdx.x * gridDim.x + f] = 0u;
 }
 
 // host launchers -------------------------------------------------------------
