@@ -1431,7 +1431,9 @@ __global__ void __launch_bounds__(256) finalize_kernel(SearchLaunch launch)
     if (f == 0 && tid < 8 && a.counter) a.counter[tid] = 0u;  // the search's 8 counters
     if (f == 0 && tid == 0 && a.count_host) *a.count_host = *a.n_frames_dev;
     if (a.n_frames_dev && f >= *a.n_frames_dev) return;
-    const FrameDev F = INL ? one.frame : a.frames[f];
+    // (by reference: a copy is kept in private memory, and the kernel takes 17
+    // us instead of 5 over 256 frames)
+    const FrameDev &F = INL ? one.frame : a.frames[f];
     // the frame's tile records, or one record per workgroup of a one-frame
     // launch
     const int rc = a.wg_records ? a.wg_records : F.tile_count;
