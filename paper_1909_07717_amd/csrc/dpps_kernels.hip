@@ -1073,8 +1073,12 @@ __device__ __forceinline__ int window_words(const LaunchArgs &a, bool inl, int w
 // 8 variants, K = 128, 3.40 ms instead of 4.42; passing power 96 us instead of 122.
 // At most 128 VGPRs, so four waves fit on each SIMD; K = 128 fits in 96 and runs
 // five (256 windows 3.56 -> 3.39 ms; at K = 64 five were slower for one small
-// frame, 16.2 -> 19.0 us, and K >= 192 does not fit).  POWER: one flat pass
-// per point at the point's own passing power (Eq. 1-2).
+// frame, 16.2 -> 19.0 us, and K >= 192 does not fit).  With tiles by
+// request and runs of tiles the same launches take 115 us, 3.37 ms and 93 us.
+// POWER: one flat pass per point at the point's own passing power (Eq. 1-2).
+// BEST: only the best record is asked for, and points that cannot hold it are
+// left out (1000 frames of 64 windows of 16 points, one flat kick: 940 -> 457
+// us, their exact fallback of 18 frames 710 -> 486).
 template <int KPH, bool POWER, bool BEST>
 __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLaunch launch)
 {
@@ -1112,14 +1116,18 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
     // Several frames: a run of consecutive tiles (three quarters of the even
     // share: frames differ in cost), then groups of `claim` tiles, so that a
     // workgroup stages few frames; the chunks of a run fill whole lines by
-    // themselves.
+    // themselves.  BEST: a quarter, since frames with a poor best leave few
+    // points out and cost many times the others, then 8 tiles of 16 points or
+    // one of 64 (1000 frames of 64 windows: 631 us with three quarters and
+    // groups of 3, 457 this way, 472 with an eighth, 593 with groups of 4;
+    // 18 whole lattices: 486 with one tile a claim, 526 with 4).
     const int C = min(G, 8), xcd = (int)((unsigned)b % (unsigned)C);
     const bool runs = args.persistent && args.n_frames > 1;
     const int even = n_tiles / G;
-    const int n_own = !args.persistent ? 1 : runs ? even - (even + 3) / 4 : max(even - 1, 0);
+    const int n_own = !args.persistent ? 1 : runs ? (BEST ? even / 4 : even - (even + 3) / 4) : max(even - 1, 0);
     const int first = runs ? b * n_own : b, stride = runs ? 1 : G;
     const int n_static = n_own * G;
-    const int claim = min(max(even / 16, 1), 8);
+    const int claim = BEST ? (even >= 32 ? 8 : 1) : min(max(even / 16, 1), 8);
     // the lane's best pass of the tile, or of all the workgroup's tiles with
     // one record per workgroup
     unsigned long long bkey = 0ull;
