@@ -2413,17 +2413,20 @@ __device__ __forceinline__ double slab_enter(double cx, double cy, double dx, do
 }
 
 // What the points of a zone share: the opponents (bit o) that can be the
-// earliest at some point of the defense area, and those within the marking
+// earliest at some place that P or Q can take, and those within the marking
 // radius of some point of the zone.
 struct RunZone {
     uint32_t guard, mark;
 };
 
-// Lanes are opponents.  P and Q lie in the (closed) defense area, so an
-// opponent whose arrival bound over the whole area is past the latest arrival
-// of another one anywhere in it never sets t_P or t_Q.  With D the least and
-// E the greatest distance to the area (widened by 1 mm for the rounding of P
-// and Q), less the radius, both scaled by amax: whatever its velocity the
+// Lanes are opponents.  P and Q lie in the rectangle as deep as the defense
+// area and as wide as the area or the goal, whichever is wider (a segment that
+// passes a narrow area by ends at a post beside it), so an opponent whose
+// arrival bound over that rectangle is past the latest arrival of another one
+// anywhere in it never sets t_P or t_Q.  With D the least and E the greatest
+// distance to the rectangle (widened by 1 mm, and by 2^-20 of its coordinates
+// and the robot's, for the rounding of P and Q and of the differences), less
+// the radius, both scaled by amax: whatever its velocity the
 // robot needs at least sqrt(D / 2) (D <= vmax^2 / 2) or D / 2vmax + vmax / 4,
 // and at most the time when it first stops moving away at its full speed,
 // |w| / sqrt 2 + R(|w|^2 + E), in the robot stage's units; 2^-12 apart for
@@ -2435,11 +2438,14 @@ __device__ __forceinline__ RunZone run_zone(const StageLDS &S, const DevParams &
 {
     const int l = lane_id();
     const float4 r = S.rob[n_tm + (l < n_op ? l : 0)];
-    const float x0 = P.goal_x - R.def_depth, x1 = P.goal_x, hw = 0.5f * R.def_width;
+    const float x0 = P.goal_x - R.def_depth, x1 = P.goal_x;
+    const float hw = fmaxf(0.5f * R.def_width, P.half_goal_w);
+    const float wide = 1e-3f + (fabsf(x0) + fabsf(x1) + hw + fabsf(r.x) + fabsf(r.y)) *
+                                   (1.0f / 1048576.0f);
     const float nx = fmaxf(fmaxf(x0 - r.x, r.x - x1), 0.0f), nyd = fmaxf(fabsf(r.y) - hw, 0.0f);
     const float fx = fmaxf(fabsf(r.x - x0), fabsf(r.x - x1)), fy = fabsf(r.y) + hw;
-    const float D = P.A * fmaxf(hsqrt(fmaf(nx, nx, nyd * nyd)) - 1e-3f - P.R, 0.0f);
-    const float E = P.A * (hsqrt(fmaf(fx, fx, fy * fy)) + 1e-3f);
+    const float D = P.A * fmaxf(hsqrt(fmaf(nx, nx, nyd * nyd)) - wide - P.R, 0.0f);
+    const float E = P.A * (hsqrt(fmaf(fx, fx, fy * fy)) + wide);
     const float w2 = fminf(0.5f * fmaf(r.z, r.z, r.w * r.w), 0.5f * P.V2);
     const float F = w2 + E;
     float lb = D <= 0.5f * P.V2 ? hsqrt(0.5f * D) : fmaf(D, P.inv2V, 0.25f * P.V);

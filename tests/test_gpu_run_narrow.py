@@ -1,0 +1,83 @@
+"""Running points with a defense area narrower than the goal, where the
+segments to the posts can end beside the area, and opponents at the goal mouth.
+An opponent left out of a zone must not change what a point scores: adding
+opponents lowers the guard time and the marking criterion of a frame to no
+more than each opponent alone gives (the same sums of minima, compared without
+tolerance), and the marking criterion to exactly the least of them."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_1909_07717_amd.framegen import Params, random_frame
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+GUARD = dict(w_goal=0.0, w_ball=0.0, w_angle=0.0, w_guard=1.0, w_defense=0.0)
+MARK = dict(w_goal=0.0, w_ball=0.0, w_angle=0.0, w_guard=0.0, w_defense=1.0)
+AREAS = [(0.0, 0.0), (0.0, 0.3), (0.0, 1.2), (0.2, 0.0), (0.2, 0.4), (0.2, 1.1), (1.2, 0.0),
+         (1.2, 0.4), (1.2, 1.2), (1.2, 2.4)]
+
+
+def mouth_frame(seed, params):
+    """Opponents at the goal's centre, at its posts and around, some moving."""
+    rng = np.random.default_rng(seed)
+    f = random_frame(rng, 3, 6)
+    g = 0.5 * params.goal_width
+    f.opp[0] = (params.goal_x, 0.0, 0.0, 0.0)
+    f.opp[1] = (params.goal_x, g, 0.0, 0.0)
+    f.opp[2] = (params.goal_x - 0.1, -g - 0.05, 0.0, 0.0)
+    f.opp[3:5, 0] = params.goal_x - rng.uniform(0.0, 1.5, 2)
+    f.opp[3:5, 1] = rng.uniform(-1.5, 1.5, 2)
+    if seed % 2:
+        f.opp[3:, 2:] = 0.0
+    f.opp = f.opp.astype(np.float32)
+    f.windows = [(float(np.float32(0.1)), 0, 0, 121, 91), (float(np.float32(0.1)), 100, 20, 21, 51)]
+    return f
+
+
+def _scores(s, frame, run):
+    best, sc = s.running_points([frame], **run)
+    torch.cuda.synchronize()
+    return sc.cpu().numpy()
+
+
+@pytest.mark.parametrize("depth,width", AREAS)
+def test_no_opponent_is_lost(depth, width):
+    from paper_1909_07717_amd import binding as B
+    p = Params(n_samples=64).as_f32()
+    s = B.Searcher(p)
+    area = dict(def_depth=depth, def_width=width, guard_norm=8.0, mark_radius=2.0)
+    for seed in range(3):
+        print(f"[narrow] depth={depth} width={width} seed={seed}", flush=True)
+        f = mouth_frame(seed, p)
+        guard, mark = _scores(s, f, dict(area, **GUARD)), _scores(s, f, dict(area, **MARK))
+        least_g, least_m = np.full_like(guard, np.inf), np.full_like(mark, np.inf)
+        for o in range(len(f.opp)):
+            one = f.copy()
+            one.opp = f.opp[o:o + 1].copy()
+            least_g = np.minimum(least_g, _scores(s, one, dict(area, **GUARD)))
+            least_m = np.minimum(least_m, _scores(s, one, dict(area, **MARK)))
+        assert (guard <= least_g).all(), (seed, float((guard - least_g).max()))
+        assert np.array_equal(mark, least_m)
+    s.close()
+
+
+@pytest.mark.parametrize("width", [0.0, 0.3, 1.1, 1.2, 2.4])
+def test_area_without_depth_matches_oracle(width):
+    """P and Q are the posts: every score against the oracle's criteria."""
+    from paper_1909_07717_amd import binding as B
+    p = Params(n_samples=64).as_f32()
+    s = B.Searcher(p)
+    area = dict(def_depth=0.0, def_width=width)
+    for seed in range(3):
+        print(f"[narrow] oracle width={width} seed={seed}", flush=True)
+        f = mouth_frame(10 + seed, p)
+        got = _scores(s, f, area)
+        run = {k: float(np.float32(v)) for k, v in dict(O.RUN_DEFAULTS, **area).items()}
+        o = O.run_search(f, p, **run)
+        want = np.asarray(o["score"], np.float64)
+        assert np.array_equal(np.isneginf(got), np.isneginf(want))
+        fin = np.isfinite(want) & (np.asarray(o["ambig"]) == 0)
+        assert np.abs(got[fin] - want[fin]).max() <= 1e-5
+    s.close()
