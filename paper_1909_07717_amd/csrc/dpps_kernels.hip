@@ -47,7 +47,9 @@ namespace dpps {
 // row of K, and 32 floats so that the halves' rows start in different banks.
 constexpr int half_rows(int K) { return 2 * K + 32; }
 
-// Dynamic LDS of the ray kernel: PM_ROWS rows of K floats per wave.
+// Dynamic LDS of the ray kernel: PM_ROWS rows of K floats per wave.  (Both
+// kernels' dynamic LDS is read as 16-byte words: it is declared on 16 bytes,
+// which pads the static LDS before it.)
 static size_t pm_bytes(int K, int waves) { return (size_t)waves * PM_ROWS * K * sizeof(float); }
 
 // The kernel's arguments, read anew from the kernarg segment: the laundered
@@ -1087,7 +1089,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
     __shared__ OutLDS O;
     // dynamic: each wave's running maxima (two rows of K for each half), its
     // path frames of two points, the tile's staged score and mask maps
-    extern __shared__ float PMX[];
+    extern __shared__ __attribute__((aligned(16))) float PMX[];
     __shared__ int s_tile;
     __shared__ float s_least[2];  // least score worth finding (this tile's, the next's)
     const int nw = blockDim.x >> 6;
@@ -1095,6 +1097,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
     const int l = lane_id();
     const int TP = args.tile_points;
     constexpr int K = KPH * 32, HROWS = half_rows(K);
+    static_assert(HROWS % 4 == 0, "the rows keep the entries behind them on 16 bytes");
     const int h = l >> 5, hl = l & 31;  // half of the wave, lane in it
     float4 *const PR = (float4 *)(PMX + nw * 2 * HROWS);
     float *const OS = (float *)(PR + nw * 2 * PR_ENTRIES);
@@ -1886,7 +1889,7 @@ __global__ void __launch_bounds__(512, 4) ray_kernel(RayArgs args)
 {
     __shared__ StageLDS S;
     __shared__ float4 PR[MAX_WAVES][PR_ENTRIES];
-    extern __shared__ float PMX[];
+    extern __shared__ __attribute__((aligned(16))) float PMX[];
     __shared__ RayRec WB[MAX_WAVES];
     __shared__ int s_tile;
     __shared__ int s_dir;  // next unclaimed direction slot of the tile
