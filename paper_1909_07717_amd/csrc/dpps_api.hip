@@ -708,25 +708,14 @@ int dpps_get_launch(const dpps_ctx *c, int32_t *tile_points, int32_t *waves_per_
 // instructions and two barriers beside its points (a pair of points: 1000 to
 // 2500), while the last round needs tiles to spread: the full frame (43 621
 // points) runs 118 us at 8 points and 116 at 16, the passing power of the same
-// points 95 and 91, 16 mixed requests (307 000 points) 461 at 8 and 400 at 64.  Malformed requests get the default
-// and are refused by build_tables.
-static int request_tile(const dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
-                        const dpps_window *windows)
+// points 95 and 91, 16 mixed requests (307 000 points) 461 at 8 and 400 at 64.
+// Taken from checked tables: an unchecked frame's window count says nothing
+// about how many windows there are to read.
+static int request_tile(const dpps_ctx *c, const HostTables &T)
 {
-    if (c->tile_set || n_frames < 1 || !frames || !windows) return c->tile_points;
-    int64_t pts = 0;
-    int nv = 1;
-    for (int32_t f = 0; f < n_frames; ++f) {
-        const dpps_frame &F = frames[f];
-        if (F.n_windows < 0 || F.window_off < 0) return c->tile_points;
-        for (int w = 0; w < F.n_windows; ++w) {
-            const dpps_window &W = windows[F.window_off + w];
-            if (W.nx > 0 && W.ny > 0) pts += (int64_t)W.nx * W.ny;
-        }
-        if (F.n_variants > nv) nv = F.n_variants;
-    }
+    if (c->tile_set) return c->tile_points;
     for (int tp = 64; tp > c->tile_points; tp /= 2)
-        if (pts >= (int64_t)10 * c->n_cu * tp && tp * nv <= 2048) return tp;
+        if (T.points >= (int64_t)10 * c->n_cu * tp && tp * T.max_variants <= 2048) return tp;
     return c->tile_points;
 }
 
@@ -753,11 +742,11 @@ int stage_batch(dpps_ctx *c, dpps_batch *b, int32_t n_frames, const dpps_frame *
                 const dpps_robot *robots, const dpps_window *windows,
                 const dpps_variant *variants, OneFrame &one, hipStream_t st)
 {
-    const int tp = request_tile(c, n_frames, frames, windows);
-    int rc = build_tables(&c->p, n_frames, frames, robots, windows, variants, tp, b->T);
+    int rc = build_tables(&c->p, n_frames, frames, robots, windows, variants, 0, b->T);
     if (rc) return rc;
     b->n_frames = n_frames;
-    b->tile_points = tp;
+    b->tile_points = request_tile(c, b->T);
+    retile(b->T, b->tile_points);
     return stage_or_carry(c, b, one, st);
 }
 
