@@ -71,6 +71,31 @@ int check_params(const dpps_params *p)
     return DPPS_OK;
 }
 
+// Arrival limits: how far past the slowest reaching kick's own time they lie,
+// and by how much (relative) that kick has to be faster than any that is met
+// there.  A limit without this margin is set past any arrival, so that nothing
+// is left out (a finite number: it is multiplied by the root of a length, 0 at
+// the ball).
+// The margin is 1 % and more for the usual ball (0.6 % at a slide ratio of 0.2,
+// 0.09 % at 0.03, when the slide ends near the third quarter's end) and has no
+// bound of its own as the ratio falls; the kernels' float32 inversions err by
+// 3e-7 at most at the limits over slide ratios of 1e-4 to 1, decelerations of
+// 1e-4 to 200 and chips of 0.02 to 1.57 rad.
+constexpr double LIMIT_FACTOR = 1.03, LIMIT_MARGIN = 1.0 / 4096.0;
+constexpr float NO_LIMIT = 1e30f;
+
+// Kick speed that is at distance s at time T (the kernels' inversion, in
+// float64): the kick that stops there, the one still sliding (flying) there, or
+// the one rolling.
+static double critical_speed(double s, double T, double icA, double icB, double D, double alpha,
+                             double beta, double ar, double hfast, double pfast)
+{
+    const double T2 = T * T, Q = s + 0.5 * ar * T2;
+    if (icA * s <= T2) return sqrt(s / D);
+    if (icB * s >= T2) return (s + hfast * T2) / (pfast * T);
+    return Q / (0.5 * beta * T + sqrt(fmax(alpha * Q + 0.25 * beta * beta * T2, 0.0)));
+}
+
 DevParams derive(const dpps_params *p)
 {
     DevParams P;
@@ -130,12 +155,17 @@ DevParams derive(const dpps_params *p)
         const double tf = s <= d1 ? 2.0 * s / (v + sqrt(fmax(v * v - 2.0 * as * s, 0.0)))
                                   : k1 * v + 2.0 * (s - d1) /
                                         (w + sqrt(fmax(w * w - 2.0 * ar * (s - d1), 0.0)));
-        const double u = lam2 / sqrt(ccD), tl = lam3 / sqrt(ccD), sf = lam1 / ccD;
+        const double vc = 1.0 / sqrt(ccD), u = lam2 * vc, tl = lam3 * vc, sf = lam1 * vc * vc;
         const double tc = s <= sf ? s / u
                                   : tl + 2.0 * (s - sf) /
                                         (u + sqrt(fmax(u * u - 2.0 * ar * (s - sf), 0.0)));
-        P.f_lim[q] = (float)(1.03 * 0.5 * A * tf);
-        P.c_lim[q] = (float)(1.03 * 0.5 * A * tc);
+        const double Tf = LIMIT_FACTOR * tf, Tc = LIMIT_FACTOR * tc;
+        const double mf = 1.0 - critical_speed(s, Tf, cTs * cTs / cD, 1.0 / (1.0 / k1 - 0.5 * as),
+                                               cD, fal, fbe, ar, 0.5 * as, 1.0) / v;
+        const double mc = 1.0 - critical_speed(s, Tc, ccTs * ccTs / ccD, lam3 / lam2, ccD, cal,
+                                               cbe, ar, 0.0, lam2) / vc;
+        P.f_lim[q] = q == 3 || mf >= LIMIT_MARGIN ? (float)(0.5 * A * Tf) : NO_LIMIT;
+        P.c_lim[q] = q == 3 || mc >= LIMIT_MARGIN ? (float)(0.5 * A * Tc) : NO_LIMIT;
     }
     P.margin_cap = p->margin_cap_s;
     P.w_ang_pi = (float)(p->w_angle / M_PI);

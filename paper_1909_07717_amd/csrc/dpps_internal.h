@@ -38,7 +38,7 @@ struct DevParams {
     float half_ar;
     // 1.03 times the ball's time (robot stage units, A T / 2) to the end of each
     // quarter of a path of length 1 m for the slowest kick that gets to its
-    // end; times scale with the square root of the length
+    // end; times scale with the square root of the length.  1e30: no limit
     float f_lim[4], c_lim[4];
     // scoring
     float margin_cap, w_ang_pi, w_dist, inv_dist_norm, w_margin;

@@ -369,9 +369,10 @@ __device__ __forceinline__ uint32_t robots_needed(const float4 *pr, bool split, 
 // is no earlier meets only slower kicks there, which no reachable variant
 // is, so minima at or past the limit may stay later than they would be and
 // every reachable variant's first crossing is still the same (critical speeds
-// at the limit are at least 1 % below that slowest kick; in the last quarter
-// the limit is past its stop, where the critical speed does not depend on
-// the arrival any more).  Pass +inf where the minima themselves are used.
+// at the limit are below that slowest kick by 2^-12 at least, or there is no
+// limit; in the last quarter it is past its stop, where the critical speed does
+// not depend on the arrival any more).  Pass +inf where the minima themselves
+// are used.
 template <int KPL, bool CLAMP, int MODE>
 __device__ __forceinline__ void robot_stage(const float4 *pr, const RobotK &P, int j0, int n,
                                             bool split, float lim, float lim_other,
