@@ -479,9 +479,10 @@ int dpps_shot_decision(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
  *      over ang_fall outside it;
  *   x4 the opponents' guard time: the segments from c to the two goal posts
  *      first meet the defense area (def_depth deep, def_width wide, in front
- *      of the goal) at P and Q; with t_P, t_Q the earliest opponent arrivals
- *      there (the robot model of dpps_search), min((t_P + t_Q) / guard_norm, 1),
- *      1 without opponents;
+ *      of the goal) at P and Q, or end there at the post where an area
+ *      narrower than the goal is passed by; with t_P, t_Q the earliest opponent
+ *      arrivals there (the robot model of dpps_search),
+ *      min((t_P + t_Q) / guard_norm, 1), 1 without opponents;
  *   x5 avoiding the defense: every opponent nearer to the ball than c marks
  *      c with weight max(0, 1 - |o - c| / mark_radius); 1 - the largest mark.
  * A point strictly inside the defense area cannot be used (score -inf).  The

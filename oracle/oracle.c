@@ -1004,8 +1004,8 @@ typedef struct {
 
 /* First point of the segment from (cx, cy) to (ex, ey) inside the closed
  * rectangle [x0, x1] x [y0, y1], by intersecting the segment with each edge
- * line and keeping the nearest crossing that lies on the edge (the end point
- * is inside by construction). */
+ * line and keeping the nearest crossing that lies on the edge; the end point
+ * where there is none (it lies in the rectangle, or that is passed by). */
 static void seg_enter_rect(double cx, double cy, double ex, double ey, double x0, double x1,
                            double y0, double y1, double *px, double *py)
 {

@@ -81,3 +81,31 @@ def test_area_without_depth_matches_oracle(width):
         fin = np.isfinite(want) & (np.asarray(o["ambig"]) == 0)
         assert np.abs(got[fin] - want[fin]).max() <= 1e-5
     s.close()
+
+
+@pytest.mark.parametrize("depth,width", [(d, w) for d in (0.0, 0.2, 1.2)
+                                         for w in (0.0, 0.4, 1.1, 1.2, 1.3)])
+def test_narrow_area_matches_oracle(depth, width):
+    """P and Q on the area's edges where the segments meet it, else the posts.
+    Points with an opponent that P or Q leaves at its radius to 0.2 mm are not
+    compared: the arrival is a square root there, which float32 offsets of
+    5e-7 m move by up to 1e-3 s."""
+    from paper_1909_07717_amd import binding as B
+    p = Params(n_samples=64).as_f32()
+    s = B.Searcher(p)
+    area = dict(def_depth=depth, def_width=width, w_guard=1.0, guard_norm=4.0)
+    for seed in range(4):
+        print(f"[narrow] oracle depth={depth} width={width} seed={seed}", flush=True)
+        f = mouth_frame(20 + seed, p)
+        got = _scores(s, f, area)
+        run = {k: float(np.float32(v)) for k, v in dict(O.RUN_DEFAULTS, **area).items()}
+        o = O.run_search(f, p, **run)
+        want = np.asarray(o["score"], np.float64)
+        assert np.array_equal(np.isneginf(got), np.isneginf(want))
+        fin = np.isfinite(want) & (np.asarray(o["ambig"]) == 0)
+        for x, y in ((o["px"], o["py"]), (o["qx"], o["qy"])):
+            for r in f.opp.astype(np.float64):
+                fin &= np.abs(np.hypot(r[0] - x, r[1] - y) - p.robot_radius) > 2e-4
+        assert fin.mean() > 0.9
+        assert np.abs(got[fin] - want[fin]).max() <= 1e-5
+    s.close()
