@@ -1120,18 +1120,31 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
     // Several frames: a run of consecutive tiles (three quarters of the even
     // share: frames differ in cost), then groups of `claim` tiles, so that a
     // workgroup stages few frames; the chunks of a run fill whole lines by
-    // themselves.  BEST: a quarter, since frames with a poor best leave few
-    // points out and cost many times the others, then 8 tiles of 16 points or
-    // one of 64 (1000 frames of 64 windows: 631 us with three quarters and
-    // groups of 3, 457 this way, 472 with an eighth, 593 with groups of 4;
-    // 18 whole lattices: 486 with one tile a claim, 526 with 4).
+    // themselves.
+    // BEST, small tiles (16 points): a pulled tile waits for the counter and
+    // then for its window and its frame, which cost more than the tile, so up to
+    // 11 tiles a workgroup are its own (30 frames of 128 windows: 168 us a call
+    // with one of 3.75 tiles its own, 115 with 3; 200 of 64: 350 and 253).
+    // Beyond, a quarter, since frames with a poor best leave few points out and
+    // cost many times the others (1000 of 64: the kernel took 631 us with three
+    // quarters, 457 with one, 472 with an eighth), then groups of as many, up to
+    // 8 (300 of 64: 476 us a call with single tiles, 294 with 4; 1000 of 64:
+    // groups of 4 593 us, of 8 457).
+    // BEST, large tiles (64 points, whole lattices): a quarter, at least one,
+    // then one tile each, or 8 from 32 tiles a workgroup on, where the last
+    // round weighs less than the pulls (9 lattices: 1 or 8 alike; 18: 486 us with
+    // 1, 526 with 4; 60: 2030 with 1, 1780 with 8; 200: 5550 and 3700).
     const int C = min(G, 8), xcd = (int)((unsigned)b % (unsigned)C);
     const bool runs = args.persistent && args.n_frames > 1;
     const int even = n_tiles / G;
-    const int n_own = !args.persistent ? 1 : runs ? (BEST ? even / 4 : even - (even + 3) / 4) : max(even - 1, 0);
+    const bool small = TP <= 16;
+    const int own = !BEST ? even - (even + 3) / 4
+                          : small && even < 12 ? even : max(even / 4, min(even, 1));
+    const int n_own = !args.persistent ? 1 : runs ? own : max(even - 1, 0);
     const int first = runs ? b * n_own : b, stride = runs ? 1 : G;
     const int n_static = n_own * G;
-    const int claim = BEST ? (even >= 32 ? 8 : 1) : min(max(even / 16, 1), 8);
+    const int claim = !BEST ? min(max(even / 16, 1), 8)
+                            : small ? min(max(even / 4, 1), 8) : even >= 32 ? 8 : 1;
     // the lane's best pass of the tile, or of all the workgroup's tiles with
     // one record per workgroup
     unsigned long long bkey = 0ull;
