@@ -2174,8 +2174,148 @@ __device__ __forceinline__ float shot_slack(const ShotLDS &H, const RobotK &rk, 
     return m;
 }
 
+// A lone position's decision (a frame's ball), by one wave from the staged
+// frame; the lanes of the record agree.  The same operations as the tiles'
+// below, but with the opponents' values in lanes instead of LDS rows (the loops
+// over them are lane reads, not waits for LDS), the quarters' bounds spread over
+// the lanes too and the samples over the whole wave.  Where only the balls are
+// asked for, the call waits for this chain and not for the ALUs: 10 balls at K =
+// 256 take 11.1 us as tiles of one, 7.2 this way (the call 16.0 and 13.8), 1000
+// balls 37.1 and 32.3 a call.
+template <int KPH, bool CLAMP>
+__device__ __forceinline__ float lone_slack(const RobotK &rk, const BallTime &bt, const float4 &fr,
+                                            float bound, int rank, int n_op, float Lf, float LA,
+                                            float D, float invA2)
+{
+    const int l = lane_id();
+    float fs[KPH / 2], tb[KPH / 2];
+#pragma unroll
+    for (int q = 0; q < KPH / 2; ++q) {
+        fs[q] = (float)(q * 64 + l + 1) * (1.0f / (float)(KPH * 32));
+        const float sk = fs[q] * Lf;
+        const float t = bt.at(sk);
+        tb[q] = sk <= D ? t : -INFINITY;  // past the ball's reach: no slack
+    }
+    float m = INFINITY;
+    for (int j = 0; j < n_op; ++j) {
+        const int o = __builtin_ctzll(__ballot(l < n_op && rank == j));
+        const float4 r = make_float4(readlane_f(fr.x, o), readlane_f(fr.y, o), readlane_f(fr.z, o),
+                                     readlane_f(fr.w, o));
+#pragma unroll
+        for (int q = 0; q < KPH / 2; ++q)
+            m = fminf(m, robot_time_h<CLAMP>(r, fs[q], LA, rk) * invA2 - tb[q]);
+        m = wave_min_dpp(m);
+        if (__ballot(l < n_op && rank > j && bound < m) == 0ull) break;
+    }
+    return m;
+}
+
+template <int KPH>
+__device__ __forceinline__ dpps_shot shot_lone(const StageLDS &S, const DevParams &P, double cx,
+                                               double cy, float min_angle, float margin)
+{
+    const int l = lane_id();
+    const int n_tm = uni(S.n_tm), n_op = uni(S.n_op);
+    // shadows: lanes are opponents, then the posts
+    const float fx = (float)cx, fy = (float)cy;
+    const float dxf = fmaxf(P.goal_x - fx, P.goal_eps);
+    const float4 r = S.rob[n_tm + (l < n_op ? l : 0)];
+    const float ox = r.x - fx, oy = r.y - fy;
+    const float Y = l < n_op ? oy : (l == n_op ? -P.half_goal_w - fy : P.half_goal_w - fy);
+    const float X = l < n_op ? ox : dxf;
+    const float ang = atan2f(Y, X);
+    const float lo = readlane_f(ang, n_op), hi = readlane_f(ang, n_op + 1);
+    const bool valid = l < n_op && r.x < P.goal_x;
+    const float rho2 = fmaf(ox, ox, oy * oy);
+    const bool blocked = __ballot(valid && rho2 <= P.R * P.R) != 0ull;
+    const float al = asinf(fminf(P.R * rsq(fmaxf(rho2, 1e-30f)), 1.0f));
+    const float s = fmaxf(ang - al, lo), e = fminf(ang + al, hi);
+    const bool has = valid && e > s;
+    // the gap behind each shadow, and (lane n_op) above the lower post
+    const float st = l < n_op ? e : lo;
+    bool cov = false;
+    float nxt = hi;
+    for (unsigned long long m = __ballot(has); m; m &= m - 1) {
+        const int k = __builtin_ctzll(m);
+        const float sk = readlane_f(s, k), ek = readlane_f(e, k);
+        cov = cov || (sk <= st && ek > st);
+        nxt = sk > st ? fminf(nxt, sk) : nxt;
+    }
+    const float w = (has || l == n_op) && !cov && !blocked ? fmaxf(nxt - st, 0.0f) : 0.0f;
+    // widest gap (ties to the lower start) and the sum of the gaps
+    float gap = 0.0f, g0 = lo, open = 0.0f;
+    for (unsigned long long m = __ballot(w > 0.0f); m; m &= m - 1) {
+        const int k = __builtin_ctzll(m);
+        const float wk = readlane_f(w, k), sk = readlane_f(st, k);
+        open += wk;
+        if (wk > gap || (wk == gap && sk < g0)) {
+            gap = wk;
+            g0 = sk;
+        }
+    }
+    const double dxg = fmax((double)P.goal_x - cx, (double)P.goal_eps);
+    const float aim = gap > 0.0f ? fmaf(0.5f, gap, g0) : atan2f(-fy, (float)dxg);
+    const double ux = (double)cosf(aim), uy = (double)sinf(aim);
+    const double L = dxg / ux;
+    const float Lf = (float)L;
+    const VarConst &vc = S.vc[0];  // the shot: the frame's only variant
+    const BallTime bt(vc);
+    const float D = unif((float)vc.D);
+    // lane (o, k): opponent o's bound over quarter k, then the least over k
+    const int o = l & 15;
+    const float k = (float)(l >> 4);
+    const float s1 = fminf(0.25f * (k + 1.0f) * Lf * (1.0f + 1.0f / 1048576.0f), D);
+    const bool in = 0.25f * k * Lf * (1.0f - 1.0f / 1048576.0f) <= D;
+    const float tb = in ? bt.at(s1) * (1.0f + 1.0f / 65536.0f) : -INFINITY;
+    const RobotK rk(P);
+    const double LA = L * (double)P.A, q0 = 0.25 * LA * (double)k;
+    double tq, qq, wn;
+    const float4 fr = robot_frame(S.rob[n_tm + (o < n_op ? o : 0)], (double)P.A, cx, cy, ux, uy, tq,
+                                  qq, wn);
+    const float lb = arrival_bound(rk, tq, qq, fr.z, (float)wn, q0, q0 + 0.25 * LA);
+    float bd = fmaf(lb * (1.0f - 1.0f / 65536.0f), P.invA2, -tb);
+    bd = fminf(bd, __shfl_xor(bd, 16, 64));
+    bd = fminf(bd, __shfl_xor(bd, 32, 64));
+    const uint32_t key = ordered_bits(bd);
+    int rank = 0;
+    for (int j = 0; j < n_op; ++j) {
+        const uint32_t y = (uint32_t)readlane_i((int)key, j);
+        rank += y < key || (y == key && j < o);
+    }
+    const float m =
+        uni(S.vel_ok)
+            ? lone_slack<KPH, false>(rk, bt, fr, bd, rank, n_op, Lf, (float)LA, D, P.invA2)
+            : lone_slack<KPH, true>(rk, bt, fr, bd, rank, n_op, Lf, (float)LA, D, P.invA2);
+    dpps_shot res;
+    res.reachable = L <= vc.D;
+    res.aim = aim;
+    res.gap = gap;
+    res.open_angle = open;
+    res.length = Lf;
+    res.t_goal = res.reachable ? (float)ball_time64(vc, L) : INFINITY;
+    res.slack = m;
+    res.shoot = gap >= min_angle && res.reachable && m > margin;
+    return res;
+}
+
+// The balls alone: one wave per frame.
+template <int KPH, bool INL>
+__global__ void __launch_bounds__(64) shot_ball_kernel(ShotLaunch launch)
+{
+    __shared__ StageLDS S;
+    const ShotArgs &a = launch.a;
+    const OneFrame &one = fresh_args<ShotLaunch>().one;
+    const int f = blockIdx.x;
+    stage_frame(a.P, INL ? one.frame : a.frames[f], INL ? one.robots : a.robots,
+                INL ? one.variants : a.variants, f, S);
+    wave_lds_sync();
+    const dpps_shot r = shot_lone<KPH>(S, a.P, (double)unif(S.bx), (double)unif(S.by), a.min_angle,
+                                       a.margin);
+    if (threadIdx.x == 0) a.ball[f] = r;
+}
+
 // Shooting decisions of one frame per workgroup: a tile of its window's
-// points, or (the first n_frames workgroups) its ball.
+// points, or (the first n_frames workgroups) its ball, as a tile of one.
 //
 // Bound by VALU issue.  What differs by position and opponent -- the shadow's
 // angles, the opponent in the shot's frame, its bounds -- has a lane per
@@ -2317,7 +2457,7 @@ __global__ void __launch_bounds__(256) shot_kernel(ShotLaunch launch)
     // The opponents in the shot's frame and their bounds: on the arrival over
     // each quarter (shaved by 2^-16) less the latest ball time there.
     const RobotK rk(P);
-    float4 fr[2];  // 16 x 32 pairs on 256 threads, 16 on 64
+    float4 fr[2];  // 16 x 32 pairs on 256 threads
     float bd[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -2368,30 +2508,37 @@ __global__ void __launch_bounds__(256) shot_kernel(ShotLaunch launch)
     for (int x = tid; x < 8 * np; x += nt) out[x] = ((const int *)H.rec)[x];
 }
 
-// Workgroups of four waves, one per tile; of one wave where only the balls are
-// asked for.
-template <int KPH>
+// Workgroups of four waves, one per frame's ball and tile; the balls alone in a
+// kernel of their own.  (With the balls beside a map by that kernel's way, maps
+// of 64 frames at K = 256 took 120.4 us a call instead of 117.8.)
+template <int KPH, bool INL>
 static void launch_shot_kph(const ShotLaunch &s, hipStream_t st)
 {
-    const dim3 grid(s.a.n_frames + (s.a.map ? s.a.n_tiles : 0)), block(s.a.map ? 256 : 64);
-    if (s.one.on)
-        hipLaunchKernelGGL((shot_kernel<KPH, true>), grid, block, 0, st, s);
+    const dim3 grid(s.a.n_frames + (s.a.map ? s.a.n_tiles : 0));
+    if (s.a.map)
+        hipLaunchKernelGGL((shot_kernel<KPH, INL>), grid, dim3(256), 0, st, s);
     else
-        hipLaunchKernelGGL((shot_kernel<KPH, false>), grid, block, 0, st, s);
+        hipLaunchKernelGGL((shot_ball_kernel<KPH, INL>), grid, dim3(64), 0, st, s);
+}
+
+template <bool INL>
+static int launch_shot_inl(const ShotLaunch &s, hipStream_t st)
+{
+    switch (s.a.P.K / 64) {
+    case 1: launch_shot_kph<2, INL>(s, st); break;
+    case 2: launch_shot_kph<4, INL>(s, st); break;
+    case 3: launch_shot_kph<6, INL>(s, st); break;
+    case 4: launch_shot_kph<8, INL>(s, st); break;
+    default: return -1;
+    }
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int launch_shot(const ShotLaunch &s, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
     if (s.a.n_frames <= 0) return 0;
-    switch (s.a.P.K / 64) {
-    case 1: launch_shot_kph<2>(s, st); break;
-    case 2: launch_shot_kph<4>(s, st); break;
-    case 3: launch_shot_kph<6>(s, st); break;
-    case 4: launch_shot_kph<8>(s, st); break;
-    default: return -1;
-    }
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    return s.one.on ? launch_shot_inl<true>(s, st) : launch_shot_inl<false>(s, st);
 }
 
 // ----------------------------------------------------------------------------
