@@ -455,6 +455,27 @@ int batch_upload(dpps_ctx *c, dpps_batch *b)
     return DPPS_OK;
 }
 
+// Own tiles of each workgroup of a persistent grid over several frames: three
+// quarters of the even share, at least one.  A pulled tile waits for the
+// counter, its window and its frame in turn (requests of 2806 and 11 011
+// points, K = 128: 69.7 us a call with every tile pulled, 60.6 with one its
+// own).  Where that wait outweighs a tile's work (K <= 128, up to 16 points),
+// up to three are all its own (9 frames of 61 x 46 points, 8 variants, K =
+// 128: 72.1 us with one of 2.5, 61.5 with two; K = 64 with two of 3.1 52.9, with
+// three 47.5; at K = 256 64.7 and 71.1), and between one and two the grid is
+// halved so that every workgroup has two (6 such frames at K = 128: 57.9 us
+// with one of 1.6, 52.5 with two; 4 at K = 64 41.6 and 33.9; 3 at K = 256 37.1
+// and 42.1).
+static int own_tiles(const dpps_ctx *c, const LaunchArgs &a, int &grid)
+{
+    if (c->p.n_samples <= 128 && a.tile_points <= 16) {
+        if (c->wg_per_cu == 0 && a.n_tiles > grid && a.n_tiles <= 2 * grid) grid = a.n_tiles / 2;
+        if (a.n_tiles / grid < 4) return a.n_tiles / grid;
+    }
+    const int even = a.n_tiles / grid, run = even - (even + 3) / 4;
+    return run > 0 ? run : even < 1 ? even : 1;
+}
+
 int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t st,
                      bool timed, const dpps_power_params *power, float *v0_out,
                      const OneFrame *one, dpps_best *best_host)
@@ -503,6 +524,7 @@ int run_batch(dpps_ctx *c, dpps_batch *b, const dpps_outputs *out, hipStream_t s
     int64_t cap = (int64_t)c->n_cu * per_cu;
     int grid = (int)(a.n_tiles < cap ? a.n_tiles : cap);
     if (!c->persistent) grid = a.n_tiles;
+    if (c->persistent && b->n_frames > 1 && grid > 0) a.n_own = own_tiles(c, a, grid);
     // one frame on a persistent grid: one best record per workgroup
     if (c->persistent && b->n_frames == 1) a.wg_records = grid;
     void *e0 = timed ? (void *)c->ev0 : nullptr, *e1 = timed ? (void *)c->ev1 : nullptr;

@@ -133,6 +133,7 @@ struct LaunchArgs {
     int32_t tile_points;
     int32_t max_variants;   // most variants of any frame (rows of the staged maps)
     int32_t persistent;
+    int32_t n_own;          // own tiles of each workgroup (several frames, with maps)
     uint32_t *counter;      // 8 persistent work counters (one per class of workgroup
                             // index mod 8); the finalize kernel resets them
     TileRec *tile_rec;      // one per tile

@@ -1117,12 +1117,10 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
     // one counter per class, so that the tiles an XCD runs together write
     // neighbouring chunks (below) and its L2 merges their lines.  C classes:
     // every class has a workgroup (a grid under 8 workgroups uses G classes).
-    // Several frames: a run of consecutive tiles (three quarters of the even
-    // share: frames differ in cost), then groups of `claim` tiles, so that a
-    // workgroup stages few frames; the chunks of a run fill whole lines by
-    // themselves.  At least one tile is its own: pulled, the first waits for the
-    // counter, its window and its frame in turn (requests of 2806 and 11 011 points,
-    // K = 128: 69.7 us a call, 60.6 with it).
+    // Several frames: a run of consecutive tiles (n_own, chosen by the host; three
+    // quarters of the even share where there are many: frames differ in cost),
+    // then groups of `claim` tiles, so that a workgroup stages few frames; the
+    // chunks of a run fill whole lines by themselves.
     // BEST, small tiles (16 points): a pulled tile waits for the counter and
     // then for its window and its frame, which cost more than the tile, so up to
     // 11 tiles a workgroup are its own (30 frames of 128 windows: 168 us a call
@@ -1140,7 +1138,7 @@ __global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLau
     const bool runs = args.persistent && args.n_frames > 1;
     const int even = n_tiles / G;
     const bool small = TP <= 16;
-    const int own = !BEST ? max(even - (even + 3) / 4, min(even, 1))
+    const int own = !BEST ? args.n_own
                           : small && even < 12 ? even : max(even / 4, min(even, 1));
     const int n_own = !args.persistent ? 1 : runs ? own : max(even - 1, 0);
     const int first = runs ? b * n_own : b, stride = runs ? 1 : G;
