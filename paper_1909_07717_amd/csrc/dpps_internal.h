@@ -251,8 +251,9 @@ int launch_search(const SearchLaunch &s, int waves_per_wg, int grid, void *strea
                   void *ev_stop);
 // Zero n 32-bit words of device memory on `stream` (a kernel, no memset).
 int launch_zero_words(uint32_t *p, int n, void *stream);
-// Resident workgroups per CU of the search kernel for this K and block size.
-int search_occupancy(int K, int waves_per_wg, int tile_points, int max_variants);
+// Resident workgroups per CU of the search kernel for this K and block size;
+// best: of the form without maps (LaunchArgs::frame_best).
+int search_occupancy(int K, int waves_per_wg, int tile_points, int max_variants, bool best = false);
 // Direction x variant search (ray kernel then its finalize) on `stream`;
 // ev_start / ev_stop (hipEvent_t or NULL) bracket the ray kernel only.
 // (cos, sin) of theta_d = 2 pi d / n for d < n into dirs (n <= 4096).

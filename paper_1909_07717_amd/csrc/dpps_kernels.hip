@@ -1070,20 +1070,26 @@ __device__ __forceinline__ int window_words(const LaunchArgs &a, bool inl, int w
 // variants) and the open angle cost a pair of points what they cost one,
 // the robot stage and the inversions cost the same per sample.  With the bounds
 // kept per quarter of the path, its arrival limits and the arguments read
-// where they are used (57-100 spilled scalars gone) the default-shape full
-// frame (8v8, 43 621 points, 32 variants, K = 256) takes 123 us instead of
-// 142 and 52.5 M VALU instructions instead of 66.9 M; 256 uneven windows at
-// 8 variants, K = 128, 3.40 ms instead of 4.42; passing power 96 us instead of 122.
-// At most 128 VGPRs, so four waves fit on each SIMD; K = 128 fits in 96 and runs
-// five (256 windows 3.56 -> 3.39 ms; at K = 64 five were slower for one small
-// frame, 16.2 -> 19.0 us, and K >= 192 does not fit).  With tiles by
-// request and runs of tiles the same launches take 115 us, 3.37 ms and 93 us.
+// where they are used the default-shape full frame (8v8, 43 621 points, 32
+// variants, K = 256) went from 142 to 123 us and from 66.9 M to 52.5 M VALU
+// instructions, 256 uneven windows at 8 variants, K = 128, from 4.42 to 3.40 ms,
+// the passing power of the full frame from 122 to 96 us; with tiles by request,
+// runs of tiles and the 16-byte LDS to 113 us, 3.25 ms and 89 us.
+// Registers: at most 128 VGPRs, so that four waves fit on each SIMD.  13 to 20
+// scalars stay spilled to lanes (57 to 100 without the late argument reads) and
+// at K = 256 18 to 27 VGPRs to scratch (K = 192: 9 to 14, K = 64: 2 or none);
+// three waves without spills took 124 us for the full frame against 118.  K =
+// 128 with maps or power runs five waves in 96 VGPRs, spilling 34 to 40 of them
+// (256 windows 3.56 -> 3.39 ms, five full frames of passing power 262 -> 244 us);
+// BEST does not (30 frames of 64 windows 132 us a call with five, 103 with four; 300
+// frames 414 and 314).  At K = 64 five were slower for one small frame, 16.2 ->
+// 19.0 us.
 // POWER: one flat pass per point at the point's own passing power (Eq. 1-2).
 // BEST: only the best record is asked for, and points that cannot hold it are
 // left out (1000 frames of 64 windows of 16 points, one flat kick: 940 -> 457
 // us, their exact fallback of 18 frames 710 -> 486).
 template <int KPH, bool POWER, bool BEST>
-__global__ void __launch_bounds__(512, KPH == 4 ? 5 : 4) search_kernel(SearchLaunch launch)
+__global__ void __launch_bounds__(512, KPH == 4 && !BEST ? 5 : 4) search_kernel(SearchLaunch launch)
 {
     const LaunchArgs &args = launch.a;
     __shared__ StageLDS S;
@@ -2797,20 +2803,29 @@ int launch_search(const SearchLaunch &s, int waves_per_wg, int grid, void *strea
     }
 }
 
-int search_occupancy(int K, int waves_per_wg, int tile_points, int max_variants)
+template <int KPL>
+static int occupancy_kpl(int block, size_t lds, bool best)
 {
     int n = 0;
-    hipError_t e = hipErrorInvalidValue;
+    const hipError_t e =
+        best ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<2 * KPL, false, true>,
+                                                            block, lds)
+             : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<2 * KPL, false, false>,
+                                                            block, lds);
+    return e == hipSuccess && n > 0 ? n : 1;
+}
+
+int search_occupancy(int K, int waves_per_wg, int tile_points, int max_variants, bool best)
+{
     const int bs = 64 * waves_per_wg;
     const size_t lds = search_lds_bytes(K, waves_per_wg, tile_points, max_variants);
     switch (K / 64) {
-    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<2, false, false>, bs, lds); break;
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<4, false, false>, bs, lds); break;
-    case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<6, false, false>, bs, lds); break;
-    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, search_kernel<8, false, false>, bs, lds); break;
-    default: break;
+    case 1: return occupancy_kpl<1>(bs, lds, best);
+    case 2: return occupancy_kpl<2>(bs, lds, best);
+    case 3: return occupancy_kpl<3>(bs, lds, best);
+    case 4: return occupancy_kpl<4>(bs, lds, best);
+    default: return 1;
     }
-    return e == hipSuccess && n > 0 ? n : 1;
 }
 
 }  // namespace dpps

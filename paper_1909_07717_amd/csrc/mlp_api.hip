@@ -622,7 +622,8 @@ static int propose(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dpps_best
     // points, two points per wave, instead of the context's shape
     const int wv = (int64_t)a.n_tiles <= (int64_t)c->n_cu ? 8 : c->waves;
     a.max_variants = b->T.max_variants;
-    int per_cu = search_occupancy(c->p.n_samples, wv, a.tile_points, a.max_variants);
+    int per_cu = search_occupancy(c->p.n_samples, wv, a.tile_points, a.max_variants,
+                                  a.frame_best != nullptr);
     int64_t cap = (int64_t)c->n_cu * per_cu;
     int grid = (int)(a.n_tiles < cap ? a.n_tiles : cap);
     if (launch_search(s, wv, grid, (void *)st, nullptr, nullptr))
@@ -681,7 +682,8 @@ static int surrogate_core(dpps_ctx *c, dpps_mlp *m, dpps_batch *b, int32_t k, dp
     a.tile_rec = m->frec;
     a.best = d_best;
     a.max_variants = b->T.max_variants;
-    const int per_cu = search_occupancy(c->p.n_samples, c->waves, a.tile_points, a.max_variants);
+    const int per_cu = search_occupancy(c->p.n_samples, c->waves, a.tile_points, a.max_variants,
+                                        a.frame_best != nullptr);
     const int64_t cap = (int64_t)c->n_cu * per_cu;
     const int grid = (int)((int64_t)a.n_tiles < cap ? a.n_tiles : cap);
     if (launch_search(s, c->waves, grid, (void *)st, nullptr, nullptr))
