@@ -2569,27 +2569,31 @@ __device__ __forceinline__ float robot_time_pt(const DevParams &P, float4 r, flo
 }
 
 // Entry parameter of the segment from c along (dx, dy) into the rectangle
-// [x0, x1] x [y0, y1] (0 when c is in it, 1 when the segment does not meet it),
-// by the slabs' entry parameters.  Unless `narrow` the segment's end lies in
-// the rectangle, so the last slab entered is the entry; a narrow rectangle may
-// be passed by, and the entry then has to lie on the edge.
+// [x0, x1] x [y0, y1] that holds its end point (slab form, FP64: a segment
+// that grazes an edge must be decided as the oracle decides it).
 __device__ __forceinline__ double slab_enter(double cx, double cy, double dx, double dy,
-                                             double x0, double x1, double y0, double y1,
-                                             bool narrow)
+                                             double x0, double x1, double y0, double y1)
 {
     // the slab's near side chosen before the one division per axis (the
     // same quotients; lanes whose dy signs differ share one division)
+    double t = 0.0;
+    if (dx != 0.0) t = fmax(t, ((dx > 0.0 ? x0 : x1) - cx) / dx);
+    if (dy != 0.0) t = fmax(t, ((dy > 0.0 ? y0 : y1) - cy) / dy);
+    return fmin(t, 1.0);
+}
+
+// The same for a rectangle that need not hold the end point: 1, the end, when
+// the segment passes it by (the entry by the slabs is then not on its edge).
+__device__ __forceinline__ double slab_enter_or_end(double cx, double cy, double dx, double dy,
+                                                    double x0, double x1, double y0, double y1)
+{
     double tx = 0.0, ty = 0.0;
     if (dx != 0.0) tx = fmax(tx, ((dx > 0.0 ? x0 : x1) - cx) / dx);
     if (dy != 0.0) ty = fmax(ty, ((dy > 0.0 ? y0 : y1) - cy) / dy);
-    const double t = fmax(tx, ty);
-    if (narrow) {
-        const double x = cx + t * dx, y = cy + t * dy;
-        const bool in_x = x >= x0 && x <= x1, in_y = y >= y0 && y <= y1;
-        const bool met = t == 0.0 ? in_x && in_y : (t == tx && in_y) || (t == ty && in_x);
-        return met ? fmin(t, 1.0) : 1.0;
-    }
-    return fmin(t, 1.0);
+    const double t = fmax(tx, ty), x = cx + t * dx, y = cy + t * dy;
+    const bool in_x = x >= x0 && x <= x1, in_y = y >= y0 && y <= y1;
+    const bool met = t == 0.0 ? in_x && in_y : (t == tx && in_y) || (t == ty && in_x);
+    return met ? fmin(t, 1.0) : 1.0;
 }
 
 // What the points of a zone share: the opponents (bit o) that can be the
@@ -2669,9 +2673,14 @@ __device__ __forceinline__ float run_eval(const StageLDS &S, const DevParams &P,
     crit[2] = fmaxf(1.0f - off / R.ang_fall, 0.0f);
     const double gxd = (double)P.goal_x - cx, hwg = (double)P.half_goal_w;
     const double dpy = hwg - cy, dqy = -hwg - cy;
-    const bool narrow = hwd < hwg;
-    const double tp_ = slab_enter(cx, cy, gxd, dpy, x0d, (double)P.goal_x, -hwd, hwd, narrow);
-    const double tq_ = slab_enter(cx, cy, gxd, dqy, x0d, (double)P.goal_x, -hwd, hwd, narrow);
+    double tp_, tq_;
+    if (hwd < hwg) {  // an area narrower than the goal
+        tp_ = slab_enter_or_end(cx, cy, gxd, dpy, x0d, (double)P.goal_x, -hwd, hwd);
+        tq_ = slab_enter_or_end(cx, cy, gxd, dqy, x0d, (double)P.goal_x, -hwd, hwd);
+    } else {
+        tp_ = slab_enter(cx, cy, gxd, dpy, x0d, (double)P.goal_x, -hwd, hwd);
+        tq_ = slab_enter(cx, cy, gxd, dqy, x0d, (double)P.goal_x, -hwd, hwd);
+    }
     const float px = (float)(cx + tp_ * gxd), py = (float)(cy + tp_ * dpy);
     const float qx = (float)(cx + tq_ * gxd), qy = (float)(cy + tq_ * dqy);
     float tP = INFINITY, tQ = INFINITY;
