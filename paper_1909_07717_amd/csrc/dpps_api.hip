@@ -1103,7 +1103,7 @@ int dpps_running_points(dpps_ctx *c, int32_t n_frames, const dpps_frame *frames,
     a.n_wins = (int32_t)b->T.wins.size();
     a.score = d_score;
     a.best = d_best;
-    if (launch_run(a, (void *)st)) return fail(DPPS_E_DEVICE, "running-point launch failed");
+    if (launch_run(a, c->n_cu, (void *)st)) return fail(DPPS_E_DEVICE, "running-point launch failed");
     return DPPS_OK;
 }
 

@@ -263,6 +263,6 @@ int launch_ray(const RayArgs &a, int waves_per_wg, int grid, void *stream, void 
 int ray_occupancy(int K, int waves_per_wg);
 // Shooting decisions: every frame's ball and (with a.map) its window points.
 int launch_shot(const ShotLaunch &s, void *stream);
-int launch_run(const RunArgs &a, void *stream);
+int launch_run(const RunArgs &a, int n_cu, void *stream);
 
 }  // namespace dpps

@@ -2712,12 +2712,12 @@ __device__ __forceinline__ float run_eval(const StageLDS &S, const DevParams &P,
 // out, squared ball distances are formed once, the marking weight once per
 // point from the nearest opponent, and the best point's criteria stay with
 // its lane instead of being computed again.  2048 frames x 4 zones (10.2 M
-// points): 315 -> 187 us.
-__global__ void __launch_bounds__(256) run_kernel(RunArgs a)
+// points): 318 -> 178 us.
+__global__ void __launch_bounds__(1024) run_kernel(RunArgs a)
 {
     __shared__ StageLDS S;
     __shared__ double ball2[DPPS_MAX_SIDE];
-    __shared__ unsigned long long red[4];
+    __shared__ unsigned long long red[16];
     const DevParams &P = a.P;
     const WinDev W = a.wins[blockIdx.x];
     stage_frame(P, a.frames[W.frame], a.robots, a.variants, W.frame, S);
@@ -2775,10 +2775,16 @@ __global__ void __launch_bounds__(256) run_kernel(RunArgs a)
     a.best[blockIdx.x] = r;
 }
 
-int launch_run(const RunArgs &a, void *stream)
+// Threads per zone: 256 where the zones fill the chip; twice and four times as
+// many for up to two zones and one a CU, where a call waits for one zone's
+// points (4 frames x 4 zones of 1200 points, 11 opponents: 29.4 us a call with
+// 256, 22.4 with 512, 20.1 with 1024; one opponent 20.4, 16.7 and 16.2; 100
+// frames, 400 zones: 52.0, 45.6 with 512; 130 frames, 520 zones, 53.5 with any).
+int launch_run(const RunArgs &a, int n_cu, void *stream)
 {
+    const int threads = a.n_wins <= n_cu ? 1024 : a.n_wins <= 2 * n_cu ? 512 : 256;
     if (a.n_wins > 0)
-        hipLaunchKernelGGL(run_kernel, dim3(a.n_wins), dim3(256), 0, (hipStream_t)stream, a);
+        hipLaunchKernelGGL(run_kernel, dim3(a.n_wins), dim3(threads), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
