@@ -145,7 +145,8 @@ int dpps_layout(const dpps_params *p, int32_t n_frames, dpps_frame *frames,
 /* Device bytes the context's memory needs to hold one dpps_search_batch
  * request of these frames with tile_points points per tile (0: 8): its
  * tables, per-tile records and per-frame best records, without the
- * caller-owned outputs.  Host-only.  A context's memory grows to a quarter
+ * caller-owned outputs (a context whose tile size is not set may take larger
+ * tiles and need less).  Host-only.  A context's memory grows to a quarter
  * above the largest request so far (rounded up to 64 KiB) when its budget
  * allows, else to the request's size exactly. */
 int dpps_request_bytes(const dpps_params *p, int32_t n_frames, const dpps_frame *frames,
@@ -214,7 +215,12 @@ int64_t dpps_batch_points(const dpps_batch *b);
  * workgroup (1, 2, 4 or 8); 0 keeps the current value.  wg_per_cu: 1..32
  * persistent workgroups per compute unit, -2 persistent with as many as fit
  * (the default), -1 one workgroup per tile (no persistence), 0 keep.
- * dpps_get_launch reports the resolved workgroups per CU (-1: one per tile). */
+ * Until a tile size is set (here or by dpps_autotune), requests of host frames
+ * (dpps_search, dpps_search_batch, dpps_search_power) take 8, 16, 32 or 64
+ * points per tile by their size; resident batches take the context's 8.
+ * dpps_get_launch reports the context's tile size and the resolved workgroups
+ * per CU (-1: one per tile; as many as fit: for frames of 64 variants, a launch
+ * of fewer may fit more, and small batches may use fewer). */
 int dpps_set_launch(dpps_ctx *c, int32_t tile_points, int32_t waves_per_wg, int32_t wg_per_cu);
 int dpps_get_launch(const dpps_ctx *c, int32_t *tile_points, int32_t *waves_per_wg,
                     int32_t *wg_per_cu);

@@ -193,7 +193,7 @@ struct RayArgs {
     const FrameDev *frames;
     const dpps_robot *robots;
     const dpps_variant *variants;
-    const TileDev *tiles;   // win = frame, p0 = first direction of the tile
+    const TileDev *tiles;   // win = frame, at = first direction of the tile
     const double2 *dirs;    // (cos, sin) of each kick direction (launch_ray_dirs)
     int32_t n_tiles;
     int32_t n_frames;
@@ -220,8 +220,7 @@ struct ShotArgs {
     const TileDev *tiles;
     int32_t n_tiles;
     int32_t n_frames;
-    int32_t tile_points;
-    float v_shot, min_angle, margin;
+    float min_angle, margin;
     dpps_shot *ball;        // one record per frame
     dpps_shot *map;         // one record per window point (may be NULL)
 };

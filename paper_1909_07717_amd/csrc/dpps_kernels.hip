@@ -622,7 +622,10 @@ __device__ __forceinline__ float vcrit(float T, float s, float s_icA, float s_ic
     const float Q = fmaf(half_ar, T2, s);
     const bool stop = s_icA <= T2;
     const bool fast = s_icB >= T2;
-    // (negative, so a NaN root, in the other regimes only)
+    // (Never negative for a flat kick in this regime.  A chip's is when its roll
+    // is a few 1e-5 of its flight, at 100 m/s^2 or 1.57 rad: the root is then no
+    // number and the chip's minimum with the landing limit takes that limit,
+    // within 6e-5 of the true speed.)
     const float m_slow = fmaf(alpha, Q, hbeta2 * T2);
     const float d_slow = fmaf(hbeta, T, hsqrt(m_slow));
     const float N = fast ? (CHIP ? s : fmaf(hfast, T2, s)) : Q;
@@ -1655,7 +1658,7 @@ __device__ __forceinline__ float half_min(float x)
     return fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// Least / greatest value over the wave (DPP within each row of 16 lanes,
+// Least value over the wave (DPP within each row of 16 lanes,
 // then the four rows), on every lane.
 __device__ __forceinline__ float wave_min_dpp(float x)
 {
@@ -1665,15 +1668,6 @@ __device__ __forceinline__ float wave_min_dpp(float x)
     x = fminf(x, row_mirror(x));
     return fminf(fminf(readlane_f(x, 0), readlane_f(x, 16)),
                  fminf(readlane_f(x, 32), readlane_f(x, 48)));
-}
-__device__ __forceinline__ float wave_max_dpp(float x)
-{
-    x = fmaxf(x, quad_xor<1>(x));
-    x = fmaxf(x, quad_xor<2>(x));
-    x = fmaxf(x, half_mirror(x));
-    x = fmaxf(x, row_mirror(x));
-    return fmaxf(fmaxf(readlane_f(x, 0), readlane_f(x, 16)),
-                 fmaxf(readlane_f(x, 32), readlane_f(x, 48)));
 }
 
 // Covered length of the union of the intervals [s, e] held by the lanes of
@@ -1728,7 +1722,7 @@ __device__ __forceinline__ float group_cover(float s, float e, bool has, float h
 // Open goal angle at up to 64 / GS points at once: lane GS g + o looks at
 // point g (its own cx, cy, and the point's goal-post angles lo, hi) and
 // opponent o (GS = 16 for up to 16 opponents, 8 for up to 8).  The same
-// construction as open_angle within each group of GS lanes; returns on every
+// construction as open_angle_pair within each group of GS lanes; returns on every
 // lane the angle of its group's point.
 template <int GS>
 __device__ float open_angle_groups(const StageLDS &S, const DevParams &P, float cx, float cy,
