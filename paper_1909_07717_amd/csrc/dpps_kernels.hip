@@ -622,11 +622,11 @@ __device__ __forceinline__ float vcrit(float T, float s, float s_icA, float s_ic
     const float Q = fmaf(half_ar, T2, s);
     const bool stop = s_icA <= T2;
     const bool fast = s_icB >= T2;
-    // (Never negative for a flat kick in this regime.  A chip's is when its roll
-    // is a few 1e-5 of its flight, at 100 m/s^2 or 1.57 rad: the root is then no
-    // number and the chip's minimum with the landing limit takes that limit,
-    // within 6e-5 of the true speed.)
-    const float m_slow = fmaf(alpha, Q, hbeta2 * T2);
+    // Never negative for a flat kick in this regime.  A chip's can be, by
+    // rounding, where its roll is a few 1e-5 of its flight (at 100 m/s^2 or 1.57
+    // rad): no root of a negative number may reach the minima that follow.
+    const float m = fmaf(alpha, Q, hbeta2 * T2);
+    const float m_slow = CHIP ? fmaxf(m, 0.0f) : m;
     const float d_slow = fmaf(hbeta, T, hsqrt(m_slow));
     const float N = fast ? (CHIP ? s : fmaf(hfast, T2, s)) : Q;
     const float D = fast ? (CHIP ? pfast * T : T) : d_slow;
